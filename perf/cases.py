@@ -213,9 +213,10 @@ def _book(case, seed, index=0) -> Book:
             # a drawn book's layer terms follow its size, so that it pays in some years
             hits = case["elts"] * case["rows"] / case["catalogue"]
             few = 1.0 if case["su"] else 0.1       # means alone seldom reach the retentions
-            by = [few * min(1.0, hits / 3.2)] * 2 + [few * min(1.0, hits * case["lam"] / 3200.0)] * 2
-            v = np.exp(rng.uniform(math.log(0.05), 0.0, size=4))
-            t = [_f32(x * f * float(w)) for x, f, w in zip(t, by, v)]
+            occ, agg = min(1.0, hits / 3.2), min(1.0, hits * case["lam"] / 3200.0)
+            v = np.exp(rng.uniform(math.log(0.1), 0.0, size=2))
+            t = [_f32(t[0] * few * occ * float(v[0])), t[1],
+                 _f32(t[2] * few * agg * float(v[1])), _f32(t[3] * 4.0 * agg)]
         elif case.get("terms", "random") == "random":
             # retentions and limits of a programme's layers lie decades apart
             v = np.exp(rng.uniform(math.log(1e5), math.log(1e9), size=4)) * s
