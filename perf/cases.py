@@ -216,7 +216,7 @@ def _book(case, seed, index=0) -> Book:
             occ, agg = min(1.0, hits / 3.2), min(1.0, hits * case["lam"] / 3200.0)
             v = np.exp(rng.uniform(math.log(0.1), 0.0, size=2))
             t = [_f32(t[0] * few * occ * float(v[0])), t[1],
-                 _f32(t[2] * few * agg * float(v[1])), _f32(t[3] * 4.0 * agg)]
+                 _f32(t[2] * few * agg * float(v[1])), _f32(LIMITS["agg_l"] * 4.0 * agg)]
         elif case.get("terms", "random") == "random":
             # retentions and limits of a programme's layers lie decades apart
             v = np.exp(rng.uniform(math.log(1e5), math.log(1e9), size=4)) * s
