@@ -56,6 +56,20 @@ size_t run_scratch_need(int64_t trial_count) {
     return 256 + ((size_t)(trial_count > 0 ? trial_count : 1) * sizeof(int32_t) + 255) / 256 * 256;
 }
 
+// The normal deviate below which z < band (or above whose mirror 1 - z < band):
+// mixed draws compare their deviate with it instead of forming z.  At most
+// kDevMax, the end of the deviate segments.
+float band_deviate(float band) {
+    if (band == kDefaultTailBand) return 5.2947f;      // Phi(-5.2947) = 2^-24
+    if (!(band < 0.5f)) return 0.0f;
+    double lo = 0.0, hi = (double)kDevMax;
+    for (int i = 0; i < 40; ++i) {
+        const double v = 0.5 * (lo + hi);
+        if (0.5 * std::erfc(v * 0.70710678118654752) < (double)band) hi = v; else lo = v;
+    }
+    return (float)hi;
+}
+
 // The FP32 pass hands the trials it cannot finish to the FP64-capable pass
 // through scratch: a counter at the start, the trial list 256 bytes in.  The
 // second pass takes up to as many wavefronts as the first keeps resident
@@ -72,6 +86,7 @@ void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_op
     } else {
         p->f64_iters = kF64QuantileIters;
     }
+    p->dev_band = band_deviate(p->tail_band);
 }
 
 // The primary-uncertainty pass of one portfolio over trials [begin, begin +
@@ -170,7 +185,8 @@ ara_status plan(ara_context *ctx, const ara_portfolio_desc *d, int32_t n_cat, La
     L->row_shape = o; o += su ? align256(sizeof(uint32_t) * (size_t)(rows ? rows : 1)) : 0;
     L->shape_keys = o; o += su ? align256(sizeof(unsigned long long) * kShapeSlots * (nl ? nl : 1)) : 0;
     L->shape_tab = o;
-    o += su ? align256(sizeof(float) * kShapeStride * kShapeSlots * (size_t)(nl ? nl : 1)) : 0;
+    o += su ? align256(sizeof(float) * (kShapeStride * kShapeSlots * (size_t)(nl ? nl : 1) + kNormFloats))
+            : 0;
     const size_t nw = ((size_t)n_cat + 31) / 32;
     const bool pu = !d->su_enabled;
     L->otab = o; o += pu ? align256(sizeof(float) * (size_t)nl * n_cat) : 0;
@@ -271,7 +287,7 @@ uint32_t fbits(float v) {
 ara_status one_shape_table(ara_context *ctx, float a, float b, hipStream_t s, void **mem,
                            float **tab) {
     *mem = nullptr;
-    const size_t bytes = 256 + sizeof(float) * kShapeStride;
+    const size_t bytes = 256 + sizeof(float) * (kShapeStride + kNormFloats);
     ARA_HIP(ctx, hipMalloc(mem, bytes));
     const unsigned long long key = ((unsigned long long)fbits(a) << 32) | fbits(b);
     ARA_HIP(ctx, hipMemcpyAsync(*mem, &key, sizeof key, hipMemcpyHostToDevice, s));
@@ -928,6 +944,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
     B.n_pf = n_su;
     B.tile = c.trial_tile;
     B.tail_band = o.tail_band;
+    B.dev_band = band_deviate(o.tail_band);
     B.trial_major = trial_major ? 1 : 0;
     B.n_items = trial_major ? ((o.trial_count + c.trial_tile - 1) / c.trial_tile) * (int64_t)n_su
                             : items;

@@ -106,18 +106,35 @@ constexpr int kF64QuantileIters = 400;
 
 // Beta shapes shared by many rows.  Each layer has kShapeSlots slots; the
 // first distinct (alpha, beta) pairs of its rows on the FP32 quantile path
-// take one each.  A slot holds, for each half of the draw grid (z <= 1/2 and
-// z > 1/2, with p = min(z, 1 - z)), the logit log(x / (1 - x)) of the
-// quantile x at kShapeK points evenly spaced in t = sqrt(-2 ln p) over
-// [sqrt(2 ln 2), sqrt(48 ln 2)] (p from 1/2 down to 2^-24): linear
-// interpolation in t starts the quantile within ~2.2e-4 of its root for every
-// shape of the FP32 domain, close enough for a single Halley step.
+// take one each.  A slot holds the quantile itself as piecewise polynomials of
+// degree 7 (8 FP32 coefficients, one 32-byte segment), interpolated in FP64 at
+// the Chebyshev points of each segment when the portfolio is loaded:
+//  * by draw: the grid integer p = min(j, 2^24 - j) (z = j 2^-24) picks the
+//    half (z <= 1/2 or above) and the octave [2^e, 2^(e+1)), its mantissa is
+//    the local coordinate d = m - 1.5 in [-1/2, 1/2), both exact in FP32;
+//  * by normal deviate v = Phi^-1(z) (rows of the two-normal mix, which never
+//    form z): segments of width 1/2 around i / 2, |i| <= kDevHalf, with the
+//    local coordinate d = 2 v - i.
+// Over FP32-evaluated draws of shapes across [1, 32]^2 the error is at most
+// 2.4e-7 (by draw) and 3.1e-7 (by deviate) of max(root, mean); a host
+// emulation of the iteration it replaced peaked at 1.6e-6 there.  Octaves and
+// half-unit steps are the widest segments that degree 7 holds to that; most
+// draws fall in a few of them, so the 64 lanes of a batch touch a handful of
+// cache lines (a one-segment-per-lane gather over a larger table was slower
+// than the iteration).
 constexpr int kShapeSlots = 16;
-constexpr int kShapeK = 128;
-// floats per slot: the two halves, then (alpha, beta, log2 B(alpha, beta), 0)
-constexpr int kShapeStride = 2 * kShapeK + 4;
-constexpr double kShapeTLo = 1.1774100225154747;   // sqrt(2 ln 2)
-constexpr double kShapeTHi = 5.768107546403532;    // sqrt(48 ln 2)
+constexpr int kSegCoefs = 8;
+constexpr int kOctaves = 23;                 // p = 1 .. 2^23 - 1
+constexpr int kDevHalf = 11;
+constexpr int kDevSegs = 2 * kDevHalf + 1;
+constexpr float kDevMax = 5.7f;              // |v| the deviate segments serve
+// floats per slot: (alpha, beta, log2 B(alpha, beta), 0) in the first segment's
+// space, the octaves of the lower then the upper half, the deviate segments
+constexpr int kSlotOct = kSegCoefs;
+constexpr int kSlotDev = kSlotOct + 2 * kOctaves * kSegCoefs;
+constexpr int kShapeStride = kSlotDev + kDevSegs * kSegCoefs;
+// after a portfolio's slots: Phi^-1(p 2^-24) by octave of p, the same segments
+constexpr int kNormFloats = kOctaves * kSegCoefs;
 
 }  // namespace ara
 
@@ -154,7 +171,7 @@ struct ara_portfolio {
     double *d_row_lnb;
     uint32_t *d_row_shape;     // per row: 1 + its shape slot, or 0
     unsigned long long *d_shape_keys;   // [layer][kShapeSlots]: (alpha, beta) bits, 0 = unused
-    float *d_shape_tab;        // [layer][kShapeSlots][kShapeStride]
+    float *d_shape_tab;        // [layer][kShapeSlots][kShapeStride], then [kNormFloats]
     float *d_otab;
     uint32_t *d_sp_bits;       // per layer [nw]: bitmap of the non-zero otab entries
     uint32_t *d_sp_rank;       // per layer [nw + 1]: set bits before each word

@@ -45,6 +45,7 @@ struct SuLaunch {
     const double *row_lnb;
     uint64_t seed;
     float tail_band;
+    float dev_band;           // the band's normal deviate (see SuArgs)
     void *ylt_layers;
     void *ylt_pf;
     int64_t *hits;
@@ -90,6 +91,7 @@ struct BatchArgs {
     int32_t n_pf;
     int32_t tile;                       // trials per work item
     float tail_band;
+    float dev_band;                     // the band's normal deviate
     int32_t trial_major;                // 1: one common range, items (tile, portfolio)
     int64_t n_items;                    // work items
     unsigned long long *counter;        // work-item counter

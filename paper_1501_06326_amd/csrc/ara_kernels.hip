@@ -19,7 +19,8 @@
 //        CDF and applies the ELT terms on real work (the paper's
 //        "convergence switching" idea applied to SIMD lanes).  A trial with
 //        a hit that needs the FP64 quantile (tail band, shapes outside the
-//        FP32 domain, the two-normal mix, FP32 non-convergence) is handed to
+//        FP32 domain, the two-normal mix of shapes without a slot, FP32
+//        non-convergence) is handed to
 //        k_ara_su_redo, which runs it again with the FP64 path in place
 //        (k_ara_su_redo4: the same code in a 4-wavefront register budget,
 //        for portfolios with FP64-quantile rows and no mixed rows).
@@ -703,6 +704,7 @@ struct SuArgs {
     const uint32_t *row_meta;
     const double *row_lnb;
     float tail_band;
+    float dev_band;           // |Phi^-1(z)| from which a mixed draw takes the FP64 quantile
     void *ylt_layers;
     void *ylt_pf;
     int64_t *hits;
@@ -711,7 +713,8 @@ struct SuArgs {
     int32_t *redo;            // trials (relative index) handed to the FP64-capable pass
     uint32_t *redo_count;
     int32_t f64_iters;        // step limit of the FP64 quantile
-    const float *shape_tab;   // the portfolio's shape tables ([layer][kShapeSlots][kShapeStride])
+    const float *shape_tab;   // the portfolio's shape tables ([layer][kShapeSlots][kShapeStride],
+                              // then the normal segments)
     const uint32_t *row_shape;   // per row: 1 + its shape slot, or 0 (the diagnostic pass)
     void *occ_view;           // occurrence view, written by the DIAG and OCC instantiations
     int64_t occ_stride;
@@ -773,6 +776,7 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
     const int64_t o0 = A.off[ti];
     const int64_t n = A.off[ti + 1] - o0;
     double pf_sum = 0.0;
+    const float *norm = A.shape_tab + (size_t)A.n_layers * kShapeSlots * kShapeStride;
 
     for (int l = 0; l < A.n_layers; ++l) {
         const LayerDev L = A.layers[l];
@@ -810,18 +814,17 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
                     // the fast passes (row indexes the paying rows), the per-row
                     // arrays in the diagnostic pass (row indexes all rows)
                     uint32_t meta, orow, shape;
-                    RowQ q;
-                    float cfrac;
+                    float scale, cfrac;
                     if (DIAG) {
                         meta = A.row_meta[row];
-                        q = A.rowq[row];
+                        scale = A.rowq[row].scale;
                         cfrac = A.row_cfrac[row];
                         orow = row;
                         shape = A.row_shape[row];
                     } else {
                         const RowF F = A.rowf[row];
                         meta = F.meta;
-                        q.scale = F.scale;
+                        scale = F.scale;
                         orow = (uint32_t)rb0 + rowf_row(F);
                         shape = rowf_shape(F);
                         cfrac = F.cfrac;
@@ -830,23 +833,6 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
                     const float *tab =
                         shape ? A.shape_tab + ((size_t)l * kShapeSlots + (shape - 1u)) * kShapeStride
                               : nullptr;
-                    if (!DIAG) {
-                        // Beta parameters: the slot's (the lanes of a batch mostly share
-                        // one), else the row's own
-                        if (tab) {
-                            const float4 h = *reinterpret_cast<const float4 *>(tab + 2 * kShapeK);
-                            q.a = h.x;
-                            q.b = h.y;
-                            q.lnb = h.z;
-                        } else if (!(meta & ROW_DET)) {
-                            const RowQ r = A.rowq[orow];
-                            q.a = r.a;
-                            q.b = r.b;
-                            q.lnb = r.lnb;
-                        } else {
-                            q.a = q.b = q.lnb = 0.0f;
-                        }
-                    }
                     const uint32_t ei = meta & 0xffffu;
                     // the layer's ELT record: an LDS read when the layer's records
                     // are staged (the global read is a different instruction, so the
@@ -865,13 +851,17 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
                     }
                     float loss = 0.0f;
                     if (meta & ROW_DET) {
-                        loss = q.scale;
-                    } else if (!REDO && (meta & (ROW_F64 | ROW_CORR))) {
-                        // shapes outside the FP32 domain and the two-normal mix
-                        // (whose special functions would inflate this pass's
-                        // register budget: inlined here they spill 387
-                        // registers at 7 waves per SIMD) are left to the
-                        // second pass
+                        loss = scale;
+                    } else if (DIAG && (scale <= ed.retention || ed.limit == 0.0f ||
+                                        ed.share == 0.0f)) {
+                        // a row that cannot pay (row_cannot_pay) adds exactly 0
+                        // whatever it draws
+                    } else if (!REDO && ((meta & ROW_F64) || ((meta & ROW_CORR) && !tab))) {
+                        // shapes outside the FP32 domain, and the two-normal mix
+                        // of shapes without a slot (its special functions would
+                        // inflate this pass's register budget: inlined here they
+                        // spill 387 registers at 7 waves per SIMD), are left to
+                        // the second pass
                         defer = true;
                     } else {
                         uint32_t jI, jC;
@@ -879,23 +869,52 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
                             L.keying == ARA_KEYING_PAPER ? (uint32_t)A.ev[o0 + seg + kl] : 0u;
                         draw_j(meta, L.keying, (uint32_t)(seg + kl), i_abs, ed.elt_id,
                                L.program_id, ev, keys, &jI, &jC);
-                        float z, zc;
-                        if (REDO) {
-                            hit_z<float>(meta, jI, jC, cfrac, &z, &zc);
-                        } else {
-                            const uint32_t j = (meta & ROW_CONLY) ? jC : jI;
-                            z = (float)j * 5.9604644775390625e-08f;
-                            zc = (float)(16777216u - j) * 5.9604644775390625e-08f;
-                        }
-                        bool need64 = (meta & ROW_F64) || fminf(z, zc) < A.tail_band;
-                        if (!need64) {
-                            bool ok;
-                            const float x = beta_quantile32(q.a, q.b, q.lnb, meta_na(meta),
-                                                            meta_nb(meta), z, zc, tab, &ok);
-                            if (ok) loss = q.scale * x; else need64 = true;
+                        bool need64 = (meta & ROW_F64) != 0;
+                        if (tab) {
+                            // the slot's segments; a mixed draw goes from the two
+                            // normal deviates to the quantile without forming z.
+                            // About 25 instructions where a Halley step and its
+                            // continued fraction took 120: 12.75 -> 10.98 ms for
+                            // 1.24e9 draws (1M trials, 16 ELTs), which the walk over
+                            // the occurrences now sets; mixed rows, once redone
+                            // whole in the second pass, 3.93 -> 0.62 ms for 40,003
+                            // trials.
+                            float x;
+                            if (meta & ROW_CORR) {
+                                const float wi = 1.0f - cfrac;
+                                const float n2 = fmaf(wi, wi, cfrac * cfrac);
+                                const float v = fmaf(norm_dev(norm, jI), wi,
+                                                     norm_dev(norm, jC) * cfrac) * rsqrtf(n2);
+                                need64 = !(fabsf(v) < A.dev_band);
+                                x = slot_quantile_dev(tab, v);
+                            } else {
+                                const uint32_t j = (meta & ROW_CONLY) ? jC : jI;
+                                need64 = (float)min(j, 16777216u - j) * 5.9604644775390625e-08f <
+                                         A.tail_band;
+                                x = slot_quantile(tab, j);
+                            }
+                            loss = scale * x;
+                        } else if (!need64) {
+                            const RowQ q = A.rowq[orow];
+                            float z, zc;
+                            if (REDO) {
+                                hit_z<float>(meta, jI, jC, cfrac, &z, &zc);
+                            } else {
+                                const uint32_t j = (meta & ROW_CONLY) ? jC : jI;
+                                z = (float)j * 5.9604644775390625e-08f;
+                                zc = (float)(16777216u - j) * 5.9604644775390625e-08f;
+                            }
+                            need64 = fminf(z, zc) < A.tail_band;
+                            if (!need64) {
+                                bool ok;
+                                const float x = beta_quantile32(q.a, q.b, q.lnb, meta_na(meta),
+                                                                meta_nb(meta), z, zc, &ok);
+                                if (ok) loss = scale * x; else need64 = true;
+                            }
                         }
                         if (need64) {
                             if (REDO) {
+                                const RowQ q = A.rowq[orow];
                                 double z64, zc64;
                                 hit_z<double>(meta, jI, jC, (double)cfrac, &z64, &zc64);
                                 bool ok;
@@ -903,7 +922,7 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
                                                                  A.row_lnb[orow], z64, zc64,
                                                                  A.f64_iters, &ok);
                                 if (!ok) report(A.status, ARA_E_NUMERIC, ti, seg + kl, ed.elt_id);
-                                loss = (float)((double)q.scale * x);
+                                loss = (float)((double)scale * x);
                             } else {
                                 defer = true;
                             }
@@ -1104,6 +1123,7 @@ __device__ __forceinline__ void batch_view(const BatchArgs &B, int p, SuArgs &A,
     A.row_meta = P.row_meta;
     A.row_lnb = P.row_lnb;
     A.tail_band = B.tail_band;
+    A.dev_band = B.dev_band;
     A.ylt_layers = P.ylt_layers;
     A.ylt_pf = P.ylt_pf;
     A.hits = nullptr;
@@ -1264,8 +1284,12 @@ __global__ __launch_bounds__(64) void k_debug_quantile(int64_t n, const float *_
         if (na == 0 || nb == 0) use64 = true;
         else {
             bool ok;
-            r = beta_quantile32(A, B, (float)(lnb * 1.4426950408889634), na, nb, zf, zcf, tab,
-                                &ok);
+            if (tab) {
+                r = slot_quantile(tab, min((uint32_t)(z[j] * 16777216.0) | 1u, 16777215u));
+                ok = true;
+            } else {
+                r = beta_quantile32(A, B, (float)(lnb * 1.4426950408889634), na, nb, zf, zcf, &ok);
+            }
             if (!ok) use64 = true;
         }
     }
@@ -1405,7 +1429,7 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
     A.rowq = p.rowq; A.rowf = p.rowf; A.row_mean = p.row_mean; A.row_cfrac = p.row_cfrac;
     A.row_meta = p.row_meta;
     A.row_lnb = p.row_lnb;
-    A.tail_band = p.tail_band; A.ylt_layers = p.ylt_layers; A.ylt_pf = p.ylt_pf;
+    A.tail_band = p.tail_band; A.dev_band = p.dev_band; A.ylt_layers = p.ylt_layers; A.ylt_pf = p.ylt_pf;
     A.hits = p.hits; A.hit_chk = p.hit_chk; A.status = p.status;
     A.redo = p.redo; A.redo_count = p.redo_count; A.f64_iters = p.f64_iters;
     A.shape_tab = p.shape_tab; A.row_shape = p.row_shape;
@@ -1581,20 +1605,36 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
     }
 }
 
-// The tables of the used slots: one block per slot, one thread per point.
-__global__ __launch_bounds__(2 * kShapeK) void k_shape_tables(const unsigned long long *__restrict__ keys,
-                                                              float *__restrict__ tab) {
+// The segments of the used slots, and after them the normal segments: one
+// block per slot, one thread per interpolation point, then one per segment.
+constexpr int kSlotSegs = 2 * kOctaves + kDevSegs;
+
+__global__ __launch_bounds__(kSlotSegs *kSegCoefs) void k_shape_tables(
+    const unsigned long long *__restrict__ keys, int32_t n_slots, float *__restrict__ tab) {
+    __shared__ double y[kSlotSegs * kSegCoefs];
+    const int seg = threadIdx.x / kSegCoefs, q = threadIdx.x % kSegCoefs;
+    float *slot = tab + (size_t)blockIdx.x * kShapeStride;
+    if ((int)blockIdx.x == n_slots) {
+        // Phi^-1 on the lower half: -sqrt(2) erfcinv(2 z)
+        if (seg < kOctaves)
+            y[threadIdx.x] = -1.4142135623730951 * erfcinv(ldexp(1.5 + seg_node(q), seg - 23));
+        __syncthreads();
+        if ((int)threadIdx.x < kOctaves)
+            seg_fit(y + threadIdx.x * kSegCoefs, slot + threadIdx.x * kSegCoefs);
+        return;
+    }
     const unsigned long long key = keys[blockIdx.x];
     if (key == 0ull) return;
     const double a = (double)__uint_as_float((uint32_t)(key >> 32));
     const double b = (double)__uint_as_float((uint32_t)key);
     const double lnb = lgamma(a) + lgamma(b) - lgamma(a + b);
-    const int upper = threadIdx.x / kShapeK, k = threadIdx.x % kShapeK;
-    float *slot = tab + (size_t)blockIdx.x * kShapeStride;
-    slot[threadIdx.x] = shape_table_logit(a, b, lnb, upper, k);
+    y[threadIdx.x] = slot_point(a, b, lnb, seg, q);
+    __syncthreads();
+    if ((int)threadIdx.x < kSlotSegs)
+        seg_fit(y + threadIdx.x * kSegCoefs, slot + kSlotOct + threadIdx.x * kSegCoefs);
     // the Beta parameters of the slot's rows, as the row fit computes them
     if (threadIdx.x == 0)
-        *reinterpret_cast<float4 *>(slot + 2 * kShapeK) =
+        *reinterpret_cast<float4 *>(slot) =
             make_float4((float)a, (float)b, (float)(lnb * 1.4426950408889634), 0.0f);
 }
 
@@ -1611,9 +1651,8 @@ hipError_t launch_shape_collect(RowF *rowf, const RowQ *rowq, int64_t row_base, 
 
 hipError_t launch_shape_tables(const unsigned long long *keys, int64_t n_slots, float *tab,
                                hipStream_t s) {
-    if (n_slots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_shape_tables, dim3((unsigned)n_slots), dim3(2 * kShapeK), 0, s, keys,
-                       tab);
+    hipLaunchKernelGGL(k_shape_tables, dim3((unsigned)n_slots + 1), dim3(kSlotSegs * kSegCoefs), 0,
+                       s, keys, (int32_t)n_slots, tab);
     return hipGetLastError();
 }
 

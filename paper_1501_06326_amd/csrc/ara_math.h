@@ -184,22 +184,50 @@ __device__ __forceinline__ float beta_guess32(float a, float b, float z, float z
     return a * rcp_f(a + b * __expf(2.0f * w));
 }
 
-// Starting point from a shape table (the layout is described with
-// kShapeSlots): the logit of the quantile, interpolated linearly in
-// t = sqrt(-2 ln p) between the two table points around the draw, on the
-// table half of its z.  z is an odd multiple of 2^-24, so p = min(z, 1 - z)
-// lies in [2^-24, 1/2) and t inside the table's range.
-__device__ __forceinline__ float shape_guess_logit(const float *tab, float z, float zc) {
-    const bool upper = z > 0.5f;
-    const float p = upper ? zc : z;
-    const float t = sqrtf(-2.0f * __logf(p));
-    const float inv_h = (float)((kShapeK - 1) / (kShapeTHi - kShapeTLo));
-    const float u = fminf(fmaxf((t - (float)kShapeTLo) * inv_h, 0.0f), (float)(kShapeK - 1));
-    const int i = min((int)u, kShapeK - 2);
-    const float f = u - (float)i;
-    const float *T = tab + (upper ? kShapeK : 0) + i;
-    const float l0 = T[0], l1 = T[1];
-    return fmaf(f, l1 - l0, l0);
+// One polynomial segment (see kShapeSlots) at its local coordinate.
+__device__ __forceinline__ float seg_poly(const float *c, float d) {
+    const float4 lo = *reinterpret_cast<const float4 *>(c);
+    const float4 hi = *reinterpret_cast<const float4 *>(c + 4);
+    float r = fmaf(hi.w, d, hi.z);
+    r = fmaf(r, d, hi.y);
+    r = fmaf(r, d, hi.x);
+    r = fmaf(r, d, lo.w);
+    r = fmaf(r, d, lo.z);
+    r = fmaf(r, d, lo.y);
+    return fmaf(r, d, lo.x);
+}
+
+// Octave and mantissa of p = min(j, 2^24 - j) for an odd grid integer j: the
+// conversion is exact, so the local coordinate carries no rounding.
+__device__ __forceinline__ int grid_octave(uint32_t j, bool *upper, float *d) {
+    *upper = j > 8388608u;
+    const uint32_t bits = __float_as_uint((float)(*upper ? 16777216u - j : j));
+    *d = __uint_as_float((bits & 0x7fffffu) | 0x3f800000u) - 1.5f;
+    return (int)(bits >> 23) - 127;
+}
+
+// The quantile of a slot's shape at the draw z = j 2^-24.
+__device__ __forceinline__ float slot_quantile(const float *slot, uint32_t j) {
+    bool upper;
+    float d;
+    const int e = grid_octave(j, &upper, &d);
+    return seg_poly(slot + kSlotOct + kSegCoefs * (e + (upper ? kOctaves : 0)), d);
+}
+
+// Phi^-1(j 2^-24) from the normal segments.
+__device__ __forceinline__ float norm_dev(const float *norm, uint32_t j) {
+    bool upper;
+    float d;
+    const int e = grid_octave(j, &upper, &d);
+    const float v = seg_poly(norm + kSegCoefs * e, d);
+    return upper ? -v : v;
+}
+
+// The quantile of a slot's shape at z = Phi(v), |v| <= kDevMax.
+__device__ __forceinline__ float slot_quantile_dev(const float *slot, float v) {
+    const float i = rintf(2.0f * v);
+    const int seg = min(max((int)i + kDevHalf, 0), kDevSegs - 1);
+    return seg_poly(slot + kSlotDev + kSegCoefs * seg, fmaf(2.0f, v, -i));
 }
 
 // I_x(a,b) (*I) and 1 - I_x(a,b) (*Ic), each on the side where it is
@@ -237,27 +265,11 @@ __device__ __forceinline__ void beta_inc32(float a, float b, float lnb2, int na,
 // step^3); a lane keeps the iterate of its own first such step, so its
 // result does not depend on how many iterations the wavefront runs.  Returns
 // false in *ok if it did not converge (the caller then uses the FP64 path).
-// With a shape table (tab, the row's slot; null without) the start comes
-// from the table instead, within ~2.2e-4 of the root: the first iteration
-// then takes every term and its step already decides convergence, so one
-// Halley step is the usual cost.  Whether a lane has a table depends on its
-// row only, so its result still does not depend on the lanes beside it.
 __device__ __forceinline__ float beta_quantile32(float a, float b, float lnb2, int na, int nb,
-                                                 float z, float zc, const float *tab, bool *ok) {
-    const bool full0 = tab != nullptr;
-    float x0;
-    bool mirror;
-    if (full0) {
-        // the small side of the root straight from the logit L = ln(x/(1-x)):
-        // x = 1/(1+e^-L) = 1/(1+e^|L|) when L <= 0, else 1 - x = 1/(1+e^L)
-        const float L = shape_guess_logit(tab, z, zc);
-        mirror = L > 0.0f;
-        x0 = rcp_f(1.0f + __expf(fabsf(L)));
-    } else {
-        x0 = beta_guess32(a, b, z, zc);
-        mirror = x0 > 0.5f;
-        if (mirror) x0 = 1.0f - x0;
-    }
+                                                 float z, float zc, bool *ok) {
+    float x0 = beta_guess32(a, b, z, zc);
+    const bool mirror = x0 > 0.5f;
+    if (mirror) x0 = 1.0f - x0;
     float A = a, B = b, Z = z, ZC = zc;
     int NA = na, NB = nb;
     if (mirror) {
@@ -280,10 +292,9 @@ __device__ __forceinline__ float beta_quantile32(float a, float b, float lnb2, i
     const float am1 = A - 1.0f, bm1 = B - 1.0f;
     bool conv = false;
     float xf = x;          // the lane's answer: its iterate at its own first convergence
-    const int nt0 = __any(full0) ? nmax : nhalf;
     for (int it = 0; it < 6; ++it) {
-        const int nt = it == 0 ? nt0 : nmax;
-        const int nown = (it == 0 && !full0) ? nh : nmax;
+        const int nt = it == 0 ? nhalf : nmax;
+        const int nown = it == 0 ? nh : nmax;
         float I, Ic, front;
         beta_inc32(A, B, lnb2, min(NA, nown), min(NB, nown), nt, x, &I, &Ic, &front);
         const float r = lower ? (I - Z) : (ZC - Ic);
@@ -297,7 +308,7 @@ __device__ __forceinline__ float beta_quantile32(float a, float b, float lnb2, i
         if (!(xn < 1.0f)) xn = 0.5f * (x + 1.0f);
         if (!conv) {
             xf = xn;
-            conv = (it > 0 || full0) && fabsf(xn - x) <= 9.765625e-4f * xn;
+            conv = it > 0 && fabsf(xn - x) <= 9.765625e-4f * xn;
         }
         x = xn;
         if (__all(conv)) break;
@@ -421,19 +432,39 @@ __device__ inline double beta_quantile64(double a, double b, double lnb, double 
     return root_low ? y : 1.0 - y;
 }
 
-// One point of a shape table (see kShapeSlots): the logit of
-// I^-1(z; a, b) at point k of half `upper` (z = p, or z = 1 - p with the
-// complement p exact), solved in FP64 on both sides of the root so the
-// logit keeps its precision in both tails.
-__device__ inline float shape_table_logit(double a, double b, double lnb, int upper, int k) {
-    const double t = kShapeTLo + (kShapeTHi - kShapeTLo) * (double)k / (double)(kShapeK - 1);
-    const double p = exp(-0.5 * t * t);
-    const double z = upper ? 1.0 - p : p, zc = upper ? p : 1.0 - p;
-    bool ok1, ok2;
-    const double x = beta_quantile64(a, b, lnb, z, zc, kF64QuantileIters, &ok1);
-    const double y = beta_quantile64(b, a, lnb, zc, z, kF64QuantileIters, &ok2);   // 1 - x
-    const double L = x <= 0.5 ? log(x) - log1p(-x) : log1p(-y) - log(y);
-    return (float)L;
+// Local coordinate of interpolation point q of a segment.
+__device__ inline double seg_node(int q) {
+    return 0.5 * cospi((2.0 * q + 1.0) / (2.0 * kSegCoefs));
+}
+
+// The value segment seg of a slot interpolates at its point q, in FP64; a slot's
+// segments run lower octaves, upper octaves, deviates.
+__device__ inline double slot_point(double a, double b, double lnb, int seg, int q) {
+    const double t = seg_node(q);
+    double z, zc;
+    if (seg < 2 * kOctaves) {
+        const bool upper = seg >= kOctaves;
+        const double p = ldexp(1.5 + t, (upper ? seg - kOctaves : seg) - 24);
+        z = upper ? 1.0 - p : p;
+        zc = upper ? p : 1.0 - p;
+    } else {
+        const double v = 0.5 * ((double)(seg - 2 * kOctaves - kDevHalf) + t);
+        z = 0.5 * erfc(-v * 0.70710678118654752);
+        zc = 0.5 * erfc(v * 0.70710678118654752);
+    }
+    bool ok;
+    return beta_quantile64(a, b, lnb, z, zc, kF64QuantileIters, &ok);
+}
+
+// Coefficients in powers of the local coordinate of the polynomial through the
+// values y at the points of a segment (divided differences, then expanded).
+__device__ inline void seg_fit(double *y, float *out) {
+    for (int k = 1; k < kSegCoefs; ++k)
+        for (int q = kSegCoefs - 1; q >= k; --q)
+            y[q] = (y[q] - y[q - 1]) / (seg_node(q) - seg_node(q - k));
+    for (int k = kSegCoefs - 2; k >= 0; --k)
+        for (int q = k; q < kSegCoefs - 1; ++q) y[q] -= seg_node(k) * y[q + 1];
+    for (int q = 0; q < kSegCoefs; ++q) out[q] = (float)y[q];
 }
 
 }  // namespace ara

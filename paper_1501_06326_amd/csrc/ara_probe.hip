@@ -95,8 +95,12 @@ __global__ __launch_bounds__(64) void k_probe_draws(int64_t n, PhiloxKeys keys, 
     const uint32_t ju = u24(philox10_x0(make_uint4(k, i, elt_id, 0u), keys));
     const float z = (float)ju * 5.9604644775390625e-08f;
     const float zc = (float)(16777216u - ju) * 5.9604644775390625e-08f;
+    if (tab) {
+        x_out[j] = slot_quantile(tab, ju);
+        return;
+    }
     bool ok;
-    const float x = beta_quantile32(a, b, lnb2, na, nb, z, zc, tab, &ok);
+    const float x = beta_quantile32(a, b, lnb2, na, nb, z, zc, &ok);
     x_out[j] = ok ? x : -1.0f;
 }
 
