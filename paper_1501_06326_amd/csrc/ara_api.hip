@@ -70,14 +70,14 @@ float band_deviate(float band) {
     return (float)hi;
 }
 
-// The FP32 pass hands the trials it cannot finish to the FP64-capable pass
-// through scratch: a counter at the start, the trial list 256 bytes in.  The
-// second pass takes up to as many wavefronts as the first keeps resident
-// (7 per SIMD), each looping over the list; surplus ones find it empty.
+// The lean pass hands the trials it cannot finish to the full pass through
+// scratch: a counter at the start, the trial list 256 bytes in.  That pass
+// takes up to as many wavefronts as it keeps resident (4 per SIMD), each
+// looping over the list; surplus ones find it empty.
 void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_opts &o) {
     p->redo_count = (uint32_t *)scr;
     p->redo = (int32_t *)(scr + 256);
-    const int64_t resident = (int64_t)ctx->n_cu * 4 * 7;
+    const int64_t resident = (int64_t)ctx->n_cu * 4 * 4;
     p->redo_grid = (int)(o.trial_count < resident ? (o.trial_count > 0 ? o.trial_count : 1)
                                                   : resident);
     if (o.debug_flags & ARA_DEBUG_QUANTILE_ONE_STEP) {
@@ -588,7 +588,8 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
         if (p->su_enabled)
             ARA_HIP_P(launch_shape_collect(p->d_rowf, p->d_rowq, hl[l].row_base, hl[l].n_rows, liveoff_l,
                                            n_catalogue, p->d_row_shape,
-                                           p->d_shape_keys + (size_t)l * kShapeSlots, s));
+                                           p->d_shape_keys + (size_t)l * kShapeSlots,
+                                           p->d_layers + l, s));
         if (!p->su_enabled)
             ARA_HIP_P(launch_build_sparse(p->d_otab + (size_t)l * n_catalogue, n_catalogue,
                                           p->d_sp_bits + (size_t)l * nwc,
@@ -704,7 +705,7 @@ ara_status run_impl(ara_context *ctx, const ara_yet *yet, const ara_portfolio *p
     p.occ_view = o.d_occ_view;
     p.occ_stride = o.occ_view_stride;
     p.status = ctx->d_status;
-    p.redo_w4 = (pf->all_flags & ROW_F64) && !(pf->all_flags & ROW_CORR);
+    p.full = (pf->all_flags & LAYER_SLOW) != 0;
     const size_t need = run_scratch_need(o.trial_count);
     char *scr = (char *)o.d_scratch;
     if (static_scratch) {
@@ -839,11 +840,13 @@ struct PuItem {
     void *ylt_layers, *ylt_pf;
 };
 
+// The secondary-uncertainty portfolios of a batch run in up to two launches:
+// those that the lean pass can take (B), then those with rows for the full
+// pass (F), whose register budget would slow the others down.
 struct BatchPlan {
-    BatchArgs B;
+    BatchArgs B, F;
     int grid, redo_grid, mode;
     bool f64out;
-    bool redo_w4;       // second pass at 4 wavefronts per SIMD (see k_ara_su_redo4)
     std::vector<PuItem> pu;
 };
 
@@ -881,10 +884,8 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: bad batch configuration");
     if (ranges && c.order == ARA_BATCH_TRIAL_MAJOR)
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: trial-major order needs one trial range");
-    int64_t total = 0, items = 0;
-    std::vector<BatchPf> h;
-    uint32_t su_flags = 0;     // OR of the row flags of the batch's SU portfolios
-    h.reserve((size_t)n);
+    int64_t total = 0, items[2] = {0, 0};
+    std::vector<BatchPf> hs[2];    // lean, full
     plan->pu.clear();
     for (int32_t i = 0; i < n; ++i) {
         const int64_t tb = ranges ? ranges[2 * i] : o.trial_begin;
@@ -901,9 +902,9 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
             plan->pu.push_back({p, tb, tc, ylt_l ? ylt_l[i] : nullptr, ylt_p ? ylt_p[i] : nullptr});
             continue;
         }
-        su_flags |= p->all_flags;
-        h.emplace_back();
-        BatchPf &b = h.back();
+        const int full = (p->all_flags & LAYER_SLOW) != 0;
+        hs[full].emplace_back();
+        BatchPf &b = hs[full].back();
         b.layers = p->d_layers;
         b.elts = p->d_elts;
         b.evoff = p->d_evoff;
@@ -922,42 +923,45 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         b.pad = 0;
         b.trial_begin = tb;
         b.trial_count = tc;
-        b.tile_base = items;
-        items += (tc + c.trial_tile - 1) / c.trial_tile;
+        b.tile_base = items[full];
+        items[full] += (tc + c.trial_tile - 1) / c.trial_tile;
         total += tc;
     }
     const size_t need = batch_need(n, total);
     if (!scratch || bytes < need)
         return fail(ctx, ARA_E_WORKSPACE_TOO_SMALL, "ara_run_batch: need %zu scratch bytes", need);
     char *sc = (char *)scratch;
+    std::vector<BatchPf> h(hs[0]);
+    h.insert(h.end(), hs[1].begin(), hs[1].end());
     if (!h.empty())
         ARA_HIP(ctx, hipMemcpyAsync(sc + batch_pf_off(), h.data(), sizeof(BatchPf) * h.size(),
                                     hipMemcpyHostToDevice, s));
-    const int32_t n_su = (int32_t)h.size();
-    BatchArgs &B = plan->B;
-    B.off = yet->d_off;
-    B.ev = yet->d_ev;
     const bool trial_major = c.order == ARA_BATCH_TRIAL_MAJOR;
-    B.trial_begin = trial_major ? o.trial_begin : 0;
-    B.trial_count = trial_major ? o.trial_count : 0;
-    B.pfs = (const BatchPf *)(sc + batch_pf_off());
-    B.n_pf = n_su;
-    B.tile = c.trial_tile;
-    B.tail_band = o.tail_band;
-    B.dev_band = band_deviate(o.tail_band);
-    B.trial_major = trial_major ? 1 : 0;
-    B.n_items = trial_major ? ((o.trial_count + c.trial_tile - 1) / c.trial_tile) * (int64_t)n_su
-                            : items;
-    B.counter = (unsigned long long *)sc;
-    B.redo_count = (uint32_t *)(sc + 8);
-    B.redo = (unsigned long long *)(sc + batch_redo_off(n));
-    B.status = status ? status : ctx->d_status;
-    if (c.waves_per_cu == 0 && B.n_items > 0x7fffffffll)
-        return fail(ctx, ARA_E_UNSUPPORTED, "ara_run_batch: more than 2^31 work items for the "
-                                            "one-workgroup-per-item form; use waves_per_cu > 0");
+    for (int full = 0; full < 2; ++full) {
+        BatchArgs &B = full ? plan->F : plan->B;
+        const int32_t n_su = (int32_t)hs[full].size();
+        B.off = yet->d_off;
+        B.ev = yet->d_ev;
+        B.trial_begin = trial_major ? o.trial_begin : 0;
+        B.trial_count = trial_major ? o.trial_count : 0;
+        B.pfs = (const BatchPf *)(sc + batch_pf_off()) + (full ? hs[0].size() : 0);
+        B.n_pf = n_su;
+        B.tile = c.trial_tile;
+        B.tail_band = o.tail_band;
+        B.dev_band = band_deviate(o.tail_band);
+        B.trial_major = trial_major ? 1 : 0;
+        B.n_items = trial_major ? ((o.trial_count + c.trial_tile - 1) / c.trial_tile) * (int64_t)n_su
+                                : items[full];
+        B.counter = (unsigned long long *)(sc + 32 * full);
+        B.redo_count = (uint32_t *)(sc + 32 * full + 8);
+        B.redo = (unsigned long long *)(sc + batch_redo_off(n));
+        B.status = status ? status : ctx->d_status;
+        if (c.waves_per_cu == 0 && B.n_items > 0x7fffffffll)
+            return fail(ctx, ARA_E_UNSUPPORTED, "ara_run_batch: more than 2^31 work items for the "
+                                                "one-workgroup-per-item form; use waves_per_cu > 0");
+    }
     plan->grid = ctx->n_cu * c.waves_per_cu;           // 0: one workgroup per item
-    plan->redo_w4 = (su_flags & ROW_F64) && !(su_flags & ROW_CORR);
-    plan->redo_grid = ctx->n_cu * 4 * (plan->redo_w4 ? 4 : 1);
+    plan->redo_grid = ctx->n_cu * 4 * 4;
     plan->mode = o.sum_mode;
     plan->f64out = o.ylt_dtype == ARA_F64;
     return ARA_OK;
@@ -967,7 +971,9 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
 // per-event table pass of each primary-uncertainty one, all on stream s.
 hipError_t launch_plan(const ara_context *ctx, const ara_yet *yet, const BatchPlan &plan,
                        hipStream_t s) {
-    hipError_t e = launch_batch(plan.B, plan.mode, plan.f64out, plan.grid, plan.redo_grid, plan.redo_w4, s);
+    hipError_t e = launch_batch(plan.B, plan.mode, plan.f64out, plan.grid, plan.redo_grid, false, s);
+    if (e == hipSuccess)
+        e = launch_batch(plan.F, plan.mode, plan.f64out, plan.grid, plan.redo_grid, true, s);
     for (size_t k = 0; k < plan.pu.size() && e == hipSuccess; ++k) {
         const PuItem &u = plan.pu[k];
         if (u.count > 0)

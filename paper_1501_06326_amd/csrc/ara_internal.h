@@ -11,13 +11,16 @@ namespace ara {
 
 // Row metadata word: bits 0-15 ELT index in the layer, bits 16-19 flags,
 // bits 20-25 / 26-31 the continued-fraction terms of the (a, b) / (b, a)
-// branches of the FP32 quantile.
+// branches of the FP32 quantile (of ROW_F64 rows: pairs of terms of the FP64 one,
+// 0 where it takes as many as needed).
 enum : uint32_t {
     ROW_DET = 1u << 16,    // loss = mean (sigma = 0 or secondary uncertainty off)
     ROW_F64 = 1u << 17,    // shape outside the FP32 quantile's domain: FP64 path
     ROW_CORR = 1u << 18,   // sigma_I > 0 and sigma_C > 0: mix two normals (section 3.2)
     ROW_CONLY = 1u << 19,  // sigma_I = 0, sigma_C > 0: z = u_C
     ROW_FLAGS = 0xFu << 16,
+    // layer flag: a row that can pay draws and has no shape slot
+    LAYER_SLOW = 1u << 31,
 };
 __host__ __device__ inline int meta_na(uint32_t m) { return (int)((m >> 20) & 63u); }
 __host__ __device__ inline int meta_nb(uint32_t m) { return (int)((m >> 26) & 63u); }
@@ -30,7 +33,7 @@ struct LayerDev {
     int64_t row_base;                    // first row of the layer in the row arrays
     int64_t evoff_base;                  // first entry of the layer's ev_off[n_cat + 1]
     int64_t otab_base;                   // first entry of the layer's otab[n_cat] (PU), or -1
-    uint32_t flags;                      // OR of the row flags of the layer
+    uint32_t flags;                      // OR of the row flags of the layer, LAYER_SLOW
     int32_t n_rows;
     int32_t nnz;                         // non-zero entries of otab (PU)
     uint32_t program_id;                 // keys z_(Prog,E) under ARA_KEYING_PAPER

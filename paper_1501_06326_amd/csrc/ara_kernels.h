@@ -54,7 +54,7 @@ struct SuLaunch {
     int32_t *redo;            // [trial_count] scratch: trials handed to the FP64-capable pass
     uint32_t *redo_count;     // scratch counter
     int redo_grid;            // blocks of the second pass
-    int redo_w4;              // second pass at 4 wavefronts per SIMD (FP64-quantile rows, no mix)
+    int full;                 // rows the lean pass cannot take: the full pass over every trial
     int32_t f64_iters;        // step limit of the FP64 quantile
     const float *shape_tab;   // shape tables [layer][kShapeSlots][kShapeStride]
     const uint32_t *row_shape;   // per row: 1 + shape slot, or 0
@@ -118,9 +118,9 @@ hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s);
 hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits, uint32_t *rank,
                                float *vals, LayerDev *d_layer, hipStream_t s);
 hipError_t launch_su(const SuLaunch &p, int mode, bool f64out, hipStream_t s);
+// full: the batch's portfolios take the full pass (see SuLaunch)
 hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
-                        bool redo_w4,
-                        hipStream_t s);
+                        bool full, hipStream_t s);
 // exclusive prefix sum of p[0, n) in place (one block; also used by the
 // exceedance-curve sort for its digit counts)
 hipError_t launch_scan_excl_u32(uint32_t *p, int64_t n, hipStream_t s);
@@ -133,7 +133,7 @@ hipError_t launch_debug_quantile(int64_t n, const float *a, const float *b, cons
 // [kShapeSlots] (rows get their slot), then the tables of n_slots slots
 hipError_t launch_shape_collect(RowF *rowf, const RowQ *rowq, int64_t row_base, int64_t n_rows,
                                 const uint32_t *liveoff, int32_t n_cat, uint32_t *row_shape,
-                                unsigned long long *keys, hipStream_t s);
+                                unsigned long long *keys, LayerDev *d_layer, hipStream_t s);
 hipError_t launch_shape_tables(const unsigned long long *keys, int64_t n_slots, float *tab,
                                hipStream_t s);
 

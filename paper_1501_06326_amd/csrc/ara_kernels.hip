@@ -11,124 +11,29 @@
 //        occurrence losses are tabulated once (lookup, ELT terms, cross-ELT
 //        sum and occurrence terms for every catalogue event) and a trial is a
 //        gather-sum over its event ids followed by the aggregate terms.
-//      - k_ara_su: secondary uncertainty.  One wavefront per trial; lanes
-//        read consecutive occurrences, look each up in the layer's event-major
-//        rows, and append the hits to an LDS queue (the fast pass only the
-//        rows that can pay: the others add exactly 0); the queue is drained
-//        64 hits at a time so every lane of a batch draws, inverts the Beta
-//        CDF and applies the ELT terms on real work (the paper's
-//        "convergence switching" idea applied to SIMD lanes).  A trial with
-//        a hit that needs the FP64 quantile (tail band, shapes outside the
-//        FP32 domain, the two-normal mix of shapes without a slot, FP32
-//        non-convergence) is handed to
-//        k_ara_su_redo, which runs it again with the FP64 path in place
-//        (k_ara_su_redo4: the same code in a 4-wavefront register budget,
-//        for portfolios with FP64-quantile rows and no mixed rows).
-//      - k_ara_batch / k_ara_batch_items: the same trial code over
-//        (portfolio, trial tile) work items of many portfolios at once.
+//      - k_ara_su (ara_su.hip): secondary uncertainty, the lean pass.  One
+//        wavefront per trial; lanes read consecutive occurrences, look each up
+//        in the layer's event-major rows, and append the hits to an LDS queue
+//        (only the rows that can pay: the others add exactly 0); the queue is
+//        drained 64 hits at a time so every lane of a batch draws, reads the
+//        quantile of its row's shape slot and applies the ELT terms on real
+//        work (the paper's "convergence switching" idea applied to SIMD lanes).
+//      - k_ara_full (ara_su.hip): portfolios with rows of shapes without a
+//        slot, or outside the FP32 domain: the same trial code with the FP32
+//        iteration in the light batches and a second queue for the FP64
+//        quantile; it also takes the trials that the lean pass hands over (a
+//        draw in the caller's tail band).
+//      - k_ara_batch* (ara_batch.hip): the same trial code over (portfolio,
+//        trial tile) work items of many portfolios at once.
 //      - the occurrence view (per-occurrence increments of the aggregate
 //        terms): the OCC instantiation of k_ara_su, or k_pu_occ_view without
 //        secondary uncertainty, both through occ_chunk's wavefront scan.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "ara_internal.h"
-#include "ara_math.h"
-#include "ara_kernels.h"
+#include "ara_device.h"
 
 namespace ara {
-
-// ---------------------------------------------------------------------------
-// small helpers
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void report(Status *st, int32_t code, int64_t a, int64_t b, int64_t c) {
-    if (atomicCAS(&st->code, 0, code) == 0) {
-        st->where[0] = a;
-        st->where[1] = b;
-        st->where[2] = c;
-    }
-}
-
-__device__ __forceinline__ float clampf_terms(float x, float r, float l) {
-    return fminf(fmaxf(x - r, 0.0f), l);
-}
-__device__ __forceinline__ double clampd_terms(double x, double r, double l) {
-    return fmin(fmax(x - r, 0.0), l);
-}
-
-// exclusive prefix sum of v over the 64 lanes of the wavefront (lane order)
-__device__ __forceinline__ int wave_excl_scan(int v, int *total) {
-    // Inclusive prefix sum over the wavefront with DPP moves: shifts within
-    // each row of 16 lanes (lanes shifted in from outside the row read 0),
-    // then lane 15 of rows 0 and 2 added into rows 1 and 3, then lane 31
-    // added into rows 2 and 3 (the other rows keep the 0 given as old).
-    int s = v;
-    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xf, 0xf, true);   // row_shr:1
-    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xf, 0xf, true);   // row_shr:2
-    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xf, 0xf, true);   // row_shr:4
-    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xf, 0xf, true);   // row_shr:8
-    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    *total = __builtin_amdgcn_readlane(s, 63);
-    return s - v;
-}
-
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
-
-// Sum accumulators for a trial's occurrence losses (ara_run_opts.sum_mode).
-template <int MODE>
-struct Acc;
-template <>
-struct Acc<ARA_SUM_NAIVE32> {
-    float s = 0.0f;
-    __device__ void add(float v) { s += v; }
-    __device__ double total() {
-        float t = s;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
-        return (double)t;
-    }
-};
-template <>
-struct Acc<ARA_SUM_KAHAN32> {
-    float s = 0.0f, c = 0.0f;   // Neumaier: exact sum = s + c (up to c's rounding)
-    __device__ void add(float v) {
-        const float t = s + v;
-        c += (fabsf(s) >= fabsf(v)) ? ((s - t) + v) : ((v - t) + s);
-        s = t;
-    }
-    __device__ double total() {
-        float S = s, C = c;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const float So = __shfl_xor(S, d, 64), Co = __shfl_xor(C, d, 64);
-            // both lanes of a pair compute the same combination (symmetric order)
-            const float a = fmaxf(fabsf(S), fabsf(So)) == fabsf(S) ? S : So;
-            const float b = (a == S) ? So : S;
-            const float t = a + b;
-            const float e = (a - t) + b;
-            C = C + Co + e;
-            S = t;
-        }
-        return (double)S + (double)C;
-    }
-};
-template <>
-struct Acc<ARA_SUM_F64> {
-    double s = 0.0;
-    __device__ void add(float v) { s += (double)v; }
-    __device__ double total() {
-        double t = s;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
-        return t;
-    }
-};
 
 // ---------------------------------------------------------------------------
 // YET validation: one wavefront per trial
@@ -332,6 +237,9 @@ __device__ void fit_row(const RawRow &r, int32_t su, RowQ *q, uint32_t *flags, f
         if (na == 0 || nb == 0) f |= ROW_F64;
         else f |= ((uint32_t)na << 20) | ((uint32_t)nb << 26);
     }
+    if (f & ROW_F64)       // pairs for the FP64 fraction (0: adaptive)
+        f |= ((uint32_t)cf_pairs((double)a, (double)b, 1e-11, 63) << 20) |
+             ((uint32_t)cf_pairs((double)b, (double)a, 1e-11, 63) << 26);
     if (si > 0.0 && sc > 0.0) {
         f |= ROW_CORR;
         *cfrac = (float)(sc / sigma);
@@ -470,58 +378,6 @@ struct PuArgs {
 };
 
 enum { TAB_GLOBAL = 0, TAB_LDS_DENSE = 1, TAB_LDS_SPARSE = 2 };
-
-// Occurrence view of 64 consecutive occurrences of one trial and layer, in
-// stored order: o (lane's occurrence loss net of the occurrence terms, 0 past
-// the end) is scanned into the running sum S (FP64, carried in *cs), the
-// aggregate terms give A = min(max(S - AggR, 0), AggL) (carried in *ca), and
-// the lane's increment A - A_prev is written at pos when valid.  Every lane
-// of the wave calls this (the scan reads all of them).
-// A DPP move of an FP64 value (both 32-bit halves with the same control);
-// lanes that receive nothing read 0.0.
-template <int CTRL, int ROWS, bool BOUND>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, BOUND);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, BOUND);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-template <bool F64OUT>
-__device__ __forceinline__ void occ_chunk(double o, bool valid, int64_t pos, int layer,
-                                          void *view, int64_t stride, float agg_r, float agg_l,
-                                          double *cs, double *ca, Status *st, int64_t trial) {
-    const int lane = threadIdx.x & 63;
-    // inclusive FP64 prefix sum over the wavefront, laid out as in wave_excl_scan
-    o += dpp_f64<0x111, 0xf, true>(o);    // row_shr:1
-    o += dpp_f64<0x112, 0xf, true>(o);    // row_shr:2
-    o += dpp_f64<0x114, 0xf, true>(o);    // row_shr:4
-    o += dpp_f64<0x118, 0xf, true>(o);    // row_shr:8
-    o += dpp_f64<0x142, 0xa, false>(o);   // row_bcast:15
-    o += dpp_f64<0x143, 0xc, false>(o);   // row_bcast:31
-    const double S = *cs + o;
-    const double A = clampd_terms(S, (double)agg_r, (double)agg_l);
-    double Ap = __shfl_up(A, 1, 64);
-    if (lane == 0) Ap = *ca;
-    if (valid) {
-        if (pos < stride) {
-            const int64_t at = (int64_t)layer * stride + pos;
-            if (F64OUT) ((double *)view)[at] = A - Ap;
-            else ((float *)view)[at] = (float)(A - Ap);
-        } else {
-            report(st, ARA_E_WORKSPACE_TOO_SMALL, trial, pos, stride);
-        }
-    }
-    *cs = readlane_f64(S, 63);
-    *ca = readlane_f64(A, 63);
-}
 
 // The layer's per-event occurrence-loss table, staged by the whole block in
 // LDS (dense, or sparse: a bit per event, the rank of each 32-event word and
@@ -674,578 +530,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7, 7))) voi
 }
 
 // ---------------------------------------------------------------------------
-// secondary uncertainty
-// ---------------------------------------------------------------------------
-// LDS per wavefront: X[kSeg] floats + Q[kQCap] pairs = 4 KB, so LDS allows 40
-// waves per CU and the register budget sets the occupancy (7 per SIMD,
-// measured best on the full-shape workload against 5, 6 and 8)
-constexpr int kSeg = 512;         // occurrences per LDS segment
-constexpr int kQCap = 256;        // hit queue (power of two)
-#define ARA_SU_OCCUPANCY __attribute__((amdgpu_waves_per_eu(7, 7)))
-// A layer's ELT records are staged in LDS when it has at most this many ELTs
-// (1 KB more per wavefront, still within the occupancy above); the draw then
-// needs one global load (the row) before its Philox key is known.
-constexpr int kEltLds = 64;
-constexpr int kQMask = kQCap - 1;
-constexpr int kPerLane = (kQCap - kWave) / kWave;   // hits a lane appends per sub-step
-
-struct SuArgs {
-    const int64_t *off;
-    const int32_t *ev;
-    int64_t trial_begin, trial_count;
-    const LayerDev *layers;
-    int32_t n_layers;
-    const EltDev *elts;
-    const uint32_t *evoff;
-    const RowQ *rowq;
-    const RowF *rowf;
-    const float *row_mean;
-    const float *row_cfrac;
-    const uint32_t *row_meta;
-    const double *row_lnb;
-    float tail_band;
-    float dev_band;           // |Phi^-1(z)| from which a mixed draw takes the FP64 quantile
-    void *ylt_layers;
-    void *ylt_pf;
-    int64_t *hits;
-    uint64_t *hit_chk;
-    Status *status;
-    int32_t *redo;            // trials (relative index) handed to the FP64-capable pass
-    uint32_t *redo_count;
-    int32_t f64_iters;        // step limit of the FP64 quantile
-    const float *shape_tab;   // the portfolio's shape tables ([layer][kShapeSlots][kShapeStride],
-                              // then the normal segments)
-    const uint32_t *row_shape;   // per row: 1 + its shape slot, or 0 (the diagnostic pass)
-    void *occ_view;           // occurrence view, written by the DIAG and OCC instantiations
-    int64_t occ_stride;
-};
-
-// The draws of a hit as 24-bit grid integers: jI keyed (k, i, elt_id, 0),
-// jC keyed (k, i, 0, 1); only those the row's flags need are drawn.
-// The two uniforms of a hit on the 2^-24 grid (j such that u = j 2^-24):
-// jI for the independent part, jC for the correlated part, drawn only when
-// the row needs them.  Occurrence keying: (k, i, elt_id, 0) and (k, i, 0, 1);
-// paper keying (section 3.1's z_(Prog,E) and z_(E)): (k, i, program, 2) and
-// (E, 0, 0, 3).
-__device__ __forceinline__ void draw_j(uint32_t flags, int32_t keying, uint32_t k, uint32_t i,
-                                       uint32_t elt_id, uint32_t program, uint32_t event,
-                                       const PhiloxKeys &keys, uint32_t *jI, uint32_t *jC) {
-    const bool paper = keying == ARA_KEYING_PAPER;
-    const uint4 cI = paper ? make_uint4(k, i, program, 2u) : make_uint4(k, i, elt_id, 0u);
-    const uint4 cC = paper ? make_uint4(event, 0u, 0u, 3u) : make_uint4(k, i, 0u, 1u);
-    *jI = (flags & ROW_CONLY) ? 0u : u24(philox10_x0(cI, keys));
-    *jC = (flags & (ROW_CONLY | ROW_CORR)) ? u24(philox10_x0(cC, keys)) : 0u;
-}
-
-// z and 1 - z of a hit (section 3.2).  A pure independent or correlated draw
-// is an exact grid value u = j 2^-24 (and 1 - u is exact too); the mixed case
-// maps both uniforms through Phi^-1 (= -sqrt(2) erfcinv(2u), taken on the side
-// of the smaller tail so the argument is exact), mixes, and maps back with
-// Phi(v) and Phi(-v).
-template <typename T>
-__device__ __forceinline__ void hit_z(uint32_t meta, uint32_t jI, uint32_t jC, T cfrac, T *z, T *zc) {
-    const T s24 = (T)5.9604644775390625e-08;
-    if (!(meta & ROW_CORR)) {
-        const uint32_t j = (meta & ROW_CONLY) ? jC : jI;
-        *z = (T)j * s24;
-        *zc = (T)(16777216u - j) * s24;
-        return;
-    }
-    auto nq = [&](uint32_t j) {
-        const T lo = (T)(j < 8388608u ? j : 16777216u - j) * ((T)2 * s24);
-        const T v = (T)1.4142135623730951 * erfcinv(lo);
-        return j < 8388608u ? -v : v;
-    };
-    const T wc = cfrac, wi = (T)1 - cfrac;
-    const T v = (nq(jI) * wi + nq(jC) * wc) / sqrt(wi * wi + wc * wc);
-    *z = (T)0.5 * erfc(-v * (T)0.7071067811865476);
-    *zc = (T)0.5 * erfc(v * (T)0.7071067811865476);
-}
-
-// One trial of the analysis, all layers (Algorithm 1 from the layer loop
-// down).  REDO = false is the lean FP32 pass: a hit that needs the FP64
-// quantile (tail band, shape outside the FP32 domain, FP32 non-convergence)
-// abandons the trial, which is then queued for the REDO = true pass, where
-// such hits take the FP64 path in place.  Returns true when abandoned.
-template <int MODE, bool F64OUT, bool DIAG, bool REDO, bool OCC = false>
-__device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys, int64_t t,
-                                         float *X, uint2 *Q, EltDev *El) {
-    const int lane = threadIdx.x;
-    const int64_t ti = A.trial_begin + t;
-    const uint32_t i_abs = (uint32_t)ti;
-    const int64_t o0 = A.off[ti];
-    const int64_t n = A.off[ti + 1] - o0;
-    double pf_sum = 0.0;
-    const float *norm = A.shape_tab + (size_t)A.n_layers * kShapeSlots * kShapeStride;
-
-    for (int l = 0; l < A.n_layers; ++l) {
-        const LayerDev L = A.layers[l];
-        const uint32_t *eo = A.evoff + L.evoff_base;
-        const int64_t rb0 = L.row_base;
-        const bool elt_lds = L.n_elts <= kEltLds;
-        if (elt_lds) {
-            __syncthreads();
-            for (int i = lane; i < L.n_elts; i += kWave) El[i] = A.elts[L.elt_begin + i];
-            __syncthreads();
-        }
-        Acc<MODE> acc;
-        uint64_t chk = 0;
-        int64_t nh = 0;
-        double occ_s = 0.0, occ_a = 0.0;      // occurrence-view carries
-        (void)occ_s;
-        (void)occ_a;
-
-        for (int64_t seg = 0; seg < n; seg += kSeg) {
-            const int segn = (int)((n - seg) < kSeg ? (n - seg) : kSeg);
-            for (int i = lane; i < segn; i += kWave) X[i] = 0.0f;
-            uint32_t qh = 0, qt = 0;   // queue head / tail (wave-uniform)
-            bool abandon = false;
-            __syncthreads();
-
-            // Drain cnt queue entries from head h, one hit per lane: draw,
-            // invert the Beta CDF, ELT terms, accumulate into X[k].
-            auto run_batch = [&](uint32_t h, int cnt) {
-                __syncthreads();
-                bool defer = false;
-                if (lane < cnt) {
-                    const uint2 e = Q[(h + lane) & kQMask];
-                    const uint32_t kl = e.x, row = e.y;
-                    // the row's flags and Beta parameters: one compact record in
-                    // the fast passes (row indexes the paying rows), the per-row
-                    // arrays in the diagnostic pass (row indexes all rows)
-                    uint32_t meta, orow, shape;
-                    float scale, cfrac;
-                    if (DIAG) {
-                        meta = A.row_meta[row];
-                        scale = A.rowq[row].scale;
-                        cfrac = A.row_cfrac[row];
-                        orow = row;
-                        shape = A.row_shape[row];
-                    } else {
-                        const RowF F = A.rowf[row];
-                        meta = F.meta;
-                        scale = F.scale;
-                        orow = (uint32_t)rb0 + rowf_row(F);
-                        shape = rowf_shape(F);
-                        cfrac = F.cfrac;
-                    }
-                    // the row's shape table, when its shape has a slot
-                    const float *tab =
-                        shape ? A.shape_tab + ((size_t)l * kShapeSlots + (shape - 1u)) * kShapeStride
-                              : nullptr;
-                    const uint32_t ei = meta & 0xffffu;
-                    // the layer's ELT record: an LDS read when the layer's records
-                    // are staged (the global read is a different instruction, so the
-                    // two are not merged into one flat load)
-                    EltDev ed;
-                    if (elt_lds) {
-                        ed = El[ei];
-                    } else {
-                        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                        const u32x4 g = __builtin_nontemporal_load(
-                            reinterpret_cast<const u32x4 *>(A.elts + L.elt_begin + ei));
-                        ed.elt_id = g.x;
-                        ed.retention = __uint_as_float(g.y);
-                        ed.limit = __uint_as_float(g.z);
-                        ed.share = __uint_as_float(g.w);
-                    }
-                    float loss = 0.0f;
-                    if (meta & ROW_DET) {
-                        loss = scale;
-                    } else if (DIAG && (scale <= ed.retention || ed.limit == 0.0f ||
-                                        ed.share == 0.0f)) {
-                        // a row that cannot pay (row_cannot_pay) adds exactly 0
-                        // whatever it draws
-                    } else if (!REDO && ((meta & ROW_F64) || ((meta & ROW_CORR) && !tab))) {
-                        // shapes outside the FP32 domain, and the two-normal mix
-                        // of shapes without a slot (its special functions would
-                        // inflate this pass's register budget: inlined here they
-                        // spill 387 registers at 7 waves per SIMD), are left to
-                        // the second pass
-                        defer = true;
-                    } else {
-                        uint32_t jI, jC;
-                        const uint32_t ev =
-                            L.keying == ARA_KEYING_PAPER ? (uint32_t)A.ev[o0 + seg + kl] : 0u;
-                        draw_j(meta, L.keying, (uint32_t)(seg + kl), i_abs, ed.elt_id,
-                               L.program_id, ev, keys, &jI, &jC);
-                        bool need64 = (meta & ROW_F64) != 0;
-                        if (tab) {
-                            // the slot's segments; a mixed draw goes from the two
-                            // normal deviates to the quantile without forming z.
-                            // About 25 instructions where a Halley step and its
-                            // continued fraction took 120: 12.75 -> 10.98 ms for
-                            // 1.24e9 draws (1M trials, 16 ELTs), which the walk over
-                            // the occurrences now sets; mixed rows, once redone
-                            // whole in the second pass, 3.93 -> 0.62 ms for 40,003
-                            // trials.
-                            float x;
-                            if (meta & ROW_CORR) {
-                                const float wi = 1.0f - cfrac;
-                                const float n2 = fmaf(wi, wi, cfrac * cfrac);
-                                const float v = fmaf(norm_dev(norm, jI), wi,
-                                                     norm_dev(norm, jC) * cfrac) * rsqrtf(n2);
-                                need64 = !(fabsf(v) < A.dev_band);
-                                x = slot_quantile_dev(tab, v);
-                            } else {
-                                const uint32_t j = (meta & ROW_CONLY) ? jC : jI;
-                                need64 = (float)min(j, 16777216u - j) * 5.9604644775390625e-08f <
-                                         A.tail_band;
-                                x = slot_quantile(tab, j);
-                            }
-                            loss = scale * x;
-                        } else if (!need64) {
-                            const RowQ q = A.rowq[orow];
-                            float z, zc;
-                            if (REDO) {
-                                hit_z<float>(meta, jI, jC, cfrac, &z, &zc);
-                            } else {
-                                const uint32_t j = (meta & ROW_CONLY) ? jC : jI;
-                                z = (float)j * 5.9604644775390625e-08f;
-                                zc = (float)(16777216u - j) * 5.9604644775390625e-08f;
-                            }
-                            need64 = fminf(z, zc) < A.tail_band;
-                            if (!need64) {
-                                bool ok;
-                                const float x = beta_quantile32(q.a, q.b, q.lnb, meta_na(meta),
-                                                                meta_nb(meta), z, zc, &ok);
-                                if (ok) loss = scale * x; else need64 = true;
-                            }
-                        }
-                        if (need64) {
-                            if (REDO) {
-                                const RowQ q = A.rowq[orow];
-                                double z64, zc64;
-                                hit_z<double>(meta, jI, jC, (double)cfrac, &z64, &zc64);
-                                bool ok;
-                                const double x = beta_quantile64((double)q.a, (double)q.b,
-                                                                 A.row_lnb[orow], z64, zc64,
-                                                                 A.f64_iters, &ok);
-                                if (!ok) report(A.status, ARA_E_NUMERIC, ti, seg + kl, ed.elt_id);
-                                loss = (float)((double)scale * x);
-                            } else {
-                                defer = true;
-                            }
-                        }
-                    }
-                    if (DIAG) {
-                        nh += 1;
-                        chk += (uint64_t)(seg + kl + 1) * 2654435761ull + (uint64_t)ed.elt_id;
-                    }
-                    if (!defer) {
-                        const float lp = ed.share * clampf_terms(loss, ed.retention, ed.limit);
-                        atomicAdd(&X[kl], lp);
-                    }
-                }
-                if (!REDO && __any(defer)) abandon = true;
-                __syncthreads();
-            };
-
-            // The fast pass enqueues only the rows that can pay, from the
-            // per-event (first record, count) pairs; the diagnostic pass
-            // visits every row so it counts every non-zero lookup.  The fast
-            // pass keeps its loads one chunk ahead: the next chunk's pairs
-            // and the event ids of the chunk after that are in flight while
-            // this chunk's hits are drawn.
-            const int32_t *evs = A.ev + o0 + seg;
-            const uint2 *lpairs = reinterpret_cast<const uint2 *>(A.evoff + L.live_base);
-            uint2 pr_next = make_uint2(0u, 0u);
-            int32_t e_after = -1;
-            if (!DIAG) {
-                if (lane < segn) pr_next = lpairs[evs[lane]];
-                if (kWave + lane < segn) e_after = evs[kWave + lane];
-            }
-            for (int c = 0; c < segn && !abandon; c += kWave) {
-                const int kl = c + lane;
-                const bool valid = kl < segn;
-                uint32_t rb = 0, cnt = 0;
-                if (DIAG) {
-                    if (valid) {
-                        const int32_t E = evs[kl];
-                        rb = eo[E];
-                        cnt = eo[E + 1] - rb;
-                    }
-                } else {
-                    rb = pr_next.x;
-                    cnt = pr_next.y;                  // zero past the segment's end
-                    pr_next = e_after >= 0 ? lpairs[e_after] : make_uint2(0u, 0u);
-                    e_after = (c + 2 * kWave + lane < segn) ? evs[c + 2 * kWave + lane] : -1;
-                }
-                uint32_t done = 0;
-                while (!abandon) {
-                    const int take = (int)min(cnt - done, (uint32_t)kPerLane);
-                    int tot;
-                    const int excl = wave_excl_scan(take, &tot);
-                    for (int j = 0; j < take; ++j)
-                        Q[(qt + excl + j) & kQMask] =
-                            make_uint2((uint32_t)kl, (uint32_t)(rb0 + rb + done + j));
-                    qt += tot;
-                    done += take;
-                    while (qt - qh >= (uint32_t)kWave && !abandon) {
-                        run_batch(qh, kWave);
-                        qh += kWave;
-                    }
-                    if (!__any(done < cnt)) break;
-                }
-            }
-            if (!abandon && qt != qh) run_batch(qh, (int)(qt - qh));
-            if (abandon) return true;
-            __syncthreads();
-            for (int i = lane; i < segn; i += kWave)
-                acc.add(clampf_terms(X[i], L.occ_r, L.occ_l));
-            if ((DIAG || OCC) && A.occ_view) {
-                const int64_t pos0 = o0 - A.off[A.trial_begin] + seg;
-                for (int c = 0; c < segn; c += kWave) {
-                    const int i = c + lane;
-                    const bool valid = i < segn;
-                    const double o = valid ? (double)clampf_terms(X[i], L.occ_r, L.occ_l) : 0.0;
-                    occ_chunk<F64OUT>(o, valid, pos0 + i, l, A.occ_view, A.occ_stride, L.agg_r,
-                                      L.agg_l, &occ_s, &occ_a, A.status, ti);
-                }
-            }
-            __syncthreads();
-        }
-
-        const double S = acc.total();
-        double Y;
-        if (MODE == ARA_SUM_F64) Y = clampd_terms(S, (double)L.agg_r, (double)L.agg_l);
-        else Y = (double)clampf_terms((float)S, L.agg_r, L.agg_l);
-        if (DIAG) {
-            nh = wave_sum(nh);
-            chk = wave_sum(chk);
-        }
-        if (lane == 0) {
-            if (F64OUT) {
-                if (A.ylt_layers) ((double *)A.ylt_layers)[(int64_t)l * A.trial_count + t] = Y;
-            } else {
-                if (A.ylt_layers) ((float *)A.ylt_layers)[(int64_t)l * A.trial_count + t] = (float)Y;
-            }
-            if (DIAG) {
-                if (A.hits) A.hits[(int64_t)l * A.trial_count + t] = nh;
-                if (A.hit_chk) A.hit_chk[(int64_t)l * A.trial_count + t] = chk;
-            }
-        }
-        if (F64OUT) pf_sum += Y;
-        else pf_sum = (double)((float)pf_sum + (float)Y);
-    }
-    if (lane == 0 && A.ylt_pf) {
-        if (F64OUT) ((double *)A.ylt_pf)[t] = pf_sum;
-        else ((float *)A.ylt_pf)[t] = (float)pf_sum;
-    }
-    return false;
-}
-
-// Main pass: one wavefront (block) per trial.  DIAG: every row visited, hit
-// counts and checksums (and the occurrence view when asked for); OCC: the
-// lean pass that also writes the occurrence view (its per-occurrence sums
-// are those of the DIAG pass: the rows it skips add +0).
-template <int MODE, bool F64OUT, bool DIAG, bool OCC = false>
-__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY void k_ara_su(SuArgs A, PhiloxKeys keys) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    const int64_t t = blockIdx.x;
-    if (t >= A.trial_count) return;
-    if (su_trial<MODE, F64OUT, DIAG, false, OCC>(A, keys, t, X, Q, El) && threadIdx.x == 0)
-        A.redo[atomicAdd(A.redo_count, 1u)] = (int32_t)t;
-}
-
-// FP64-capable pass over the trials the main pass handed over; the count is
-// read on the device, so no host round trip is needed between the passes.
-template <int MODE, bool F64OUT, bool DIAG, bool OCC>
-__device__ __forceinline__ void su_redo_loop(const SuArgs &A, const PhiloxKeys &keys, float *X,
-                                             uint2 *Q, EltDev *El) {
-    // the list holds at most one entry per trial of the run; an entry outside
-    // the run (scratch shared by runs that overlapped, against the contract)
-    // is reported instead of followed
-    const uint32_t cnt = *A.redo_count;
-    const uint32_t n = cnt < (uint32_t)A.trial_count ? cnt : (uint32_t)A.trial_count;
-    for (uint32_t r = blockIdx.x; r < n; r += gridDim.x) {
-        const int32_t t = A.redo[r];
-        if (t < 0 || (int64_t)t >= A.trial_count) {
-            if (threadIdx.x == 0) report(A.status, ARA_E_INVALID_ARG, r, t, A.trial_count);
-            continue;
-        }
-        su_trial<MODE, F64OUT, DIAG, true, OCC>(A, keys, (int64_t)t, X, Q, El);
-    }
-}
-
-template <int MODE, bool F64OUT, bool DIAG, bool OCC = false>
-__global__ __launch_bounds__(64) void k_ara_su_redo(SuArgs A, PhiloxKeys keys) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    su_redo_loop<MODE, F64OUT, DIAG, OCC>(A, keys, X, Q, El);
-}
-
-// The same pass held to 4 wavefronts per SIMD (128 registers, spilling the
-// rest): for portfolios whose handed-over draws are FP64 quantiles (shapes
-// outside the FP32 domain, capped sigma) four resident wavefronts hide more
-// of the FP64 latency than one unspilled one; with two-normal-mix rows the
-// FP32 special functions of the mix spill too and the one-wavefront form
-// above is faster (both measured on the full shape).
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ara_su_redo4(
-    SuArgs A, PhiloxKeys keys) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    su_redo_loop<MODE, F64OUT, false, false>(A, keys, X, Q, El);
-}
-
-// ---------------------------------------------------------------------------
-// batched portfolios: one persistent launch over (trial tile, portfolio)
-// work items, trial-major so the portfolios of one tile run close together
-// and share that tile's event ids from cache; an atomic counter hands out the
-// items (load balance across portfolios of very different cost)
-// ---------------------------------------------------------------------------
-__global__ void k_batch_reset(unsigned long long *counter, uint32_t *redo_count) {
-    *counter = 0ull;
-    *redo_count = 0u;
-}
-
-__global__ void k_reset_u32(uint32_t *p) { *p = 0u; }
-
-__device__ __forceinline__ void batch_view(const BatchArgs &B, int p, SuArgs &A, PhiloxKeys &keys) {
-    const BatchPf &P = B.pfs[p];
-    A.off = B.off;
-    A.ev = B.ev;
-    A.trial_begin = P.trial_begin;
-    A.trial_count = P.trial_count;
-    A.layers = P.layers;
-    A.n_layers = P.n_layers;
-    A.elts = P.elts;
-    A.evoff = P.evoff;
-    A.rowq = P.rowq;
-    A.rowf = P.rowf;
-    A.row_mean = P.row_mean;
-    A.row_cfrac = P.row_cfrac;
-    A.row_meta = P.row_meta;
-    A.row_lnb = P.row_lnb;
-    A.tail_band = B.tail_band;
-    A.dev_band = B.dev_band;
-    A.ylt_layers = P.ylt_layers;
-    A.ylt_pf = P.ylt_pf;
-    A.hits = nullptr;
-    A.hit_chk = nullptr;
-    A.status = B.status;
-    A.redo = nullptr;
-    A.redo_count = nullptr;
-    A.f64_iters = kF64QuantileIters;
-    A.shape_tab = P.shape_tab;
-    A.row_shape = nullptr;
-    A.occ_view = nullptr;
-    A.occ_stride = 0;
-    keys.k0 = P.k0;
-    keys.k1 = P.k1;
-}
-
-// One work item of a batch: a tile of B.tile trials of one portfolio.  The
-// item index is wave-uniform; the portfolio and tile are derived from it
-// (trial-major: tile-then-portfolio; portfolio-major: each portfolio's block
-// of items in turn).
-template <int MODE, bool F64OUT>
-__device__ __forceinline__ void batch_item(const BatchArgs &B, unsigned long long item, float *X,
-                                           uint2 *Q, EltDev *El) {
-    int64_t tile;
-    int p;
-    if (B.trial_major) {
-        tile = (int64_t)(item / (unsigned long long)B.n_pf);
-        p = (int)(item % (unsigned long long)B.n_pf);
-    } else {
-        // the portfolio whose block of work items holds this item
-        int lo_p = 0, hi_p = B.n_pf - 1;
-        while (lo_p < hi_p) {
-            const int mid = (lo_p + hi_p + 1) >> 1;
-            if ((unsigned long long)B.pfs[mid].tile_base <= item) lo_p = mid; else hi_p = mid - 1;
-        }
-        p = lo_p;
-        tile = (int64_t)item - B.pfs[p].tile_base;
-    }
-    // wave-uniform by construction; said explicitly so the portfolio's
-    // pointers are read with scalar loads into scalar registers
-    p = __builtin_amdgcn_readfirstlane(p);
-    tile = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(tile >> 32)) << 32) |
-                     (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tile));
-    SuArgs A;
-    PhiloxKeys keys;
-    batch_view(B, p, A, keys);
-    const int64_t t0 = tile * B.tile;
-    const int64_t t1 = (t0 + B.tile) < A.trial_count ? (t0 + B.tile) : A.trial_count;
-    for (int64_t t = t0; t < t1; ++t)
-        if (su_trial<MODE, F64OUT, false, false>(A, keys, t, X, Q, El) && threadIdx.x == 0)
-            B.redo[atomicAdd(B.redo_count, 1u)] = ((unsigned long long)p << 32) | (uint64_t)t;
-}
-
-// Persistent form: grid-wide loop over work items taken from an atomic
-// counter (waves_per_cu wavefronts per CU stay resident).
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(64) void k_ara_batch(BatchArgs B) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    const unsigned long long n_items = (unsigned long long)B.n_items;
-    while (true) {
-        unsigned long long item = 0;
-        if (threadIdx.x == 0) item = atomicAdd(B.counter, 1ull);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)item);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(item >> 32));
-        item = ((unsigned long long)hi << 32) | lo;
-        if (item >= n_items) break;
-        batch_item<MODE, F64OUT>(B, item, X, Q, El);
-    }
-}
-
-// One workgroup per work item: the dispatcher hands the items out in index
-// order as wavefronts retire, and a wavefront keeps no state across items,
-// so the kernel runs at the single-portfolio kernel's occupancy.
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY void k_ara_batch_items(BatchArgs B) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    const unsigned long long item = blockIdx.x;
-    if (item >= (unsigned long long)B.n_items) return;
-    batch_item<MODE, F64OUT>(B, item, X, Q, El);
-}
-
-template <int MODE, bool F64OUT>
-__device__ __forceinline__ void batch_redo_loop(const BatchArgs &B, float *X, uint2 *Q, EltDev *El) {
-    const uint32_t n = *B.redo_count;
-    for (uint32_t r = blockIdx.x; r < n; r += gridDim.x) {
-        const unsigned long long e = B.redo[r];
-        const int p = (int)(e >> 32);
-        const int64_t t = (int64_t)(e & 0xffffffffull);
-        if (p >= B.n_pf || t >= B.pfs[p].trial_count) {     // see k_ara_su_redo
-            if (threadIdx.x == 0) report(B.status, ARA_E_INVALID_ARG, r, p, t);
-            continue;
-        }
-        SuArgs A;
-        PhiloxKeys keys;
-        batch_view(B, p, A, keys);
-        su_trial<MODE, F64OUT, false, true>(A, keys, t, X, Q, El);
-    }
-}
-
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(64) void k_ara_batch_redo(BatchArgs B) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    batch_redo_loop<MODE, F64OUT>(B, X, Q, El);
-}
-
-// the batch's second pass in the register budget of k_ara_su_redo4
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ara_batch_redo4(
-    BatchArgs B) {
-    __shared__ float X[kSeg];
-    __shared__ uint2 Q[kQCap];
-    __shared__ EltDev El[kEltLds];
-    batch_redo_loop<MODE, F64OUT>(B, X, Q, El);
-}
-
-// ---------------------------------------------------------------------------
 // diagnostics
 // ---------------------------------------------------------------------------
 __global__ void k_debug_philox(int64_t n, const uint32_t *__restrict__ ctr, PhiloxKeys keys,
@@ -1295,7 +579,9 @@ __global__ __launch_bounds__(64) void k_debug_quantile(int64_t n, const float *_
     }
     if (use64) {
         bool ok;
-        r = (float)beta_quantile64((double)A, (double)B, lnb, z[j], zc[j], kF64QuantileIters, &ok);
+        r = (float)beta_quantile64((double)A, (double)B, lnb, cf_pairs((double)A, (double)B, 1e-11, 63),
+                                   cf_pairs((double)B, (double)A, 1e-11, 63), z[j], zc[j],
+                                   kF64QuantileIters, &ok);
         if (!ok) r = __builtin_nanf("");
     }
     x[j] = r;
@@ -1421,84 +707,9 @@ hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s) {
     return f64out ? pu_dispatch<ARA_SUM_F64, true>(p, s) : pu_dispatch<ARA_SUM_F64, false>(p, s);
 }
 
-template <int MODE, bool F64OUT>
-static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
-    SuArgs A;
-    A.off = p.off; A.ev = p.ev; A.trial_begin = p.trial_begin; A.trial_count = p.trial_count;
-    A.layers = p.layers; A.n_layers = p.n_layers; A.elts = p.elts; A.evoff = p.evoff;
-    A.rowq = p.rowq; A.rowf = p.rowf; A.row_mean = p.row_mean; A.row_cfrac = p.row_cfrac;
-    A.row_meta = p.row_meta;
-    A.row_lnb = p.row_lnb;
-    A.tail_band = p.tail_band; A.dev_band = p.dev_band; A.ylt_layers = p.ylt_layers; A.ylt_pf = p.ylt_pf;
-    A.hits = p.hits; A.hit_chk = p.hit_chk; A.status = p.status;
-    A.redo = p.redo; A.redo_count = p.redo_count; A.f64_iters = p.f64_iters;
-    A.shape_tab = p.shape_tab; A.row_shape = p.row_shape;
-    A.occ_view = p.occ_view; A.occ_stride = p.occ_stride;
-    const PhiloxKeys keys = philox_keys(p.seed);
-    // a kernel, not hipMemsetAsync, so the sequence can be captured in a graph
-    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(1), 0, s, p.redo_count);
-    const dim3 g((unsigned)p.trial_count), gr((unsigned)p.redo_grid);
-    if (p.hits || p.hit_chk) {
-        hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, true>), g, dim3(64), 0, s, A, keys);
-        hipLaunchKernelGGL((k_ara_su_redo<MODE, F64OUT, true>), gr, dim3(64), 0, s, A, keys);
-    } else if (p.occ_view) {
-        hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, true>), g, dim3(64), 0, s, A, keys);
-        hipLaunchKernelGGL((k_ara_su_redo<MODE, F64OUT, false, true>), gr, dim3(64), 0, s, A, keys);
-    } else {
-        hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false>), g, dim3(64), 0, s, A, keys);
-        if (p.redo_w4)
-            hipLaunchKernelGGL((k_ara_su_redo4<MODE, F64OUT>), gr, dim3(64), 0, s, A, keys);
-        else
-            hipLaunchKernelGGL((k_ara_su_redo<MODE, F64OUT, false>), gr, dim3(64), 0, s, A, keys);
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_scan_excl_u32(uint32_t *p, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_scan_excl_u32, dim3(1), dim3(1024), 0, s, p, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_su(const SuLaunch &p, int mode, bool f64out, hipStream_t s) {
-    if (p.trial_count <= 0) return hipSuccess;
-    if (mode == ARA_SUM_NAIVE32) return f64out ? su_dispatch2<ARA_SUM_NAIVE32, true>(p, s)
-                                               : su_dispatch2<ARA_SUM_NAIVE32, false>(p, s);
-    if (mode == ARA_SUM_KAHAN32) return f64out ? su_dispatch2<ARA_SUM_KAHAN32, true>(p, s)
-                                               : su_dispatch2<ARA_SUM_KAHAN32, false>(p, s);
-    return f64out ? su_dispatch2<ARA_SUM_F64, true>(p, s) : su_dispatch2<ARA_SUM_F64, false>(p, s);
-}
-
-// grid <= 0: one workgroup per work item; otherwise the persistent form with
-// that many workgroups.
-template <int MODE, bool F64OUT>
-static void batch_dispatch(const BatchArgs &B, int grid, int redo_grid, bool redo_w4,
-                           hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(1), 0, s, B.counter, B.redo_count);
-    if (grid <= 0)
-        hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT>), dim3((unsigned)B.n_items), dim3(64),
-                           0, s, B);
-    else
-        hipLaunchKernelGGL((k_ara_batch<MODE, F64OUT>), dim3(grid), dim3(64), 0, s, B);
-    if (redo_w4)
-        hipLaunchKernelGGL((k_ara_batch_redo4<MODE, F64OUT>), dim3(redo_grid), dim3(64), 0, s, B);
-    else
-        hipLaunchKernelGGL((k_ara_batch_redo<MODE, F64OUT>), dim3(redo_grid), dim3(64), 0, s, B);
-}
-
-hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
-                        bool redo_w4, hipStream_t s) {
-    if (B.n_items <= 0 || B.n_pf <= 0) return hipSuccess;
-    if (mode == ARA_SUM_NAIVE32) {
-        if (f64out) batch_dispatch<ARA_SUM_NAIVE32, true>(B, grid, redo_grid, redo_w4, s);
-        else batch_dispatch<ARA_SUM_NAIVE32, false>(B, grid, redo_grid, redo_w4, s);
-    } else if (mode == ARA_SUM_KAHAN32) {
-        if (f64out) batch_dispatch<ARA_SUM_KAHAN32, true>(B, grid, redo_grid, redo_w4, s);
-        else batch_dispatch<ARA_SUM_KAHAN32, false>(B, grid, redo_grid, redo_w4, s);
-    } else {
-        if (f64out) batch_dispatch<ARA_SUM_F64, true>(B, grid, redo_grid, redo_w4, s);
-        else batch_dispatch<ARA_SUM_F64, false>(B, grid, redo_grid, redo_w4, s);
-    }
     return hipGetLastError();
 }
 
@@ -1584,11 +795,13 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
                                                       const uint32_t *__restrict__ liveoff,
                                                       int32_t n_cat,
                                                       const unsigned long long *__restrict__ keys,
-                                                      uint32_t *__restrict__ row_shape) {
+                                                      uint32_t *__restrict__ row_shape,
+                                                      LayerDev *__restrict__ layer) {
     __shared__ unsigned long long slot[kShapeSlots];
     if (threadIdx.x < kShapeSlots) slot[threadIdx.x] = keys[threadIdx.x];
     __syncthreads();
     const uint32_t n = liveoff[n_cat];
+    bool slow = false;         // a row that needs the full pass
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         RowF &F = rowf[row_base + i];
         uint32_t sh = 0;
@@ -1602,7 +815,9 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
         }
         F.rs = (F.rs & ~31u) | sh;
         row_shape[row_base + rowf_row(F)] = sh;
+        slow = slow || (sh == 0u && !(F.meta & ROW_DET));
     }
+    if (__any(slow) && (threadIdx.x & 63) == 0) atomicOr(&layer->flags, LAYER_SLOW);
 }
 
 // The segments of the used slots, and after them the normal segments: one
@@ -1640,12 +855,12 @@ __global__ __launch_bounds__(kSlotSegs *kSegCoefs) void k_shape_tables(
 
 hipError_t launch_shape_collect(RowF *rowf, const RowQ *rowq, int64_t row_base, int64_t n_rows,
                                 const uint32_t *liveoff, int32_t n_cat, uint32_t *row_shape,
-                                unsigned long long *keys, hipStream_t s) {
+                                unsigned long long *keys, LayerDev *d_layer, hipStream_t s) {
     hipLaunchKernelGGL(k_shape_collect, dim3(1), dim3(256), 0, s, rowf, rowq, row_base, liveoff,
                        n_cat, keys);
     // a grid over the layer's rows (the paying ones are a prefix of them)
     hipLaunchKernelGGL(k_shape_assign, dim3(grid_for(n_rows > 0 ? n_rows : 1, 256, 1024)),
-                       dim3(256), 0, s, rowf, rowq, row_base, liveoff, n_cat, keys, row_shape);
+                       dim3(256), 0, s, rowf, rowq, row_base, liveoff, n_cat, keys, row_shape, d_layer);
     return hipGetLastError();
 }
 

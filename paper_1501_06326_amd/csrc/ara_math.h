@@ -140,32 +140,6 @@ __device__ __forceinline__ void beta_cf32(float a, float b, float x, int n, int 
     *Dout = D;
 }
 
-// Terms of the continued fraction that FP32 needs (truncation below 1e-8
-// relative) at the slowest point of its branch, x = (a+1)/(a+b+2); it
-// converges faster for smaller x.  Evaluated in FP64 at load time; 0 when
-// more than 62 terms would be needed.  The reference takes 200 terms: where
-// 62 terms reach 1e-8 the fraction converges at least as fast as 0.75^n, so
-// 200 terms are exact to FP64 rounding.
-__device__ inline int cf_terms(double a, double b) {
-    const double x = (a + 1.0) / (a + b + 2.0);
-    auto eval = [&](int n) {
-        double K = 1.0;
-        for (int j = n; j >= 1; --j) {
-            const int m = j >> 1;
-            // d_j = p / q; K <- 1 + d_j / K with one division
-            const double p = (j & 1) ? -(a + m) * (a + b + m) * x : m * (b - m) * x;
-            const double q = (j & 1) ? (a + 2.0 * m) * (a + 2.0 * m + 1.0)
-                                     : (a + 2.0 * m - 1.0) * (a + 2.0 * m);
-            K = 1.0 + p / (q * K);
-        }
-        return 1.0 / K;
-    };
-    const double ref = eval(200);
-    for (int n = 2; n <= 62; n += 2)
-        if (fabs(eval(n) / ref - 1.0) < 1e-8) return n;
-    return 0;
-}
-
 // Initial guess: Abramowitz & Stegun 26.2.22 for the upper-tail normal
 // deviate y of the smaller tail probability, then A&S 26.5.22 for the Beta
 // quantile (valid for a, b > 1/2; used here for a, b >= 1).
@@ -347,87 +321,173 @@ __device__ inline double beta_cf64(double a, double b, double x) {
     return 1.0 / K;
 }
 
-__device__ inline void beta_inc64(double a, double b, double lnb, double x, double *I, double *Ic,
-                                  double *logdens) {
-    const double lx = log(x), l1x = log1p(-x);
-    const double e = a * lx + b * l1x - lnb;
-    *logdens = e - lx - l1x;
-    if (x * (a + b + 2.0) < a + 1.0) {
-        const double P = exp(e) * beta_cf64(a, b, x) / a;
-        *I = P;
-        *Ic = 1.0 - P;
-    } else {
-        const double Q = exp(e) * beta_cf64(b, a, 1.0 - x) / b;
-        *Ic = Q;
-        *I = 1.0 - Q;
+// Pairs of terms (2m - 1, 2m) after which the fraction stays within tol
+// (relative) of its limit at the slowest point of its branch,
+// x = (a+1)/(a+b+2) (it converges faster for smaller x); 0 when more than
+// most are needed.  Evaluated forward in FP64 at load time, once to the limit
+// and once to the count: O(n) where evaluating every candidate backward took
+// O(n^2) terms (k_fit_rows over 768k rows 0.33 ms before).
+__device__ inline int cf_pairs(double a, double b, double tol, int most) {
+    const double x = (a + 1.0) / (a + b + 2.0), apb = a + b;
+    double ref = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+        double Am2 = 1.0, Bm2 = 0.0, Am1 = 1.0, Bm1 = 1.0, qprev = 1.0, K = 1.0;
+        const int last = pass ? most : 2000;
+        for (int m = 0; m < last; ++m) {
+            const double fm = (double)m, t0 = a + 2.0 * fm;
+            const double qo = t0 * (t0 + 1.0), ao = qprev * (-(a + fm) * (apb + fm) * x);
+            const double A1 = qo * Am1 + ao * Am2, B1 = qo * Bm1 + ao * Bm2;
+            const double qe = (t0 + 1.0) * (t0 + 2.0), ae = qo * ((fm + 1.0) * (b - fm - 1.0) * x);
+            const double A2 = qe * A1 + ae * Am1, B2 = qe * B1 + ae * Bm1;
+            qprev = qe;
+            const double s = 1.0 / B2, Kn = A2 * s;
+            Am2 = A1 * s;
+            Bm2 = B1 * s;
+            Am1 = Kn;
+            Bm1 = 1.0;
+            if (pass ? fabs(ref / Kn - 1.0) < tol : fabs(Kn - K) <= 1e-15 * fabs(Kn)) {
+                if (pass) return m + 1;
+                K = Kn;
+                break;
+            }
+            K = Kn;
+        }
+        ref = K;
     }
+    return 0;
 }
 
-// Solve I_x(a,b) = z for a root known to lie in (0, hi0]; Halley steps
-// bracketed by [lo, hi] (every evaluation of the increasing I_x shrinks the
-// bracket); a step leaving the bracket falls back to bisection, geometric
-// while the bracket spans decades.  Returns false in *ok on failure.
-__device__ inline double beta_solve64(double a, double b, double lnb, double z, double zc,
-                                      double x, double hi0, int max_iter, bool *ok) {
+// Terms the FP32 quantile takes (truncation below 1e-8; even, at most 62).
+__device__ inline int cf_terms(double a, double b) { return 2 * cf_pairs(a, b, 1e-8, 31); }
+
+// The fraction backward from a known number of pairs, without divisions (see
+// beta_cf32); every pair is scaled by an approximate reciprocal of its N, which
+// cancels in the ratio.  About 25 instructions a pair where the forward form
+// with its division and its convergence test takes 45.  Returns 1 / K.
+__device__ inline double beta_cf64_pairs(double a, double b, double x, int pairs) {
+    const double am1 = a - 1.0, apbm1 = (a + b) - 1.0;
+    double N = 1.0, D = 1.0, fm = (double)pairs;
+    for (int m = pairs; m >= 1; --m, fm -= 1.0) {
+        const double te = fma(2.0, fm, am1);
+        const double qe = fma(te, te, te), qo = fma(te, te, -te);
+        const double mx = fm * x;
+        const double pe = (b - fm) * mx;
+        const double po = -(am1 + fm) * ((apbm1 + fm) * x);
+        const double D1 = qe * N;
+        const double N1 = fma(pe, D, D1);
+        const double D2 = qo * N1;
+        const double N2 = fma(po, D1, D2);
+        const double s = __builtin_amdgcn_rcp(N2);
+        N = N2 * s;
+        D = D2 * s;
+    }
+    return D / N;
+}
+
+// I_x(a, b), 1 - I_x(a, b) and the prefactor x^a (1-x)^b / B(a, b); na / nb
+// the pairs of the (a, b) and (b, a) branches, 0: as many as it takes.
+__device__ inline void beta_inc64(double a, double b, double lnb, int na, int nb, double x,
+                                  double *I, double *Ic, double *front) {
+    const double e = exp(a * log(x) + b * log1p(-x) - lnb);
+    *front = e;
+    const bool direct = x * (a + b + 2.0) < a + 1.0;
+    const double A = direct ? a : b, B = direct ? b : a, X = direct ? x : 1.0 - x;
+    const int pairs = direct ? na : nb;
+    const double v = e * (pairs ? beta_cf64_pairs(A, B, X, pairs) : beta_cf64(A, B, X)) / A;
+    *I = direct ? v : 1.0 - v;
+    *Ic = direct ? 1.0 - v : v;
+}
+
+// Solve I_x(a,b) = z for a root in (0, hi0] (hi0 <= 1); Halley steps bracketed
+// by [lo, hi] (every evaluation of the increasing I_x shrinks the bracket); a
+// step leaving the bracket falls back to bisection, geometric while the
+// bracket spans decades.  A Halley step below 1e-4 of the root ends it: the
+// next error is its cube, below 1e-10 of the root where FP32 losses round at
+// 6e-8 (a test for 1e-14 sits in the noise of I_x for one draw in twelve, and
+// the 64 lanes of a wavefront waited for the draw that stalled).  Returns false
+// in *ok on failure.
+__device__ inline double beta_solve64(double a, double b, double lnb, int na, int nb, double z,
+                                      double zc, double x, double hi0, int max_iter, bool *ok) {
     const bool lower = z <= zc;
     double lo = 0.0, hi = hi0;
     if (!(x > 0.0 && x < hi)) x = 0.5 * hi;
     *ok = false;
     for (int it = 0; it < max_iter; ++it) {
-        double I, Ic, ld;
-        beta_inc64(a, b, lnb, x, &I, &Ic, &ld);
+        double I, Ic, front;
+        beta_inc64(a, b, lnb, na, nb, x, &I, &Ic, &front);
         const double r = lower ? (I - z) : (zc - Ic);
         if (r == 0.0) { *ok = true; return x; }
         if (r < 0.0) lo = x; else hi = x;
-        // the root lies below 1e-300 (near-Bernoulli shapes): 0 to double
-        // precision, and the loss it scales underflows in FP32 anyway
-        if (hi <= 1e-300) { *ok = true; return 0.0; }
-        const double dens = exp(ld);
-        const double u = r / dens;
-        const double hh = (a - 1.0) / x - (b - 1.0) / (1.0 - x);
-        const double t = u / (1.0 - 0.5 * fmin(1.0, u * hh));
-        double xn = x - t;
-        if (!(xn > lo && xn < hi)) {
+        // the root lies below 1e-100 (near-Bernoulli shapes): 0, as the FP32
+        // loss it scales is
+        if (hi <= 1e-100) { *ok = true; return 0.0; }
+        const double w = 1.0 - x;
+        const double rf = r / front;
+        const double uh = rf * fma(a - 1.0, w, -(b - 1.0) * x);
+        double xn = x - rf * (x * w) / (1.0 - 0.5 * fmin(1.0, uh));
+        const bool halley = xn > lo && xn < hi;
+        if (!halley) {
             if (lo > 0.0 && hi > 4.0 * lo) xn = sqrt(lo * hi);
             else if (lo == 0.0) xn = 1e-3 * hi;
             else xn = 0.5 * (lo + hi);
         }
-        if (fabs(xn - x) <= 1e-14 * xn || hi - lo <= 1e-15 * hi) { *ok = true; return xn; }
+        if ((halley && fabs(xn - x) <= 1e-4 * xn) || hi - lo <= 1e-15 * hi) {
+            *ok = true;
+            return xn;
+        }
         x = xn;
     }
     return x;
 }
 
-// FP64 quantile (any shape a, b > 0; lnb = ln B(a, b)): the root side is
-// chosen from I_{1/2}(a, b), the small side solved, the other recovered by
-// 1 - y; at most max_iter steps.
-__device__ inline double beta_quantile64(double a, double b, double lnb, double z, double zc,
-                                        int max_iter, bool *ok) {
-    double Ih, Ihc, ld;
-    beta_inc64(a, b, lnb, 0.5, &Ih, &Ihc, &ld);
-    const bool root_low = (z <= zc) ? (z <= Ih) : (zc >= Ihc);
-    double A = a, B = b, Z = z, ZC = zc;
-    if (!root_low) { A = b; B = a; Z = zc; ZC = z; }
-    double x;
-    if (A >= 1.0 && B >= 1.0) {
+// FP64 quantile (any shape a, b > 0; lnb = ln B(a, b); na, nb as beta_inc64):
+// the smaller side of the root is solved, the other recovered by 1 - y; at
+// most max_iter steps.
+__device__ __attribute__((noinline)) inline double beta_quantile64(double a, double b, double lnb, int na, int nb, double z,
+                                         double zc, int max_iter, bool *ok) {
+    double x, hi0;
+    bool root_low;
+    if (a >= 1.0 && b >= 1.0) {
         // Abramowitz & Stegun 26.2.22 / 26.5.22 (as beta_guess32, in FP64):
-        // within a few per cent of the root for shapes of any size, where the
-        // small-x expansion below starts far off for large shapes
-        const bool lowz = Z < 0.5;
-        const double t = sqrt(-2.0 * log(lowz ? Z : ZC));
+        // within a few per cent of the root for shapes of any size; a root
+        // near 1/2 may be solved from the other side, so the bracket is whole
+        const bool lowz = z < zc;
+        const double t = sqrt(-2.0 * log(lowz ? z : zc));
         double y = t - (2.30753 + 0.27061 * t) / (1.0 + t * (0.99229 + 0.04481 * t));
         if (!lowz) y = -y;
         const double lam = (y * y - 3.0) / 6.0;
-        const double ra = 1.0 / (2.0 * A - 1.0), rb = 1.0 / (2.0 * B - 1.0);
+        const double ra = 1.0 / (2.0 * a - 1.0), rb = 1.0 / (2.0 * b - 1.0);
         const double rh = 0.5 * (ra + rb);
         const double w = y * sqrt(1.0 / rh + lam) * rh - (rb - ra) * (lam + 5.0 / 6.0 - (2.0 / 3.0) * rh);
-        x = A / (A + B * exp(2.0 * w));
+        const double g = exp(2.0 * w);
+        x = a / (a + b * g);
+        root_low = x <= 0.5;
+        if (!root_low) x = b * g / (a + b * g);
+        x = fmin(x, 0.75);
+        hi0 = 1.0;
     } else {
-        // the leading term of the small-x expansion I_x ~ x^A / (A B(A, B))
-        x = exp((log(Z) + log(A) + lnb) / A);
+        // the leading term of the small-x expansion I_x ~ x^a / (a B(a, b)), at
+        // both ends: a root below 1e-100, or that far below 1, is 0 or 1 to the
+        // FP32 loss (nearly every draw of a near-Bernoulli shape)
+        const double l0 = (log(z * a) + lnb) / a, l1 = (log(zc * b) + lnb) / b;
+        if (l0 < -230.0 || l1 < -230.0) {
+            *ok = true;
+            return l0 < -230.0 ? 0.0 : 1.0;
+        }
+        double Ih, Ihc, front;
+        beta_inc64(a, b, lnb, na, nb, 0.5, &Ih, &Ihc, &front);
+        root_low = (z <= zc) ? (z <= Ih) : (zc >= Ihc);
+        x = exp(root_low ? l0 : l1);
+        // the expansion's next term
+        const double A = root_low ? a : b, B = root_low ? b : a;
+        const double c = 1.0 + (1.0 - B) * x / (A + 1.0);
+        x = c > 0.1 ? x / c : x;
+        if (!(x < 0.5)) x = 0.25;
+        hi0 = 0.5;
     }
-    if (!(x < 0.5)) x = 0.25;
-    double y = beta_solve64(A, B, lnb, Z, ZC, x, 0.5, max_iter, ok);
+    const double y = beta_solve64(root_low ? a : b, root_low ? b : a, lnb, root_low ? na : nb,
+                                  root_low ? nb : na, root_low ? z : zc, root_low ? zc : z, x, hi0,
+                                  max_iter, ok);
     if (y == 0.0) *ok = true;    // root below the smallest double
     return root_low ? y : 1.0 - y;
 }
@@ -453,7 +513,7 @@ __device__ inline double slot_point(double a, double b, double lnb, int seg, int
         zc = 0.5 * erfc(v * 0.70710678118654752);
     }
     bool ok;
-    return beta_quantile64(a, b, lnb, z, zc, kF64QuantileIters, &ok);
+    return beta_quantile64(a, b, lnb, 0, 0, z, zc, kF64QuantileIters, &ok);
 }
 
 // Coefficients in powers of the local coordinate of the polynomial through the

@@ -1,4 +1,7 @@
-"""The quantile of shapes with a slot, at the edges of its polynomial segments.
+"""Quantiles of secondary uncertainty at their edges: polynomial segments, the FP64
+path, and the queues of the full pass.
+
+The quantile of shapes with a slot, at the edges of its polynomial segments.
 
 By draw: grid points on both sides of every octave edge of min(z, 1 - z), both
 halves, against the FP64 oracle's inverse.  Bound: the segments interpolate to
@@ -60,5 +63,65 @@ def test_mixed_rows_unequal_parts(ara, part):
     # a wide tail band hands draws to the FP64 quantile: the same trials within the bound
     r2 = ara.run(y, p, tail_band=0.01)
     assert np.all(np.abs(r2["ylt"].double().cpu().numpy() - ref["ylt"]) <= 1e-5 * ref["gross"] + 1e-3)
+    ara.free_portfolio(p)
+    ara.free_yet(y)
+
+
+# FP64 quantile: shapes outside the FP32 domain.  It ends on a Halley step below
+# 1e-4 of the root, whose error is the step's cube (1e-12) times a constant of
+# order ten; the result is FP32, so 1e-7 of max(root, mean).
+@pytest.mark.parametrize("a,b", [(0.3, 0.4), (0.02, 3.0), (5e-7, 1.5e-6), (0.7, 60.0), (40.0, 2.0),
+                                 (33.0, 33.0), (400.0, 30.0), (5.0, 0.5), (2e4, 1e4)])
+def test_fp64_quantile(ara, a, b):
+    rng = np.random.default_rng(11)
+    j = 2 * rng.integers(0, 1 << 23, 4000) + 1
+    j[:8] = [1, 3, 5, (1 << 24) - 1, (1 << 24) - 3, (1 << 23) - 1, (1 << 23) + 1, 12345]
+    z, zc = j / 2.0 ** 24, ((1 << 24) - j) / 2.0 ** 24
+    print("fp64 quantile", a, b, flush=True)
+    A, B = np.full(j.size, a, np.float32), np.full(j.size, b, np.float32)
+    x, path = ara.debug_beta_quantile(A, B, z, zc)
+    ref = oracle.betaincinv(float(A[0]), float(B[0]), z, zc)
+    assert np.all(path == 1)
+    assert np.max(np.abs(x - ref) / np.maximum(ref, a / (a + b))) <= 1e-7
+
+
+@pytest.mark.parametrize("n_occ", [1, 63, 64, 65, 130, 511, 512, 513, 1100])
+def test_full_pass_queues(ara, n_occ):
+    """Trials of n_occ occurrences over rows of every kind (no draw, slotted,
+    FP32 iteration, FP64 shape, near-Bernoulli, mixed with and without a slot),
+    so both queues of the full pass fill and drain at every remainder: the
+    oracle within 1e-5 G + 1e-3, the diagnostic pass and a batch bit for bit."""
+    from workloads import ELT, YET, Layer, Portfolio
+    rng = np.random.default_rng(n_occ)
+    n_cat, n_trials = 40, 12
+    elts = []
+    for e in range(6):
+        n = 30
+        ev = np.sort(rng.choice(n_cat, n, replace=False)).astype(np.int32)
+        m = np.exp(rng.normal(12, 1, n)).astype(np.float32)
+        frac = rng.choice([0.0, 0.1, 0.5, 0.8, 3.0], n).astype(np.float32)
+        top = rng.choice([1.5, 4.0, 9.0], n).astype(np.float32)
+        corr = rng.choice([0.0, 0.0, 0.4, 1.0], n).astype(np.float32)
+        elts.append(ELT(elt_id=7 * e, event_ids=ev, mean=m,
+                        sigma_i=(m * frac * (1 - corr)).astype(np.float32),
+                        sigma_c=(m * frac * corr).astype(np.float32),
+                        max_loss=(m * top).astype(np.float32), retention=1e5, limit=5e6, share=0.9))
+    pf = Portfolio(layers=[Layer(elts=elts, occ_retention=1e5, occ_limit=2e7, agg_retention=1e6,
+                                 agg_limit=1e12)], seed=99)
+    off = np.arange(n_trials + 1, dtype=np.int64) * n_occ
+    yet = YET(offsets=off, event_ids=rng.integers(0, n_cat, off[-1]).astype(np.int32), times=None,
+              n_catalogue=n_cat)
+    print("full pass queues", n_occ, flush=True)
+    ref = oracle.run_ara(yet, pf)
+    y = ara.load_yet(yet)
+    p = ara.load_portfolio(pf, n_cat)
+    r = ara.run(y, p)["ylt"]
+    err = np.abs(r.double().cpu().numpy() - ref["ylt"])
+    assert np.all(err <= 1e-5 * ref["gross"] + 1e-3)
+    d = ara.run(y, p, diagnostics=True)
+    assert torch.equal(d["ylt"], r)
+    assert np.array_equal(d["hits"].cpu().numpy(), ref["hits"])
+    for cfg in (None, (2, 4, 1)):
+        assert torch.equal(ara.run_batch(y, [p, p], cfg=cfg)[1]["ylt"], r)
     ara.free_portfolio(p)
     ara.free_yet(y)
