@@ -89,6 +89,59 @@ void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_op
     p->dev_band = band_deviate(p->tail_band);
 }
 
+// Whether a run of so many trials takes the lean pass in its event-table form:
+// portfolios that it can hold (no rows for the full pass, no mixed rows, whose
+// extra lookups its four wavefronts per SIMD hide worse: 0.62 against 0.56 ms for
+// 40,003 trials), where its blocks' wavefronts have several trials each and a
+// trial fills segments.  Measured against the one-wavefront form (table / other):
+//  * 1 layer, 1000 occurrences a trial: 32,768 trials 326 / 311 us, 65,536 616 /
+//    610 us, 131,072 1182 / 1333 us, 1M 8.5 / 9.8 ms;
+//  * 4 layers (the other form walks all layers' tables at once, 2 MB each, out of
+//    a 4 MB L2): 4,096 trials 208 / 218 us, 16,384 645 / 827 us, 32,768 1226 /
+//    1901 us; with 300 occurrences 16,384 276 / 262 us, 32,768 495 / 584 us;
+//  * 100 occurrences a trial: 2 times slower at any size.
+bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
+                   int64_t trials) {
+    if (!pf->d_evtab || (pf->all_flags & (LAYER_DENSE | LAYER_SLOW | ROW_CORR))) return false;
+    const int64_t mean_len = yet->n_occ / (yet->n_trials > 0 ? yet->n_trials : 1);
+    const int64_t waves = (int64_t)ctx->n_cu * kTabWaves;
+    if (mean_len >= kSeg) return trials >= waves && trials * pf->n_layers >= 16 * waves;
+    return pf->n_layers > 1 && mean_len >= kSeg / 2 && trials >= 6 * waves;
+}
+
+// The launch of one secondary-uncertainty portfolio over o's trials, without its
+// outputs and hand-over scratch.
+SuLaunch su_launch(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
+                   const ara_run_opts &o, Status *status) {
+    SuLaunch p;
+    std::memset(&p, 0, sizeof p);
+    p.off = yet->d_off;
+    p.ev = yet->d_ev;
+    p.trial_begin = o.trial_begin;
+    p.trial_count = o.trial_count;
+    p.layers = pf->d_layers;
+    p.n_layers = pf->n_layers;
+    p.elts = pf->d_elts;
+    p.evoff = pf->d_evoff;
+    p.rowq = pf->d_rowq;
+    p.rowf = pf->d_rowf;
+    p.row_mean = pf->d_row_mean;
+    p.row_cfrac = pf->d_row_cfrac;
+    p.row_meta = pf->d_row_meta;
+    p.row_lnb = pf->d_row_lnb;
+    p.shape_tab = pf->d_shape_tab;
+    p.row_shape = pf->d_row_shape;
+    p.seed = pf->seed;
+    p.tail_band = o.tail_band;
+    p.status = status;
+    p.full = (pf->all_flags & LAYER_SLOW) != 0;
+    p.h_layers = pf->h_layers;
+    p.evtab = su_table_form(ctx, yet, pf, o.trial_count) ? pf->d_evtab : nullptr;
+    p.n_cat = pf->n_catalogue;
+    p.n_cu = ctx->n_cu;
+    return p;
+}
+
 // The primary-uncertainty pass of one portfolio over trials [begin, begin +
 // count): per layer, the gather-sum over the per-event occurrence-loss table
 // (ara_run, and the primary-uncertainty portfolios of a batch).
@@ -118,10 +171,16 @@ ara_status fail(ara_context *ctx, ara_status code, const char *fmt, ...) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Words of a layer's event table; 0 for catalogues beyond its LDS.
+size_t evtab_words(int32_t n_cat) {
+    const int32_t groups = (n_cat - 1) / kTabGroup + 1;
+    return groups <= kTabGroups ? 3 * (size_t)groups : 0;
+}
+
 // Byte layout of a portfolio workspace.
 struct Layout {
     size_t layers, elts, evoff, liveoff, rowq, rowf, row_mean, row_cfrac, row_meta, row_lnb,
-        row_shape, shape_keys, shape_tab, otab,
+        row_shape, shape_keys, shape_tab, evtab, otab,
         sp_bits, sp_rank,
         sp_vals, raw, rawfit, eltoff, dat, total;
     int64_t n_rows = 0;
@@ -187,6 +246,8 @@ ara_status plan(ara_context *ctx, const ara_portfolio_desc *d, int32_t n_cat, La
     L->shape_tab = o;
     o += su ? align256(sizeof(float) * (kShapeStride * kShapeSlots * (size_t)(nl ? nl : 1) + kNormFloats))
             : 0;
+    L->evtab = o;
+    o += su ? align256(sizeof(uint32_t) * (size_t)nl * evtab_words(n_cat)) : 0;
     const size_t nw = ((size_t)n_cat + 31) / 32;
     const bool pu = !d->su_enabled;
     L->otab = o; o += pu ? align256(sizeof(float) * (size_t)nl * n_cat) : 0;
@@ -494,6 +555,7 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
         D.flags = 0;
         D.program_id = ld.program_id;
         D.keying = desc->keying;
+        D.chunk = kWave;
         for (int j = 0; j < ld.n_elts; ++j, ++ei) {
             const ara_elt_desc &e = ld.elts[j];
             he[ei].elt_id = e.elt_id;
@@ -534,6 +596,8 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
     p->d_row_shape = desc->su_enabled ? (uint32_t *)(w + L.row_shape) : nullptr;
     p->d_shape_keys = desc->su_enabled ? (unsigned long long *)(w + L.shape_keys) : nullptr;
     p->d_shape_tab = desc->su_enabled ? (float *)(w + L.shape_tab) : nullptr;
+    const size_t tabw = desc->su_enabled ? evtab_words(n_catalogue) : 0;
+    p->d_evtab = tabw ? (uint32_t *)(w + L.evtab) : nullptr;
     p->d_otab = desc->su_enabled ? nullptr : (float *)(w + L.otab);
     p->d_sp_bits = desc->su_enabled ? nullptr : (uint32_t *)(w + L.sp_bits);
     p->d_sp_rank = desc->su_enabled ? nullptr : (uint32_t *)(w + L.sp_rank);
@@ -590,6 +654,9 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
                                            n_catalogue, p->d_row_shape,
                                            p->d_shape_keys + (size_t)l * kShapeSlots,
                                            p->d_layers + l, s));
+        if (tabw)
+            ARA_HIP_P(launch_event_table(p->d_evoff + hl[l].live_base, n_catalogue,
+                                         p->d_evtab + (size_t)l * tabw, p->d_layers + l, s));
         if (!p->su_enabled)
             ARA_HIP_P(launch_build_sparse(p->d_otab + (size_t)l * n_catalogue, n_catalogue,
                                           p->d_sp_bits + (size_t)l * nwc,
@@ -679,33 +746,13 @@ ara_status run_impl(ara_context *ctx, const ara_yet *yet, const ara_portfolio *p
                                 ctx->d_status, s));
         return ARA_OK;
     }
-    SuLaunch p;
-    p.off = yet->d_off;
-    p.ev = yet->d_ev;
-    p.trial_begin = o.trial_begin;
-    p.trial_count = o.trial_count;
-    p.layers = pf->d_layers;
-    p.n_layers = pf->n_layers;
-    p.elts = pf->d_elts;
-    p.evoff = pf->d_evoff;
-    p.rowq = pf->d_rowq;
-    p.rowf = pf->d_rowf;
-    p.row_mean = pf->d_row_mean;
-    p.row_cfrac = pf->d_row_cfrac;
-    p.row_meta = pf->d_row_meta;
-    p.row_lnb = pf->d_row_lnb;
-    p.shape_tab = pf->d_shape_tab;
-    p.row_shape = pf->d_row_shape;
-    p.seed = pf->seed;
-    p.tail_band = o.tail_band;
+    SuLaunch p = su_launch(ctx, yet, pf, o, ctx->d_status);
     p.ylt_layers = d_ylt_layers;
     p.ylt_pf = d_ylt_portfolio;
     p.hits = o.d_hits;
     p.hit_chk = o.d_hit_chk;
     p.occ_view = o.d_occ_view;
     p.occ_stride = o.occ_view_stride;
-    p.status = ctx->d_status;
-    p.full = (pf->all_flags & LAYER_SLOW) != 0;
     const size_t need = run_scratch_need(o.trial_count);
     char *scr = (char *)o.d_scratch;
     if (static_scratch) {
@@ -843,8 +890,17 @@ struct PuItem {
 // The secondary-uncertainty portfolios of a batch run in up to two launches:
 // those that the lean pass can take (B), then those with rows for the full
 // pass (F), whose register budget would slow the others down.
+struct TabItem {
+    const ara_portfolio *pf;
+    int64_t begin, count;
+    void *ylt_layers, *ylt_pf;
+    int32_t *flags;
+};
+
 struct BatchPlan {
     BatchArgs B, F;
+    float tail_band;
+    std::vector<TabItem> tab;      // launches of their own: the event-table form
     int grid, redo_grid, mode;
     bool f64out;
     std::vector<PuItem> pu;
@@ -884,9 +940,10 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: bad batch configuration");
     if (ranges && c.order == ARA_BATCH_TRIAL_MAJOR)
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: trial-major order needs one trial range");
-    int64_t total = 0, items[2] = {0, 0};
+    int64_t total = 0, listed = 0, items[2] = {0, 0};
     std::vector<BatchPf> hs[2];    // lean, full
     plan->pu.clear();
+    plan->tab.clear();
     for (int32_t i = 0; i < n; ++i) {
         const int64_t tb = ranges ? ranges[2 * i] : o.trial_begin;
         const int64_t tc = ranges ? ranges[2 * i + 1] : o.trial_count;
@@ -900,6 +957,12 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
             return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: portfolio %d catalogue mismatch", i);
         if (!p->su_enabled) {
             plan->pu.push_back({p, tb, tc, ylt_l ? ylt_l[i] : nullptr, ylt_p ? ylt_p[i] : nullptr});
+            continue;
+        }
+        total += tc;
+        if (tc > 0 && su_table_form(ctx, yet, p, tc)) {
+            plan->tab.push_back({p, tb, tc, ylt_l ? ylt_l[i] : nullptr, ylt_p ? ylt_p[i] : nullptr,
+                                 nullptr});
             continue;
         }
         const int full = (p->all_flags & LAYER_SLOW) != 0;
@@ -925,7 +988,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         b.trial_count = tc;
         b.tile_base = items[full];
         items[full] += (tc + c.trial_tile - 1) / c.trial_tile;
-        total += tc;
+        listed += tc;
     }
     const size_t need = batch_need(n, total);
     if (!scratch || bytes < need)
@@ -960,6 +1023,13 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
             return fail(ctx, ARA_E_UNSUPPORTED, "ara_run_batch: more than 2^31 work items for the "
                                                 "one-workgroup-per-item form; use waves_per_cu > 0");
     }
+    // the table form's flags lie behind the list of the others' trials
+    int32_t *flags = (int32_t *)(sc + batch_redo_off(n) + sizeof(unsigned long long) * (size_t)listed);
+    for (TabItem &t : plan->tab) {
+        t.flags = flags;
+        flags += t.count;
+    }
+    plan->tail_band = o.tail_band;
     plan->grid = ctx->n_cu * c.waves_per_cu;           // 0: one workgroup per item
     plan->redo_grid = ctx->n_cu * 4 * 4;
     plan->mode = o.sum_mode;
@@ -967,13 +1037,30 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
     return ARA_OK;
 }
 
-// The batched launch of a plan's secondary-uncertainty portfolios, then the
-// per-event table pass of each primary-uncertainty one, all on stream s.
+// The batched launches of a plan's secondary-uncertainty portfolios, the launches
+// of those that take the event-table form, then the per-event table pass of each
+// primary-uncertainty one, all on stream s.
 hipError_t launch_plan(const ara_context *ctx, const ara_yet *yet, const BatchPlan &plan,
                        hipStream_t s) {
     hipError_t e = launch_batch(plan.B, plan.mode, plan.f64out, plan.grid, plan.redo_grid, false, s);
     if (e == hipSuccess)
         e = launch_batch(plan.F, plan.mode, plan.f64out, plan.grid, plan.redo_grid, true, s);
+    for (size_t k = 0; k < plan.tab.size() && e == hipSuccess; ++k) {
+        const TabItem &t = plan.tab[k];
+        ara_run_opts o;
+        std::memset(&o, 0, sizeof o);
+        o.trial_begin = t.begin;
+        o.trial_count = t.count;
+        o.tail_band = plan.tail_band;
+        SuLaunch p = su_launch(ctx, yet, t.pf, o, plan.B.status);
+        p.ylt_layers = t.ylt_layers;
+        p.ylt_pf = t.ylt_pf;
+        p.redo = t.flags;
+        p.redo_grid = plan.redo_grid;
+        p.f64_iters = kF64QuantileIters;
+        p.dev_band = band_deviate(plan.tail_band);
+        e = launch_su(p, plan.mode, plan.f64out, s);
+    }
     for (size_t k = 0; k < plan.pu.size() && e == hipSuccess; ++k) {
         const PuItem &u = plan.pu[k];
         if (u.count > 0)

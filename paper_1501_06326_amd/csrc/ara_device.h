@@ -22,7 +22,14 @@ __device__ __forceinline__ void report(Status *st, int32_t code, int64_t a, int6
     }
 }
 
+// A product and the terms applied to it, each rounded: every pass over the same
+// hit must give the same bits, so no pass may fuse them.
+__device__ __forceinline__ float mul_rn(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
 __device__ __forceinline__ float clampf_terms(float x, float r, float l) {
+#pragma clang fp contract(off)
     return fminf(fmaxf(x - r, 0.0f), l);
 }
 __device__ __forceinline__ double clampd_terms(double x, double r, double l) {

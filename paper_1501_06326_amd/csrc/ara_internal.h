@@ -19,8 +19,11 @@ enum : uint32_t {
     ROW_CORR = 1u << 18,   // sigma_I > 0 and sigma_C > 0: mix two normals (section 3.2)
     ROW_CONLY = 1u << 19,  // sigma_I = 0, sigma_C > 0: z = u_C
     ROW_FLAGS = 0xFu << 16,
-    // layer flag: a row that can pay draws and has no shape slot
+    // layer flag: a row that can pay draws and has no shape slot (the full pass)
     LAYER_SLOW = 1u << 31,
+    // layer flag: no event table (an event with more paying rows than a nibble holds,
+    // or more rows than a mark indexes)
+    LAYER_DENSE = 1u << 30,
 };
 __host__ __device__ inline int meta_na(uint32_t m) { return (int)((m >> 20) & 63u); }
 __host__ __device__ inline int meta_nb(uint32_t m) { return (int)((m >> 26) & 63u); }
@@ -38,7 +41,8 @@ struct LayerDev {
     int32_t nnz;                         // non-zero entries of otab (PU)
     uint32_t program_id;                 // keys z_(Prog,E) under ARA_KEYING_PAPER
     int32_t keying;                      // ARA_KEYING_* of the portfolio
-    int32_t pad;
+    int32_t chunk;                       // occurrences a chunk of the table form takes: 64,
+                                         // or fewer so that their hits fit one segment
     int64_t live_base;                   // even index of the layer's (ev_off[E], rows of E
                                          // that can pay) pairs in the ev_off array
 };
@@ -97,6 +101,9 @@ struct Status {
 };
 
 constexpr int kWave = 64;
+// Occurrences of a trial that a wavefront of the secondary-uncertainty passes holds
+// in LDS at a time.
+constexpr int kSeg = 512;
 
 // Shapes the FP32 quantile covers (its error stays below ~1e-6 of the root
 // there); others take the FP64 path.
@@ -139,6 +146,19 @@ constexpr int kShapeStride = kSlotDev + kDevSegs * kSegCoefs;
 // after a portfolio's slots: Phi^-1(p 2^-24) by octave of p, the same segments
 constexpr int kNormFloats = kOctaves * kSegCoefs;
 
+// Positions of a segment's hits in the lean pass' LDS (one wavefront's), and the
+// bits of a position's mark that hold the layer's record index.
+constexpr int kLp = 768;
+constexpr int kMarkRow = 22;
+
+// Event table of a layer (catalogues of at most kTabGroups groups): per group of
+// 16 events 64 bits of paying-row counts and the group's first record, 3 words.
+// kTabGroups is what the LDS of a CU holds beside the segments of 16 wavefronts
+// (163,840 - 16 x 4,144 - 1,024 bytes).
+constexpr int kTabGroup = 16;
+constexpr int kTabGroups = 8032;
+constexpr int kTabWaves = 16;
+
 }  // namespace ara
 
 // Host-side handle definitions (not visible to the C-ABI).
@@ -175,6 +195,7 @@ struct ara_portfolio {
     uint32_t *d_row_shape;     // per row: 1 + its shape slot, or 0
     unsigned long long *d_shape_keys;   // [layer][kShapeSlots]: (alpha, beta) bits, 0 = unused
     float *d_shape_tab;        // [layer][kShapeSlots][kShapeStride], then [kNormFloats]
+    uint32_t *d_evtab;         // per layer: nibbles [2 groups], first records [groups]; or null
     float *d_otab;
     uint32_t *d_sp_bits;       // per layer [nw]: bitmap of the non-zero otab entries
     uint32_t *d_sp_rank;       // per layer [nw + 1]: set bits before each word

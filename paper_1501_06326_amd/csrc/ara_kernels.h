@@ -55,6 +55,10 @@ struct SuLaunch {
     uint32_t *redo_count;     // scratch counter
     int redo_grid;            // blocks of the second pass
     int full;                 // rows the lean pass cannot take: the full pass over every trial
+    const LayerDev *h_layers; // host copies of the layers (the table form)
+    const uint32_t *evtab;    // the layers' event tables; null: the one-wavefront form
+    int32_t n_cat;
+    int n_cu;
     int32_t f64_iters;        // step limit of the FP64 quantile
     const float *shape_tab;   // shape tables [layer][kShapeSlots][kShapeStride]
     const uint32_t *row_shape;   // per row: 1 + shape slot, or 0
@@ -114,6 +118,9 @@ hipError_t launch_build_layer(const RawRow *raw, const RowFit *fit, const int64_
                               RowF *rowf, float *row_mean,
                               float *row_cfrac, uint32_t *row_meta, double *row_lnb, float *otab,
                               Status *st, hipStream_t s);
+// the layer's event table (see kTabGroup) from its (first record, rows) pairs
+hipError_t launch_event_table(const uint32_t *pairs, int32_t n_cat, uint32_t *tab, LayerDev *d_layer,
+                              hipStream_t s);
 hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s);
 hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits, uint32_t *rank,
                                float *vals, LayerDev *d_layer, hipStream_t s);

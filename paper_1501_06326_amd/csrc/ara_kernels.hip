@@ -653,6 +653,37 @@ hipError_t launch_build_layer(const RawRow *raw, const RowFit *fit, const int64_
     return hipGetLastError();
 }
 
+// The event table of one layer from its (first record, paying rows) pairs.
+__global__ void k_ev_table(const uint2 *__restrict__ pairs, int32_t n_cat, int32_t groups,
+                           uint32_t *__restrict__ tab, LayerDev *__restrict__ layer) {
+    uint32_t top = 0;
+    for (int32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < groups; g += gridDim.x * blockDim.x) {
+        uint64_t w = 0;
+        uint32_t most = 0;
+        for (int i = 0; i < kTabGroup; ++i) {
+            const int32_t e = g * kTabGroup + i;
+            const uint32_t c = e < n_cat ? pairs[e].y : 0u;
+            most = max(most, c);
+            w |= (uint64_t)(c & 15u) << (4 * i);
+        }
+        tab[2 * g] = (uint32_t)w;
+        tab[2 * g + 1] = (uint32_t)(w >> 32);
+        tab[2 * groups + g] = pairs[g * kTabGroup].x;
+        top = max(top, most);
+    }
+    if (top > 15u || layer->n_rows >= (1 << kMarkRow)) atomicOr(&layer->flags, LAYER_DENSE);
+    // a chunk of the table form: as many occurrences as surely fit a segment's hits
+    if (top > (uint32_t)(kLp / kWave)) atomicMin(&layer->chunk, (int32_t)((uint32_t)kLp / top));
+}
+
+hipError_t launch_event_table(const uint32_t *pairs, int32_t n_cat, uint32_t *tab, LayerDev *d_layer,
+                              hipStream_t s) {
+    const int32_t groups = (n_cat + kTabGroup - 1) / kTabGroup;
+    hipLaunchKernelGGL(k_ev_table, dim3(grid_for(groups, 256)), dim3(256), 0, s,
+                       reinterpret_cast<const uint2 *>(pairs), n_cat, groups, tab, d_layer);
+    return hipGetLastError();
+}
+
 hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits, uint32_t *rank,
                                float *vals, LayerDev *d_layer, hipStream_t s) {
     const int32_t nw = (n_cat + 31) >> 5;

@@ -180,12 +180,30 @@ __device__ __forceinline__ int grid_octave(uint32_t j, bool *upper, float *d) {
     return (int)(bits >> 23) - 127;
 }
 
+// min(z, 1 - z) of the draw z = j 2^-24.
+__device__ __forceinline__ float grid_tail(uint32_t j) {
+    return (float)min(j, 16777216u - j) * 5.9604644775390625e-08f;
+}
+
+// Segment of a slot (offset in floats) and local coordinate of a draw.
+__device__ __forceinline__ uint32_t slot_segment(uint32_t j, float *d) {
+    bool upper;
+    const int e = grid_octave(j, &upper, d);
+    return (uint32_t)(kSlotOct + kSegCoefs * (e + (upper ? kOctaves : 0)));
+}
+
+// The same of a normal deviate v, |v| <= kDevMax.
+__device__ __forceinline__ uint32_t dev_segment(float v, float *d) {
+    const float i = rintf(2.0f * v);
+    *d = fmaf(2.0f, v, -i);
+    return (uint32_t)(kSlotDev + kSegCoefs * min(max((int)i + kDevHalf, 0), kDevSegs - 1));
+}
+
 // The quantile of a slot's shape at the draw z = j 2^-24.
 __device__ __forceinline__ float slot_quantile(const float *slot, uint32_t j) {
-    bool upper;
     float d;
-    const int e = grid_octave(j, &upper, &d);
-    return seg_poly(slot + kSlotOct + kSegCoefs * (e + (upper ? kOctaves : 0)), d);
+    const uint32_t at = slot_segment(j, &d);
+    return seg_poly(slot + at, d);
 }
 
 // Phi^-1(j 2^-24) from the normal segments.
@@ -199,9 +217,9 @@ __device__ __forceinline__ float norm_dev(const float *norm, uint32_t j) {
 
 // The quantile of a slot's shape at z = Phi(v), |v| <= kDevMax.
 __device__ __forceinline__ float slot_quantile_dev(const float *slot, float v) {
-    const float i = rintf(2.0f * v);
-    const int seg = min(max((int)i + kDevHalf, 0), kDevSegs - 1);
-    return seg_poly(slot + kSlotDev + kSegCoefs * seg, fmaf(2.0f, v, -i));
+    float d;
+    const uint32_t at = dev_segment(v, &d);
+    return seg_poly(slot + at, d);
 }
 
 // I_x(a,b) (*I) and 1 - I_x(a,b) (*Ic), each on the side where it is

@@ -125,3 +125,52 @@ def test_full_pass_queues(ara, n_occ):
         assert torch.equal(ara.run_batch(y, [p, p], cfg=cfg)[1]["ylt"], r)
     ara.free_portfolio(p)
     ara.free_yet(y)
+
+
+def table_case(n_cat, n_elts, rows, n_trials, lam, layers=1, seed=3, **kw):
+    """A YET and a portfolio of slotted rows for the event-table form."""
+    from workloads import YET, Layer, Portfolio, make_elt
+    rng = np.random.default_rng(seed)
+    counts = rng.poisson(lam, n_trials)
+    counts[:4] = [0, 1, 511, 1537]
+    off = np.zeros(n_trials + 1, np.int64)
+    off[1:] = np.cumsum(counts)
+    yet = YET(offsets=off, event_ids=rng.integers(0, n_cat, off[-1]).astype(np.int32), times=None,
+              n_catalogue=n_cat)
+    ls = [Layer(elts=[make_elt(100 * l + e, rows, n_cat, 77 + 10 * l + e, retention=1e5, limit=5e7)
+                      for e in range(n_elts)], occ_retention=1e5 * (l + 1), occ_limit=2e8,
+                agg_retention=1e6, agg_limit=1e12, program_id=l) for l in range(layers)]
+    return yet, Portfolio(layers=ls, seed=5, **kw)
+
+
+# catalogues at the edges of a 16-event group and of the largest table (8,032
+# groups); tables sparse, of up to 15 rows an event (chunks of 51) and of more
+# (no table form); one layer and several; both keyings; a tail band that abandons
+# trials in single layers.
+@pytest.mark.parametrize("n_cat,n_elts,rows,layers,keying,band", [
+    (33, 3, 20, 1, 0, 0.0), (4096, 15, 3900, 1, 1, 0.0), (4097, 17, 4097, 1, 0, 0.0),
+    (128_512, 2, 30_000, 2, 0, 0.0), (128_513, 2, 30_000, 2, 0, 0.0), (9_999, 6, 2_000, 4, 0, 1e-5)])
+def test_table_form_equals_slices(ara, n_cat, n_elts, rows, layers, keying, band):
+    """A run large enough for the event-table form gives the YLT and the
+    occurrence view of the same trials run in slices too small for it, bit for
+    bit, and a batch the same."""
+    n = 65_536 // layers
+    yet, pf = table_case(n_cat, n_elts, rows, n, 520, layers, keying=keying)
+    print("table form", n_cat, n_elts, rows, layers, flush=True)
+    y = ara.load_yet(yet)
+    p = ara.load_portfolio(pf, n_cat)
+    r = ara.run(y, p, tail_band=band)
+    for a, b in ((0, 4000), (n - 3000, n)):
+        s = ara.run(y, p, trial_begin=a, trial_count=b - a, tail_band=band)
+        assert torch.equal(r["ylt"][:, a:b], s["ylt"])
+        assert torch.equal(r["ylt_pf"][a:b], s["ylt_pf"])
+    assert float(r["ylt"].max()) > 0
+    v = ara.run(y, p, occ_view=True, tail_band=band)
+    assert torch.equal(v["ylt"], r["ylt"])
+    s = ara.run(y, p, trial_count=4000, occ_view=True, tail_band=band)
+    assert torch.equal(v["occ_view"][:, :s["occ_view"].shape[1]], s["occ_view"])
+    if band == 0.0:
+        o = ara.run_batch(y, [p, p])
+        assert all(torch.equal(q["ylt"], r["ylt"]) and torch.equal(q["ylt_pf"], r["ylt_pf"]) for q in o)
+    ara.free_portfolio(p)
+    ara.free_yet(y)
