@@ -89,8 +89,8 @@ def kernel_sources_sha256():
     import re
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_1501_06326_amd", "csrc")
-    for f in ("ara_kernels.hip", "ara_su.hip", "ara_su.h", "ara_device.h", "ara_math.h",
-              "ara_internal.h", "ara_kernels.h", "ara_probe.hip"):
+    for f in ("ara_kernels.hip", "ara_pu.hip", "ara_su.hip", "ara_su.h", "ara_device.h",
+              "ara_math.h", "ara_internal.h", "ara_kernels.h", "ara_probe.hip"):
         with open(os.path.join(csrc, f), encoding="utf-8") as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)

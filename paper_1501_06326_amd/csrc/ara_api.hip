@@ -3,6 +3,7 @@
 // reporting.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -266,32 +267,56 @@ hipError_t enqueue_pu(const ara_context *ctx, const ara_yet *yet, const ara_port
                       int64_t begin, int64_t count, int32_t sum_mode, bool f64out,
                       void *ylt_layers, void *ylt_pf, void *occ_view, int64_t occ_stride,
                       Status *status, hipStream_t s) {
-    const size_t nwc = ((size_t)pf->n_catalogue + 31) / 32;
-    for (int l = 0; l < pf->n_layers; ++l) {
+    const size_t nw = ((size_t)pf->n_catalogue + 31) / 32;
+    const size_t dense = sizeof(float) * (size_t)pf->n_catalogue, bits = sizeof(uint32_t) * nw;
+    auto sparse = [&](int l) {
+        return sizeof(uint32_t) * (2 * nw + 1 + (size_t)pf->h_layers[l].nnz);
+    };
+    // occurrences of the run, from the table's mean trial
+    const double occ = (double)yet->n_occ * (double)count / (double)std::max<int64_t>(yet->n_trials, 1);
+    const bool large = occ >= kPuLargeOcc;
+    for (int l = 0; l < pf->n_layers;) {
         PuLaunch p;
         p.off = yet->d_off;
         p.ev = yet->d_ev;
         p.trial_begin = begin;
         p.trial_count = count;
-        p.otab = pf->d_otab + (int64_t)l * pf->n_catalogue;
-        p.sp_bits = pf->d_sp_bits + (size_t)l * nwc;
-        p.sp_rank = pf->d_sp_rank + (size_t)l * (nwc + 1);
-        p.sp_vals = pf->d_sp_vals + (size_t)l * pf->n_catalogue;
-        p.nnz = pf->h_layers[l].nnz;
         p.n_cat = pf->n_catalogue;
-        p.agg_r = pf->h_layers[l].agg_r;
-        p.agg_l = pf->h_layers[l].agg_l;
-        p.layer = l;
+        p.n_cu = ctx->n_cu;
         p.ylt_layers = ylt_layers;
         p.ylt_pf = ylt_pf;
         p.accumulate_pf = l > 0;
         p.occ_view = occ_view;
         p.occ_stride = occ_stride;
         p.status = status;
-        // blocks of 16 wavefronts, two resident per CU (LDS table <= 60 KB)
-        const int64_t blocks = (count + 15) / 16;
-        const int64_t g = blocks < (int64_t)ctx->n_cu * 2 ? blocks : (int64_t)ctx->n_cu * 2;
-        p.grid = (int)(g < 1 ? 1 : g);
+        p.n_layers = 1;
+        if (dense <= 32 * 1024) {
+            p.form = PU_DENSE;
+            p.lds = dense;
+        } else if (sparse(l) <= (large ? kPuLdsOne : kPuLdsTwo)) {
+            p.form = PU_SPARSE;
+            p.lds = sparse(l);
+            while (!occ_view && p.n_layers < kPuLayers && l + p.n_layers < pf->n_layers &&
+                   p.lds + sparse(l + p.n_layers) <= kPuLdsOne)
+                p.lds += sparse(l + p.n_layers++);
+        } else if (large && bits <= kPuLdsOne) {
+            p.form = PU_BITS;
+            p.lds = bits;
+        } else {
+            p.form = PU_GLOBAL;
+            p.lds = 0;
+        }
+        for (int u = 0; u < p.n_layers; ++u, ++l) {
+            PuTable &T = p.tab[u];
+            T.otab = pf->d_otab + (int64_t)l * pf->n_catalogue;
+            T.bits = pf->d_sp_bits + (size_t)l * nw;
+            T.rank = pf->d_sp_rank + (size_t)l * (nw + 1);
+            T.vals = pf->d_sp_vals + (size_t)l * pf->n_catalogue;
+            T.nnz = pf->h_layers[l].nnz;
+            T.agg_r = pf->h_layers[l].agg_r;
+            T.agg_l = pf->h_layers[l].agg_l;
+            T.layer = l;
+        }
         const hipError_t e = launch_pu(p, sum_mode, f64out, s);
         if (e != hipSuccess) return e;
     }

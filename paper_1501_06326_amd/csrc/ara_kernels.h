@@ -8,22 +8,39 @@
 
 namespace ara {
 
+// One layer of a primary-uncertainty pass: its per-event occurrence losses, dense
+// and sparse (bitmap [nw], rank [nw + 1], values [nnz]), and its aggregate terms.
+struct PuTable {
+    const float *otab;
+    const uint32_t *bits, *rank;
+    const float *vals;
+    int32_t nnz;
+    float agg_r, agg_l;
+    int32_t layer;
+};
+constexpr int kPuLayers = 4;                  // layers a pass takes together
+constexpr size_t kPuLdsOne = 156 * 1024;      // LDS of one block per CU
+constexpr size_t kPuLdsTwo = 78 * 1024;       // of each of two
+// Occurrences from which a layer whose table leaves a CU one block (or that needs the
+// bitmap form) takes it: each block stages up to 156 KB first.  250,000 events,
+// scattered loads against LDS: 2M occurrences 14 - 19 us against 13 - 24 us (by trial
+// length), 4M 22 - 25 us against 14 - 21 us, 64M 295 - 342 us against 86 - 262 us.
+constexpr double kPuLargeOcc = 4e6;
+enum { PU_GLOBAL = 0, PU_DENSE, PU_SPARSE, PU_BITS };
+
 struct PuLaunch {
     const int64_t *off;
     const int32_t *ev;
     int64_t trial_begin, trial_count;
-    const float *otab;          // the layer's per-event occurrence losses [n_cat]
-    const uint32_t *sp_bits;    // its sparse form: bitmap [nw], rank [nw + 1], values [nnz]
-    const uint32_t *sp_rank;
-    const float *sp_vals;
-    int32_t nnz;
+    PuTable tab[kPuLayers];     // consecutive layers
+    int n_layers;               // more than one: PU_SPARSE without a view
+    int form;                   // PU_*: where the tables are read from
+    size_t lds;                 // bytes of them in LDS
     int32_t n_cat;
-    float agg_r, agg_l;
-    int32_t layer;
+    int n_cu;
     void *ylt_layers;
     void *ylt_pf;
     int32_t accumulate_pf;      // 0: ylt_pf = Y, 1: ylt_pf += Y
-    int grid;
     void *occ_view;             // optional occurrence view (see ara_run_opts)
     int64_t occ_stride;
     Status *status;

@@ -360,175 +360,6 @@ __global__ void k_sp_vals(const float *__restrict__ otab, int32_t n_cat,
     if (blockIdx.x == 0 && threadIdx.x == 0) layer->nnz = (int32_t)rank[nw];
 }
 
-struct PuArgs {
-    const int64_t *off;
-    const int32_t *ev;
-    int64_t trial_begin, trial_count;
-    const float *otab;
-    const uint32_t *sp_bits, *sp_rank;
-    const float *sp_vals;
-    int32_t nnz, n_cat;
-    float agg_r, agg_l;
-    int32_t layer;
-    void *ylt_layers, *ylt_pf;
-    int32_t accumulate_pf;
-    void *occ_view;
-    int64_t occ_stride;
-    Status *status;
-};
-
-enum { TAB_GLOBAL = 0, TAB_LDS_DENSE = 1, TAB_LDS_SPARSE = 2 };
-
-// The layer's per-event occurrence-loss table, staged by the whole block in
-// LDS (dense, or sparse: a bit per event, the rank of each 32-event word and
-// the non-zero values) or read from global memory (catalogues too large).
-template <int TAB>
-__device__ __forceinline__ void pu_stage_table(const PuArgs &P, uint32_t *sm) {
-    const int32_t nw = (P.n_cat + 31) >> 5;
-    if (TAB == TAB_LDS_DENSE) {
-        float *tab = (float *)sm;
-        for (int i = threadIdx.x; i < P.n_cat; i += blockDim.x) tab[i] = P.otab[i];
-    } else if (TAB == TAB_LDS_SPARSE) {
-        uint32_t *bits = sm, *rank = sm + nw;
-        float *vals = (float *)(sm + 2 * nw + 1);
-        for (int i = threadIdx.x; i < nw; i += blockDim.x) bits[i] = P.sp_bits[i];
-        for (int i = threadIdx.x; i <= nw; i += blockDim.x) rank[i] = P.sp_rank[i];
-        for (int i = threadIdx.x; i < P.nnz; i += blockDim.x) vals[i] = P.sp_vals[i];
-    }
-    if (TAB != TAB_GLOBAL) __syncthreads();
-}
-
-template <int TAB>
-__device__ __forceinline__ float pu_look(const PuArgs &P, const uint32_t *sm, int32_t E) {
-    if (TAB == TAB_GLOBAL) return P.otab[E];
-    if (TAB == TAB_LDS_DENSE) return ((const float *)sm)[E];
-    const int32_t nw = (P.n_cat + 31) >> 5;
-    const uint32_t w = sm[E >> 5];
-    const uint32_t m = 1u << (E & 31);
-    return (w & m) ? ((const float *)(sm + 2 * nw + 1))[sm[nw + (E >> 5)] + __popc(w & (m - 1u))]
-                   : 0.0f;
-}
-
-// Occurrence view of a primary-uncertainty layer (one wavefront per trial):
-// the per-event occurrence losses of the layer's table, in stored order.  The
-// table sits in LDS as for the YLT pass (16-wavefront blocks sharing a copy):
-// read from global memory, its 64 scattered lookups per chunk load the L2
-// with a request per lane.
-template <bool F64OUT, int TAB>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_pu_occ_view(PuArgs P) {
-    extern __shared__ uint32_t sm[];
-    pu_stage_table<TAB>(P, sm);
-    const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const int64_t nwv = (int64_t)gridDim.x * (blockDim.x / 64);
-    const int64_t base = P.off[P.trial_begin];
-    for (int64_t t = wid; t < P.trial_count; t += nwv) {
-        const int64_t a = P.off[P.trial_begin + t], b = P.off[P.trial_begin + t + 1];
-        double cs = 0.0, ca = 0.0;
-        for (int64_t c = a; c < b; c += 64) {
-            const int64_t j = c + lane;
-            const bool valid = j < b;
-            const double o =
-                valid ? (double)pu_look<TAB>(P, sm, __builtin_nontemporal_load(P.ev + j)) : 0.0;
-            occ_chunk<F64OUT>(o, valid, j - base, P.layer, P.occ_view, P.occ_stride, P.agg_r,
-                              P.agg_l, &cs, &ca, P.status, P.trial_begin + t);
-        }
-    }
-}
-
-// A 16-byte load of the event-id stream, marked non-temporal: every id is read
-// once, so it should not displace the cached tables (11 % faster for the
-// primary-uncertainty pass, 0.76 -> 0.67 ms at the full shape).
-__device__ __forceinline__ int4 ld_stream(const int4 *p) {
-    typedef int i32x4 __attribute__((ext_vector_type(4)));
-    const i32x4 g = __builtin_nontemporal_load(reinterpret_cast<const i32x4 *>(p));
-    return make_int4(g.x, g.y, g.z, g.w);
-}
-
-// One wavefront per trial (persistent grid-stride over trials).  With the
-// table in LDS a block is 16 wavefronts sharing one copy, two blocks per CU
-// (32 wavefronts: the LDS copy per wavefront is what limited occupancy);
-// with the table in global memory blocks are 4 wavefronts.  Event ids are
-// streamed with 16-byte loads (after a scalar head that reaches 16-byte
-// alignment), four loads in flight per lane.
-template <int MODE, bool F64OUT, int TAB>
-__device__ __forceinline__ void pu_trials(const PuArgs &P) {
-    extern __shared__ uint32_t sm[];
-    pu_stage_table<TAB>(P, sm);
-    auto look = [&](int32_t E) -> float { return pu_look<TAB>(P, sm, E); };
-    const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const int64_t nwv = (int64_t)gridDim.x * (blockDim.x / 64);
-    for (int64_t t = wid; t < P.trial_count; t += nwv) {
-        const int64_t a = P.off[P.trial_begin + t], b = P.off[P.trial_begin + t + 1];
-        const int64_t n = b - a;
-        Acc<MODE> acc;
-        // the four losses of one 16-byte load: compensated summation adds
-        // their pairwise sum (error within 2 ulp of the group, so the trial's
-        // error stays a few ulp of its total whatever its length) at a
-        // quarter of the per-element cost; the other modes add them one by one
-        auto add4 = [&](const int4 q) {
-            if (MODE == ARA_SUM_KAHAN32) {
-                acc.add((look(q.x) + look(q.y)) + (look(q.z) + look(q.w)));
-            } else {
-                acc.add(look(q.x)); acc.add(look(q.y)); acc.add(look(q.z)); acc.add(look(q.w));
-            }
-        };
-        // int32 elements up to the next 16-byte boundary of the event-id stream
-        int64_t head = (int64_t)(((16u - ((uint32_t)(uintptr_t)(P.ev + a) & 15u)) & 15u) >> 2);
-        if (head > n) head = n;
-        if (lane < head) acc.add(look(P.ev[a + lane]));
-        const int4 *v4 = (const int4 *)(P.ev + a + head);
-        const int64_t n4 = (n - head) >> 2;
-        for (int64_t i = lane; i < n4; i += 4 * 64) {
-            const bool h1 = i + 64 < n4, h2 = i + 128 < n4, h3 = i + 192 < n4;
-            const int4 q0 = ld_stream(v4 + i);
-            int4 q1 = make_int4(0, 0, 0, 0), q2 = q1, q3 = q1;
-            if (h1) q1 = ld_stream(v4 + i + 64);
-            if (h2) q2 = ld_stream(v4 + i + 128);
-            if (h3) q3 = ld_stream(v4 + i + 192);
-            add4(q0);
-            if (h1) add4(q1);
-            if (h2) add4(q2);
-            if (h3) add4(q3);
-        }
-        const int64_t done = head + 4 * n4;
-        if (lane < n - done) acc.add(look(P.ev[a + done + lane]));
-        const double S = acc.total();
-        if (lane == 0) {
-            double Y;
-            if (MODE == ARA_SUM_F64) Y = clampd_terms(S, (double)P.agg_r, (double)P.agg_l);
-            else Y = (double)clampf_terms((float)S, P.agg_r, P.agg_l);
-            if (F64OUT) {
-                if (P.ylt_layers) ((double *)P.ylt_layers)[(int64_t)P.layer * P.trial_count + t] = Y;
-                if (P.ylt_pf) {
-                    double *p = (double *)P.ylt_pf + t;
-                    *p = P.accumulate_pf ? *p + Y : Y;
-                }
-            } else {
-                if (P.ylt_layers)
-                    ((float *)P.ylt_layers)[(int64_t)P.layer * P.trial_count + t] = (float)Y;
-                if (P.ylt_pf) {
-                    float *p = (float *)P.ylt_pf + t;
-                    *p = P.accumulate_pf ? *p + (float)Y : (float)Y;
-                }
-            }
-        }
-    }
-}
-
-// Table in LDS: 16 wavefronts per block, 8 per SIMD (two blocks per CU).
-template <int MODE, bool F64OUT, int TAB>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ara_pu(PuArgs P) {
-    pu_trials<MODE, F64OUT, TAB>(P);
-}
-
-// Table in global memory (catalogues too large for LDS): 4 wavefronts per block.
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7, 7))) void k_ara_pu_global(PuArgs P) {
-    pu_trials<MODE, F64OUT, TAB_GLOBAL>(P);
-}
-
 // ---------------------------------------------------------------------------
 // diagnostics
 // ---------------------------------------------------------------------------
@@ -693,49 +524,6 @@ hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits,
     hipLaunchKernelGGL(k_sp_vals, dim3(grid_for(nw, 256)), dim3(256), 0, s, otab, n_cat, bits, rank,
                        vals, d_layer);
     return hipGetLastError();
-}
-
-template <int MODE, bool F64OUT>
-static hipError_t pu_dispatch(const PuLaunch &p, hipStream_t s) {
-    PuArgs A;
-    A.off = p.off; A.ev = p.ev; A.trial_begin = p.trial_begin; A.trial_count = p.trial_count;
-    A.otab = p.otab; A.sp_bits = p.sp_bits; A.sp_rank = p.sp_rank; A.sp_vals = p.sp_vals;
-    A.nnz = p.nnz; A.n_cat = p.n_cat; A.agg_r = p.agg_r; A.agg_l = p.agg_l; A.layer = p.layer;
-    A.ylt_layers = p.ylt_layers; A.ylt_pf = p.ylt_pf; A.accumulate_pf = p.accumulate_pf;
-    A.occ_view = p.occ_view; A.occ_stride = p.occ_stride; A.status = p.status;
-    const size_t nw = ((size_t)p.n_cat + 31) / 32;
-    const size_t dense = (size_t)p.n_cat * sizeof(float);
-    const size_t sparse = (2 * nw + 1 + (size_t)p.nnz) * sizeof(uint32_t);
-    // p.grid counts blocks of 16 wavefronts (two per CU at most)
-    const dim3 g(p.grid), b(1024);
-    if (p.occ_view) {
-        if (dense <= 32 * 1024)
-            hipLaunchKernelGGL((k_pu_occ_view<F64OUT, TAB_LDS_DENSE>), g, b, dense, s, A);
-        else if (sparse <= 60 * 1024)
-            hipLaunchKernelGGL((k_pu_occ_view<F64OUT, TAB_LDS_SPARSE>), g, b, sparse, s, A);
-        else
-            hipLaunchKernelGGL((k_pu_occ_view<F64OUT, TAB_GLOBAL>), dim3(p.grid * 4), dim3(256), 0,
-                               s, A);
-    }
-    if (dense <= 32 * 1024) {
-        hipLaunchKernelGGL((k_ara_pu<MODE, F64OUT, TAB_LDS_DENSE>), g, b, dense, s, A);
-    } else if (sparse <= 60 * 1024) {
-        hipLaunchKernelGGL((k_ara_pu<MODE, F64OUT, TAB_LDS_SPARSE>), g, b, sparse, s, A);
-    } else {
-        const int64_t g4 = (p.trial_count + 3) / 4 < (int64_t)p.grid * 8 ? (p.trial_count + 3) / 4
-                                                                         : (int64_t)p.grid * 8;
-        hipLaunchKernelGGL((k_ara_pu_global<MODE, F64OUT>), dim3((unsigned)g4), dim3(256), 0, s, A);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s) {
-    if (p.trial_count <= 0) return hipSuccess;
-    if (mode == ARA_SUM_NAIVE32) return f64out ? pu_dispatch<ARA_SUM_NAIVE32, true>(p, s)
-                                               : pu_dispatch<ARA_SUM_NAIVE32, false>(p, s);
-    if (mode == ARA_SUM_KAHAN32) return f64out ? pu_dispatch<ARA_SUM_KAHAN32, true>(p, s)
-                                               : pu_dispatch<ARA_SUM_KAHAN32, false>(p, s);
-    return f64out ? pu_dispatch<ARA_SUM_F64, true>(p, s) : pu_dispatch<ARA_SUM_F64, false>(p, s);
 }
 
 hipError_t launch_scan_excl_u32(uint32_t *p, int64_t n, hipStream_t s) {
