@@ -183,7 +183,7 @@ struct Layout {
     size_t layers, elts, evoff, liveoff, rowq, rowf, row_mean, row_cfrac, row_meta, row_lnb,
         row_shape, shape_keys, shape_tab, evtab, otab,
         sp_bits, sp_rank,
-        sp_vals, raw, rawfit, eltoff, dat, total;
+        sp_vals, raw, rawfit, rank, parts, eltoff, dat, total;
     int64_t n_rows = 0;
     int32_t n_elts = 0, max_layer_elts = 0;
 };
@@ -257,6 +257,8 @@ ara_status plan(ara_context *ctx, const ara_portfolio_desc *d, int32_t n_cat, La
     L->sp_vals = o; o += pu ? align256(sizeof(float) * (size_t)nl * n_cat) : 0;
     L->raw = o; o += align256(sizeof(RawRow) * (size_t)(rows ? rows : 1));
     L->rawfit = o; o += align256(sizeof(RowFit) * (size_t)(rows ? rows : 1));
+    L->rank = o; o += align256(sizeof(uint32_t) * (size_t)(rows ? rows : 1));
+    L->parts = o; o += align256(sizeof(uint32_t) * 2 * (size_t)ev_tiles(n_cat));
     L->eltoff = o; o += align256(sizeof(int64_t) * (size_t)(ne + 1));
     L->dat = o; o += align256(sizeof(int32_t) * (size_t)(mx ? mx : 1) * n_cat);
     L->total = o;
@@ -671,7 +673,7 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
         ARA_HIP_P(launch_build_layer(d_raw, d_fit, d_eltoff, p->d_elts, p->d_layers + l, hl[l],
                                      n_catalogue,
                                      p->su_enabled, d_dat, p->d_evoff, liveoff_l,
-                                     p->d_rowq, p->d_rowf, p->d_row_mean,
+                                     (uint32_t *)(w + L.rank), (uint32_t *)(w + L.parts), p->d_rowq, p->d_rowf, p->d_row_mean,
                                      p->d_row_cfrac, p->d_row_meta, p->d_row_lnb, p->d_otab,
                                      ctx->d_status, s));
         if (p->su_enabled)

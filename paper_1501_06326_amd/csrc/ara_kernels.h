@@ -8,6 +8,10 @@
 
 namespace ara {
 
+// Events per block of the load's per-event passes (they cover n_cat + 1 offsets).
+constexpr int kEvTile = 256;
+inline int32_t ev_tiles(int32_t n_cat) { return (int32_t)(((int64_t)n_cat + kEvTile) / kEvTile); }
+
 // One layer of a primary-uncertainty pass: its per-event occurrence losses, dense
 // and sparse (bitmap [nw], rank [nw + 1], values [nnz]), and its aggregate terms.
 struct PuTable {
@@ -128,11 +132,13 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_check_rows(const RawRow *raw, int64_t n, int32_t n_cat, int32_t su, Status *st,
                              hipStream_t s);
 hipError_t launch_fit_rows(const RawRow *raw, int64_t n, int32_t su, RowFit *fit, hipStream_t s);
+// (rank: a word per row of the portfolio; parts: two per tile of kEvTile events, of
+// the layer being built)
 hipError_t launch_build_layer(const RawRow *raw, const RowFit *fit, const int64_t *elt_row_off,
                               const EltDev *elts,
                               LayerDev *d_layer, const LayerDev &h_layer, int32_t n_cat, int32_t su,
-                              int32_t *dat, uint32_t *evoff, uint32_t *liveoff, RowQ *rowq,
-                              RowF *rowf, float *row_mean,
+                              int32_t *dat, uint32_t *evoff, uint32_t *liveoff, uint32_t *rank,
+                              uint32_t *parts, RowQ *rowq, RowF *rowf, float *row_mean,
                               float *row_cfrac, uint32_t *row_meta, double *row_lnb, float *otab,
                               Status *st, hipStream_t s);
 // the layer's event table (see kTabGroup) from its (first record, rows) pairs
@@ -147,7 +153,6 @@ hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int
                         bool full, hipStream_t s);
 // exclusive prefix sum of p[0, n) in place (one block; also used by the
 // exceedance-curve sort for its digit counts)
-hipError_t launch_scan_excl_u32(uint32_t *p, int64_t n, hipStream_t s);
 hipError_t launch_debug_philox(int64_t n, const uint32_t *ctr, uint64_t key, uint32_t *out,
                                hipStream_t s);
 hipError_t launch_debug_quantile(int64_t n, const float *a, const float *b, const double *z,

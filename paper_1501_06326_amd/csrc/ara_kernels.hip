@@ -116,7 +116,7 @@ __global__ void k_check_rows(const RawRow *__restrict__ raw, int64_t n, int32_t 
 // one ELT is a duplicate.
 __global__ void k_dat_scatter(const RawRow *__restrict__ raw, const int64_t *__restrict__ elt_row_off,
                               int32_t elt_begin, int32_t n_elts, int32_t n_cat,
-                              int32_t *__restrict__ dat, Status *st) {
+                              int32_t *__restrict__ dat, uint32_t *__restrict__ rank, Status *st) {
     const int64_t r0 = elt_row_off[elt_begin], r1 = elt_row_off[elt_begin + n_elts];
     for (int64_t r = r0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < r1;
          r += (int64_t)gridDim.x * blockDim.x) {
@@ -126,6 +126,7 @@ __global__ void k_dat_scatter(const RawRow *__restrict__ raw, const int64_t *__r
             if (elt_row_off[elt_begin + mid] <= r) lo = mid; else hi = mid - 1;
         }
         const int32_t e = raw[r].event;
+        rank[r] = ~0u;                 // until k_ev_count finds the row
         if (e < 0 || e >= n_cat) continue;
         const int32_t old = atomicCAS(&dat[(int64_t)lo * n_cat + e], -1, (int32_t)(r - r0));
         if (old != -1) report(st, ARA_E_BAD_ELT_ROW, -2, r, e);
@@ -142,32 +143,66 @@ __device__ __forceinline__ bool row_cannot_pay(const RawRow &rr, const EltDev &e
     return scale <= ed.retention || ed.limit == 0.0f || ed.share == 0.0f;
 }
 
-// Rows per catalogue event in the layer (evoff) and rows that can pay (liveoff).
-__global__ void k_ev_count(const int32_t *__restrict__ dat, const RawRow *__restrict__ raw,
-                           const int64_t *__restrict__ elt_row_off, const EltDev *__restrict__ elts,
-                           int32_t elt_begin, int32_t n_elts, int32_t n_cat, int32_t su,
-                           uint32_t *__restrict__ evoff, uint32_t *__restrict__ liveoff) {
-    for (int32_t e = blockIdx.x * blockDim.x + threadIdx.x; e <= n_cat; e += gridDim.x * blockDim.x) {
-        uint32_t c = 0, live = 0;
-        if (e < n_cat)
-            for (int j = 0; j < n_elts; ++j) {
+// The rows of each catalogue event of a layer, an event a thread: their number (evoff)
+// and that of the rows that can pay (liveoff), both also summed per tile of kEvTile
+// events (parts, a row of tiles for each); for each row its ELT and its rank among the
+// event's rows that can, or cannot, pay; and the event's occurrence loss when
+// secondary uncertainty is off.
+__global__ __launch_bounds__(kEvTile) void k_ev_count(
+    const int32_t *__restrict__ dat, const RawRow *__restrict__ raw, const EltDev *__restrict__ elts,
+    const LayerDev *__restrict__ layer, int32_t n_cat, int32_t su, int32_t tiles,
+    uint32_t *__restrict__ evoff, uint32_t *__restrict__ liveoff, uint32_t *__restrict__ parts,
+    uint32_t *__restrict__ rank, float *__restrict__ otab) {
+    __shared__ uint32_t sums[2][kEvTile / 64];
+    const LayerDev L = *layer;
+    raw += L.row_base;
+    rank += L.row_base;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int32_t e = tile * kEvTile + (int32_t)threadIdx.x;
+        uint32_t dead = 0, live = 0;
+        float X = 0.0f;
+        if (e < n_cat) {
+#pragma unroll 4
+            for (int j = 0; j < L.n_elts; ++j) {
                 const int32_t r = dat[(int64_t)j * n_cat + e];
                 if (r < 0) continue;
-                ++c;
-                live += row_cannot_pay(raw[elt_row_off[elt_begin] + r], elts[elt_begin + j], su)
-                            ? 0u : 1u;
+                const RawRow rr = raw[r];
+                const EltDev ed = elts[L.elt_begin + j];
+                uint32_t &n = row_cannot_pay(rr, ed, su) ? dead : live;
+                rank[r] = (n++ << 16) | (uint32_t)j;
+                // (a row that cannot pay adds exactly 0)
+                X += ed.share * clampf_terms(rr.mean, ed.retention, ed.limit);
             }
-        evoff[e] = c;
-        liveoff[e] = live;
+            if (otab) otab[L.otab_base + e] = clampf_terms(X, L.occ_r, L.occ_l);
+        }
+        if (e <= n_cat) {
+            evoff[e] = dead + live;
+            liveoff[e] = live;
+        }
+        const uint32_t c = wave_sum(dead + live), cl = wave_sum(live);
+        if (lane == 0) {
+            sums[0][w] = c;
+            sums[1][w] = cl;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            uint32_t t = 0;
+            for (int q = 0; q < kEvTile / 64; ++q) t += sums[threadIdx.x][q];
+            parts[(int64_t)threadIdx.x * tiles + tile] = t;
+        }
+        __syncthreads();
     }
 }
 
-// In-place exclusive scan of n values with one 1024-thread block: rounds of
+// In-place exclusive scan of n values with one 1024-thread block (block b those at
+// p + b n): rounds of
 // 8 tiles of 1024 values, loaded together (coalesced) and scanned tile by
 // tile in order with a wavefront scan and the 16 wavefront totals in LDS.
 __global__ __launch_bounds__(1024) void k_scan_excl_u32(uint32_t *p, int64_t n) {
     constexpr int kTiles = 8;
     __shared__ uint32_t wsum[16];
+    p += (int64_t)blockIdx.x * n;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     uint32_t carry = 0;                          // sum of everything before the round
     for (int64_t base = 0; base < n; base += (int64_t)kTiles * 1024) {
@@ -262,65 +297,81 @@ __global__ void k_fit_rows(const RawRow *__restrict__ raw, int64_t n, int32_t su
     }
 }
 
-// Event-major rows of one layer: for every catalogue event, its rows in the
-// layer's ELT order, with the fitted Beta constants; also the per-event
-// occurrence loss table when secondary uncertainty is off.
-__global__ void k_ev_fill(const int32_t *__restrict__ dat, const RawRow *__restrict__ raw,
-                          const RowFit *__restrict__ fit,
-                          const int64_t *__restrict__ elt_row_off, const EltDev *__restrict__ elts,
-                          LayerDev *__restrict__ layer, int32_t n_cat, int32_t su,
-                          const uint32_t *__restrict__ evoff, uint32_t *__restrict__ live_out,
-                          const uint32_t *__restrict__ liveoff, RowQ *__restrict__ rowq,
-                          RowF *__restrict__ rowf,
-                          float *__restrict__ row_mean, float *__restrict__ row_cfrac,
-                          uint32_t *__restrict__ row_meta, double *__restrict__ row_lnb,
-                          float *__restrict__ otab) {
+// The counts of k_ev_count become offsets: each tile's scan on top of the tiles before
+// it; and the (first record, paying rows) pair of each event.
+__global__ __launch_bounds__(kEvTile) void k_ev_offsets(uint32_t *__restrict__ evoff,
+                                                        uint32_t *__restrict__ liveoff, int32_t n_cat,
+                                                        int32_t tiles, const uint32_t *__restrict__ parts,
+                                                        uint2 *__restrict__ pairs) {
+    __shared__ uint32_t sums[2][kEvTile / 64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int32_t e = tile * kEvTile + (int32_t)threadIdx.x;
+        const uint32_t c = e <= n_cat ? evoff[e] : 0u, live = e <= n_cat ? liveoff[e] : 0u;
+        int tc, tl;
+        uint32_t oc = (uint32_t)wave_excl_scan((int)c, &tc) + parts[tile];
+        uint32_t ol = (uint32_t)wave_excl_scan((int)live, &tl) + parts[tiles + tile];
+        if (lane == 0) {
+            sums[0][w] = (uint32_t)tc;
+            sums[1][w] = (uint32_t)tl;
+        }
+        __syncthreads();
+        for (int q = 0; q < w; ++q) {
+            oc += sums[0][q];
+            ol += sums[1][q];
+        }
+        if (e <= n_cat) {
+            evoff[e] = oc;
+            liveoff[e] = ol;
+        }
+        if (e < n_cat) pairs[e] = make_uint2(ol, live);
+        __syncthreads();
+    }
+}
+
+// Event-major rows of one layer, a raw row a thread: for every catalogue event its
+// rows that can pay and then those that cannot, each in the layer's ELT order, with the
+// fitted Beta constants; the rows that can pay also as compact records.  With a thread
+// per event (and its rows in a loop) the scattered row took its turn behind the 15
+// others': 12,000 rows x 16 ELTs over 100,000 events 40 us, now 14.5; with the offsets
+// from two launches of one block each (49 us each) a layer's load took 245 us, now 68.
+__global__ void k_row_place(const RawRow *__restrict__ raw, const RowFit *__restrict__ fit,
+                            const uint32_t *__restrict__ rank, const EltDev *__restrict__ elts,
+                            LayerDev *__restrict__ layer, int32_t su,
+                            const uint32_t *__restrict__ evoff, const uint2 *__restrict__ pairs,
+                            RowQ *__restrict__ rowq, RowF *__restrict__ rowf,
+                            float *__restrict__ row_mean, float *__restrict__ row_cfrac,
+                            uint32_t *__restrict__ row_meta, double *__restrict__ row_lnb) {
     const LayerDev L = *layer;
     uint32_t fl_or = 0;
-    for (int32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n_cat; e += gridDim.x * blockDim.x) {
-        int64_t pos = L.row_base + evoff[e];
-        int64_t fpos = L.row_base + liveoff[e];       // compact record of the next paying row
-        uint32_t live = 0;
-        float X = 0.0f;
-        // rows that can pay first, then the rows whose ELT terms give 0 for
-        // every draw (row_cannot_pay)
-        for (int pass = 0; pass < 2; ++pass)
-            for (int j = 0; j < L.n_elts; ++j) {
-                const int32_t r = dat[(int64_t)j * n_cat + e];
-                if (r < 0) continue;
-                const int64_t ri = elt_row_off[L.elt_begin] + r;
-                const RawRow rr = raw[ri];
-                const EltDev ed = elts[L.elt_begin + j];
-                const bool dead = row_cannot_pay(rr, ed, su);
-                if (dead != (pass == 1)) continue;
-                const RowFit rf = fit[ri];
-                const RowQ q = rf.q;
-                const uint32_t f = rf.flags;
-                const float cf = rf.cfrac;
-                const double lb = rf.lnb;
-                row_lnb[pos] = lb;
-                rowq[pos] = q;
-                row_mean[pos] = rr.mean;
-                row_cfrac[pos] = cf;
-                row_meta[pos] = f | (uint32_t)j;
-                fl_or |= f & ROW_FLAGS;
-                if (!dead) {
-                    RowF F;
-                    F.scale = q.scale;
-                    F.meta = f | (uint32_t)j;
-                    F.rs = (uint32_t)(pos - L.row_base) << 5;   // shape set by k_shape_assign
-                    F.cfrac = cf;
-                    rowf[fpos++] = F;
-                }
-                ++pos;
-                live += dead ? 0u : 1u;
-                X += ed.share * clampf_terms(rr.mean, ed.retention, ed.limit);
-            }
-        live_out[2 * e] = liveoff[e];
-        live_out[2 * e + 1] = live;
-        if (otab) otab[L.otab_base + e] = clampf_terms(X, L.occ_r, L.occ_l);
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < L.n_rows; i += gridDim.x * blockDim.x) {
+        const uint32_t at = rank[L.row_base + i];
+        if (at == ~0u) continue;               // a duplicate, already reported
+        const RawRow rr = raw[L.row_base + i];
+        const RowFit rf = fit[L.row_base + i];
+        const uint32_t j = at & 0xffffu, k = at >> 16;
+        const bool dead = row_cannot_pay(rr, elts[L.elt_begin + (int32_t)j], su);
+        const uint2 own = pairs[rr.event];
+        const int64_t pos = (int64_t)evoff[rr.event] + (dead ? own.y + k : k);
+        const int64_t row = L.row_base + pos;
+        row_lnb[row] = rf.lnb;
+        rowq[row] = rf.q;
+        row_mean[row] = rr.mean;
+        row_cfrac[row] = rf.cfrac;
+        row_meta[row] = rf.flags | j;
+        fl_or |= rf.flags & ROW_FLAGS;
+        if (!dead) {
+            RowF F;
+            F.scale = rf.q.scale;
+            F.meta = rf.flags | j;
+            F.rs = (uint32_t)pos << 5;         // shape set by k_shape_assign
+            F.cfrac = rf.cfrac;
+            rowf[L.row_base + own.x + k] = F;
+        }
     }
-    if (fl_or) atomicOr(&layer->flags, fl_or);
+    // one atomic per wavefront and flag at most
+    for (uint32_t f = ROW_DET; f <= ROW_CONLY; f <<= 1)
+        if (__any(fl_or & f) && (threadIdx.x & 63) == 0) atomicOr(&layer->flags, f);
 }
 
 // ---------------------------------------------------------------------------
@@ -462,25 +513,28 @@ hipError_t launch_fit_rows(const RawRow *raw, int64_t n, int32_t su, RowFit *fit
 hipError_t launch_build_layer(const RawRow *raw, const RowFit *fit, const int64_t *elt_row_off,
                               const EltDev *elts,
                               LayerDev *d_layer, const LayerDev &h_layer, int32_t n_cat, int32_t su,
-                              int32_t *dat, uint32_t *evoff, uint32_t *liveoff, RowQ *rowq,
-                              RowF *rowf, float *row_mean,
+                              int32_t *dat, uint32_t *evoff, uint32_t *liveoff, uint32_t *rank,
+                              uint32_t *parts, RowQ *rowq, RowF *rowf, float *row_mean,
                               float *row_cfrac, uint32_t *row_meta, double *row_lnb, float *otab,
                               Status *st, hipStream_t s) {
     const int64_t nd = (int64_t)h_layer.n_elts * n_cat;
+    const int32_t tiles = ev_tiles(n_cat);
     hipError_t e = launch_fill_i32(dat, nd > 0 ? nd : 1, -1, s);
     if (e != hipSuccess) return e;
     if (h_layer.n_rows > 0)
         hipLaunchKernelGGL(k_dat_scatter, dim3(grid_for(h_layer.n_rows, 256)), dim3(256), 0, s,
-                           raw, elt_row_off, h_layer.elt_begin, h_layer.n_elts, n_cat, dat, st);
+                           raw, elt_row_off, h_layer.elt_begin, h_layer.n_elts, n_cat, dat, rank, st);
     uint32_t *eo = evoff + h_layer.evoff_base;
-    hipLaunchKernelGGL(k_ev_count, dim3(grid_for((int64_t)n_cat + 1, 256)), dim3(256), 0, s, dat,
-                       raw, elt_row_off, elts, h_layer.elt_begin, h_layer.n_elts, n_cat, su, eo,
-                       liveoff);
-    hipLaunchKernelGGL(k_scan_excl_u32, dim3(1), dim3(1024), 0, s, eo, (int64_t)n_cat + 1);
-    hipLaunchKernelGGL(k_scan_excl_u32, dim3(1), dim3(1024), 0, s, liveoff, (int64_t)n_cat + 1);
-    hipLaunchKernelGGL(k_ev_fill, dim3(grid_for(n_cat, 256)), dim3(256), 0, s, dat, raw, fit,
-                       elt_row_off, elts, d_layer, n_cat, su, eo, evoff + h_layer.live_base,
-                       liveoff, rowq, rowf, row_mean, row_cfrac, row_meta, row_lnb, otab);
+    uint2 *pairs = reinterpret_cast<uint2 *>(evoff + h_layer.live_base);
+    const dim3 g((unsigned)(tiles < 65536 ? tiles : 65536)), b(kEvTile);
+    hipLaunchKernelGGL(k_ev_count, g, b, 0, s, dat, raw, elts, d_layer, n_cat, su, tiles, eo, liveoff,
+                       parts, rank, otab);
+    hipLaunchKernelGGL(k_scan_excl_u32, dim3(2), dim3(1024), 0, s, parts, (int64_t)tiles);
+    hipLaunchKernelGGL(k_ev_offsets, g, b, 0, s, eo, liveoff, n_cat, tiles, parts, pairs);
+    if (h_layer.n_rows > 0)
+        hipLaunchKernelGGL(k_row_place, dim3(grid_for(h_layer.n_rows, 256)), dim3(256), 0, s, raw, fit,
+                           rank, elts, d_layer, su, eo, pairs, rowq, rowf, row_mean, row_cfrac,
+                           row_meta, row_lnb);
     return hipGetLastError();
 }
 
@@ -526,12 +580,6 @@ hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits,
     return hipGetLastError();
 }
 
-hipError_t launch_scan_excl_u32(uint32_t *p, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scan_excl_u32, dim3(1), dim3(1024), 0, s, p, n);
-    return hipGetLastError();
-}
-
 hipError_t launch_debug_philox(int64_t n, const uint32_t *ctr, uint64_t key, uint32_t *out,
                                hipStream_t s) {
     if (n <= 0) return hipSuccess;
@@ -554,11 +602,11 @@ hipError_t launch_debug_quantile(int64_t n, const float *a, const float *b, cons
 // ---------------------------------------------------------------------------
 // The distinct Beta shapes of one layer's paying rows on the FP32 quantile
 // path into kShapeSlots slots, by a rule that depends on the rows alone (so
-// every load of a portfolio gives every row the same path): among the
-// layer's first kShapeScan paying rows, each thread lists the first distinct
-// shapes of its contiguous chunk in row order and thread 0 merges the lists
-// in chunk order until the slots are full (one block per layer; keys
-// [kShapeSlots] receives the slots, 0 = unused).  k_shape_assign then gives
+// every load of a portfolio gives every row the same path): the first distinct
+// ones, in row order, among the layer's first kShapeScan paying rows, found one
+// after the other as the first row whose shape has no slot yet (one block per
+// layer, its keys in registers, 6 us; lists per thread merged by one thread
+// took 72; keys [kShapeSlots] receives the slots, 0 = unused).  k_shape_assign then gives
 // every paying row 1 + its slot, or 0, in its compact record and in the
 // per-row array.
 constexpr uint32_t kShapeScan = 4096;
@@ -570,40 +618,49 @@ __device__ __forceinline__ unsigned long long shape_key(const RowQ &q) {
     return ((unsigned long long)__float_as_uint(q.a) << 32) | __float_as_uint(q.b);
 }
 
-__global__ __launch_bounds__(256) void k_shape_collect(const RowF *__restrict__ rowf,
-                                                       const RowQ *__restrict__ rowq,
-                                                       int64_t row_base,
-                                                       const uint32_t *__restrict__ liveoff,
-                                                       int32_t n_cat,
-                                                       unsigned long long *__restrict__ keys) {
-    __shared__ unsigned long long loc[256][kShapeSlots];
-    __shared__ int locn[256];
+__global__ __launch_bounds__(1024) void k_shape_collect(const RowF *__restrict__ rowf,
+                                                        const RowQ *__restrict__ rowq,
+                                                        int64_t row_base,
+                                                        const uint32_t *__restrict__ liveoff,
+                                                        int32_t n_cat,
+                                                        unsigned long long *__restrict__ keys) {
+    constexpr int kPer = kShapeScan / 1024;
+    __shared__ uint32_t first[16];
     __shared__ unsigned long long slot[kShapeSlots];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     const uint32_t n = min(liveoff[n_cat], kShapeScan);
-    const uint32_t per = (n + 255u) / 256u;
-    const uint32_t lo = (uint32_t)tid * per, hi = min(n, lo + per);
-    int m = 0;
-    for (uint32_t i = lo; i < hi && m < kShapeSlots; ++i) {
-        const RowF F = rowf[row_base + i];
-        if (!shape_eligible(F)) continue;
-        const unsigned long long key = shape_key(rowq[row_base + rowf_row(F)]);
-        bool seen = false;
-        for (int q = 0; q < m; ++q) seen = seen || loc[tid][q] == key;
-        if (!seen) loc[tid][m++] = key;
+    unsigned long long key[kPer];          // of row q * 1024 + tid, 0: none, or in a slot
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const uint32_t i = (uint32_t)(q * 1024 + tid);
+        key[q] = 0ull;
+        if (i < n) {
+            const RowF F = rowf[row_base + i];
+            if (shape_eligible(F)) key[q] = shape_key(rowq[row_base + rowf_row(F)]);
+        }
     }
-    locn[tid] = m;
-    __syncthreads();
-    if (tid == 0) {
-        int ns = 0;
-        for (int t = 0; t < 256 && ns < kShapeSlots; ++t)
-            for (int q = 0; q < locn[t] && ns < kShapeSlots; ++q) {
-                const unsigned long long key = loc[t][q];
-                bool seen = false;
-                for (int k = 0; k < ns; ++k) seen = seen || slot[k] == key;
-                if (!seen) slot[ns++] = key;
-            }
-        for (int k = ns; k < kShapeSlots; ++k) slot[k] = 0ull;
+    if (tid < kShapeSlots) slot[tid] = 0ull;
+    for (int k = 0; k < kShapeSlots; ++k) {
+        uint32_t f = ~0u;
+#pragma unroll
+        for (int q = kPer - 1; q >= 0; --q) {
+            const uint64_t m = __ballot(key[q] != 0ull);
+            if (m) f = (uint32_t)(q * 1024 + w * 64 + __builtin_ctzll(m));
+        }
+        if (lane == 0) first[w] = f;
+        __syncthreads();
+        f = first[0];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) f = min(f, first[q]);
+        if (f == ~0u) break;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+            if (f == (uint32_t)(q * 1024 + tid)) slot[k] = key[q];
+        __syncthreads();
+        const unsigned long long mine = slot[k];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+            if (key[q] == mine) key[q] = 0ull;
     }
     __syncthreads();
     if (tid < kShapeSlots) keys[tid] = slot[tid];
@@ -675,7 +732,7 @@ __global__ __launch_bounds__(kSlotSegs *kSegCoefs) void k_shape_tables(
 hipError_t launch_shape_collect(RowF *rowf, const RowQ *rowq, int64_t row_base, int64_t n_rows,
                                 const uint32_t *liveoff, int32_t n_cat, uint32_t *row_shape,
                                 unsigned long long *keys, LayerDev *d_layer, hipStream_t s) {
-    hipLaunchKernelGGL(k_shape_collect, dim3(1), dim3(256), 0, s, rowf, rowq, row_base, liveoff,
+    hipLaunchKernelGGL(k_shape_collect, dim3(1), dim3(1024), 0, s, rowf, rowq, row_base, liveoff,
                        n_cat, keys);
     // a grid over the layer's rows (the paying ones are a prefix of them)
     hipLaunchKernelGGL(k_shape_assign, dim3(grid_for(n_rows > 0 ? n_rows : 1, 256, 1024)),
