@@ -476,6 +476,16 @@ def _on(stream):
 
 
 # ---- convenience layer -------------------------------------------------------
+def _address(a):
+    """The address of a contiguous array's data.  A writable one gives it through its
+    buffer in a quarter of the time of ``a.ctypes`` (a portfolio of 64 tables asks 320
+    times)."""
+    try:
+        return C.addressof(C.c_char.from_buffer(a))
+    except (TypeError, ValueError):          # read-only, or empty
+        return a.ctypes.data
+
+
 class _Desc:
     """Holds a portfolio description and the host arrays it points into."""
 
@@ -496,8 +506,8 @@ class _Desc:
                 d = elts[j]
                 d.elt_id = int(e.elt_id) & 0xFFFFFFFF
                 d.n_rows = int(ev.shape[0])
-                d.event_ids, d.mean, d.sigma_i = ev.ctypes.data, mu.ctypes.data, si.ctypes.data
-                d.sigma_c, d.max_loss = sc.ctypes.data, mx.ctypes.data
+                d.event_ids, d.mean, d.sigma_i = _address(ev), _address(mu), _address(si)
+                d.sigma_c, d.max_loss = _address(sc), _address(mx)
                 d.retention, d.limit, d.share = float(e.retention), float(e.limit), float(e.share)
             L = layers[li]
             L.n_elts = len(layer.elts)
