@@ -104,24 +104,39 @@ void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_op
     p->dev_band = band_deviate(p->tail_band);
 }
 
-// Whether a run of so many trials takes the lean pass in its event-table form:
-// portfolios that it can hold (no rows for the full pass, no mixed rows, whose
-// extra lookups its four wavefronts per SIMD hide worse: 0.62 against 0.56 ms for
-// 40,003 trials), where its blocks' wavefronts have several trials each and a
-// trial fills segments.  Measured against the one-wavefront form (table / other):
-//  * 1 layer, 1000 occurrences a trial: 32,768 trials 326 / 311 us, 65,536 616 /
-//    610 us, 131,072 1182 / 1333 us, 1M 8.5 / 9.8 ms;
-//  * 4 layers (the other form walks all layers' tables at once, 2 MB each, out of
-//    a 4 MB L2): 4,096 trials 208 / 218 us, 16,384 645 / 827 us, 32,768 1226 /
-//    1901 us; with 300 occurrences 16,384 276 / 262 us, 32,768 495 / 584 us;
-//  * 100 occurrences a trial: 2 times slower at any size.
+// Whether a run of so many trials takes the lean pass in its event-table form (with the
+// table of small catalogues in LDS, or the filter of larger ones), for portfolios that it
+// can hold: no rows for the full pass, no mixed rows, whose extra lookups its four
+// wavefronts per SIMD hide worse (0.62 against 0.56 ms for 40,003 trials).  Per layer it
+// costs a launch and the staging, and its trials take whole segments of kSeg occurrences;
+// it saves the scattered pair lookups, which cost the more the more of them miss the 4 MB
+// L2 of an XCD.  Measured, one-wavefront form / this one (lam: occurrences a trial; hits:
+// rows per event):
+//  * the layers' pairs and an eighth of their records, which are read by hits alone, beyond
+//    the L2: 1 layer of 1M events, 0.3 hits: lam 300 x 4,096 trials 25 / 22 us, 1000 x 65,536
+//    763 / 326; 4 layers of 250,000 events: 300 x 16,384 153 / 163 (0.07 hits) and 407 / 288
+//    (2.9), 1000 x 4,096 103 / 113 and 241 / 234, 1000 x 16,384 516 / 316 and 1339 / 740; 3 of
+//    100,000 events, 3.2 hits: 300 x 32,768 377 / 378, 1000 x 16,384 559 / 500.  The line is
+//    where bytes times occurrences pay for the layers' launches.
+//  * within it, the ids beyond the 256 MB last-level cache, so that the form's ids a segment
+//    ahead count: 1 layer of 250,000 events lam 520 x 200,000 638 / 547; of 100,000 events,
+//    3.2 hits, 640 x 262,144 1708 / 1668, 520 x 262,144 1414 / 1437, 1000 x 1M 9.8 / 8.5 ms.
+//  * within both, segments well filled: 2 layers of 100,000 events lam 1000 x 16,384 355 / 340
+//    (3.2 hits) and 177 / 171 (0.2), 520 x 65,536 733 / 742 and 341 / 407; 1 of 250,000 events
+//    768 x 16,384 88 / 85; but 1 of 100,000 with 3.2 hits, 900 x 65,536 512 / 555.
+//  * 100 occurrences a trial: up to 2 times slower.
 bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
                    int64_t trials) {
     if (!pf->d_evtab || (pf->all_flags & (LAYER_DENSE | LAYER_SLOW | ROW_CORR))) return false;
+    if (trials < (int64_t)ctx->n_cu * kTabWaves) return false;
     const int64_t mean_len = yet->n_occ / (yet->n_trials > 0 ? yet->n_trials : 1);
-    const int64_t waves = (int64_t)ctx->n_cu * kTabWaves;
-    if (mean_len >= kSeg) return trials >= waves && trials * pf->n_layers >= 16 * waves;
-    return pf->n_layers > 1 && mean_len >= kSeg / 2 && trials >= 6 * waves;
+    const double occ = (double)trials * (double)mean_len, mb = 1024.0 * 1024.0;
+    const double bytes = 8.0 * pf->n_layers * (double)pf->n_catalogue + 2.0 * (double)pf->n_rows;
+    if (bytes > 4.0 * mb) return mean_len >= kSeg / 2 && occ * bytes >= 16e6 * mb * pf->n_layers;
+    if (4.0 * occ > 256.0 * mb)
+        return mean_len >= (ev_filter(pf->n_catalogue) ? kSeg : kSeg * 5 / 4);
+    return mean_len >= kSeg * 3 / 2 && trials >= 16384 &&
+           (pf->n_layers > 1 || pf->n_rows <= pf->n_catalogue);
 }
 
 // The launch of one secondary-uncertainty portfolio over o's trials, without its
@@ -185,12 +200,6 @@ ara_status fail(ara_context *ctx, ara_status code, const char *fmt, ...) {
     } while (0)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-// Words of a layer's event table; 0 for catalogues beyond its LDS.
-size_t evtab_words(int32_t n_cat) {
-    const int32_t groups = (n_cat - 1) / kTabGroup + 1;
-    return groups <= kTabGroups ? 3 * (size_t)groups : 0;
-}
 
 // Byte layout of a portfolio workspace.
 struct Layout {
@@ -769,7 +778,7 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
                                            n_catalogue, p->d_row_shape,
                                            p->d_shape_keys + (size_t)l * kShapeSlots,
                                            p->d_layers + l, s));
-        if (tabw)
+        if (p->d_evtab)
             ARA_HIP_P(launch_event_table(p->d_evoff + hl[l].live_base, n_catalogue,
                                          p->d_evtab + (size_t)l * tabw, p->d_layers + l, s));
         if (!p->su_enabled)

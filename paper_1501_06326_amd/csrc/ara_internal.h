@@ -158,6 +158,18 @@ constexpr int kMarkRow = 22;
 constexpr int kTabGroup = 16;
 constexpr int kTabGroups = 8032;
 constexpr int kTabWaves = 16;
+constexpr int32_t kTabWords = 3 * kTabGroups;
+// Larger catalogues keep a filter there instead: a bit per 2^filter_shift events.
+inline bool ev_filter(int32_t n_cat) { return (n_cat - 1) / kTabGroup >= kTabGroups; }
+inline int filter_shift(int32_t n_cat) {
+    int s = 0;
+    while ((((int64_t)n_cat - 1) >> s) >= (int64_t)kTabWords * 32) ++s;
+    return s;
+}
+inline size_t evtab_words(int32_t n_cat) {
+    if (ev_filter(n_cat)) return (size_t)((((int64_t)n_cat - 1) >> filter_shift(n_cat)) / 32 + 1);
+    return 3 * (size_t)((n_cat - 1) / kTabGroup + 1);
+}
 
 }  // namespace ara
 
@@ -195,7 +207,8 @@ struct ara_portfolio {
     uint32_t *d_row_shape;     // per row: 1 + its shape slot, or 0
     unsigned long long *d_shape_keys;   // [layer][kShapeSlots]: (alpha, beta) bits, 0 = unused
     float *d_shape_tab;        // [layer][kShapeSlots][kShapeStride], then [kNormFloats]
-    uint32_t *d_evtab;         // per layer: nibbles [2 groups], first records [groups]; or null
+    uint32_t *d_evtab;         // per layer: nibbles [2 groups], first records [groups], or the
+                               // filter's bits
     float *d_otab;
     uint32_t *d_sp_bits;       // per layer [nw]: bitmap of the non-zero otab entries
     uint32_t *d_sp_rank;       // per layer [nw + 1]: set bits before each word

@@ -561,9 +561,34 @@ __global__ void k_ev_table(const uint2 *__restrict__ pairs, int32_t n_cat, int32
     if (top > (uint32_t)(kLp / kWave)) atomicMin(&layer->chunk, (int32_t)((uint32_t)kLp / top));
 }
 
+// The event filter of one layer, a thread per bit.
+__global__ void k_ev_filter(const uint2 *__restrict__ pairs, int32_t n_cat, int32_t shift, int32_t words,
+                            uint32_t *__restrict__ tab, LayerDev *__restrict__ layer) {
+    uint32_t top = 0;
+    const int64_t bits = (int64_t)words * 32;
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < ((bits + 63) & ~(int64_t)63);
+         b += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t most = 0;
+        for (int64_t e = b << shift; e < min((b + 1) << shift, (int64_t)n_cat); ++e)
+            most = max(most, pairs[e].y);
+        const uint64_t m = __ballot(most != 0u);
+        if ((b & 31) == 0 && b < bits) tab[b >> 5] = (uint32_t)(b & 32 ? m >> 32 : m);
+        top = max(top, most);
+    }
+    if (top > 15u || layer->n_rows >= (1 << kMarkRow)) atomicOr(&layer->flags, LAYER_DENSE);
+    if (top > (uint32_t)(kLp / kWave)) atomicMin(&layer->chunk, (int32_t)((uint32_t)kLp / top));
+}
+
 hipError_t launch_event_table(const uint32_t *pairs, int32_t n_cat, uint32_t *tab, LayerDev *d_layer,
                               hipStream_t s) {
-    const int32_t groups = (n_cat + kTabGroup - 1) / kTabGroup;
+    if (ev_filter(n_cat)) {
+        const int32_t words = (int32_t)evtab_words(n_cat);
+        hipLaunchKernelGGL(k_ev_filter, dim3(grid_for((int64_t)words * 32, 256, 4096)), dim3(256), 0, s,
+                           reinterpret_cast<const uint2 *>(pairs), n_cat, filter_shift(n_cat), words,
+                           tab, d_layer);
+        return hipGetLastError();
+    }
+    const int32_t groups = (n_cat - 1) / kTabGroup + 1;
     hipLaunchKernelGGL(k_ev_table, dim3(grid_for(groups, 256)), dim3(256), 0, s,
                        reinterpret_cast<const uint2 *>(pairs), n_cat, groups, tab, d_layer);
     return hipGetLastError();

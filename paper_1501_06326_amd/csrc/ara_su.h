@@ -178,6 +178,20 @@ __device__ __forceinline__ uint2 tab_pair(const EvTab &T, int32_t E) {
     return make_uint2(r, (uint32_t)(W >> sh) & 15u);
 }
 
+// A layer's event filter, of catalogues too large for the table: a bit per 2^shift
+// events says whether any has rows; only those look up their pair in memory.
+struct EvFilter {
+    const uint32_t *bits;
+    const uint2 *pairs;
+    int shift;
+};
+__device__ __forceinline__ uint2 tab_pair(const EvFilter &T, int32_t E) {
+    const uint32_t b = (uint32_t)E >> T.shift;
+    uint2 r = make_uint2(0u, 0u);
+    if ((T.bits[b >> 5] >> (b & 31u)) & 1u) r = T.pairs[E];
+    return r;
+}
+
 // The lean pass' LDS of one wavefront: positions of a segment's hits, and where
 // each occurrence's begin.
 constexpr int kSumChunks = 4;
@@ -572,11 +586,11 @@ __device__ __forceinline__ void load_ids(SegIds &I, const int32_t *evs, int64_t 
 // which wait for nothing but LDS.  Ids loaded a chunk ahead inside the turns
 // were waited for by the next turn's record: loads return in order, and the wait
 // counts merge at the loop.
-template <int MODE, bool F64OUT, bool OCC>
+template <int MODE, bool F64OUT, bool OCC, typename TAB>
 __device__ __forceinline__ bool su_layer_tab(const SuArgs &A, const PhiloxKeys &keys,
                                              const LayerDev &L, int l, int64_t t, int64_t o0,
                                              int64_t n, SegIds &I, const int32_t *evs_next,
-                                             int64_t n_next, const LeanLds &S, const EvTab &T,
+                                             int64_t n_next, const LeanLds &S, const TAB &T,
                                              double *Y_out) {
     float *LP = S.LP;
     uint32_t *MK = reinterpret_cast<uint32_t *>(S.LP);

@@ -2,6 +2,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ara_su.h"
 
 namespace ara {
@@ -54,9 +56,8 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_full(SuArgs A, Ph
     }
 }
 
-// Lean pass of one layer with its event table in LDS: one block of 16
-// wavefronts per CU holds the table, and each wavefront takes a trial at a time
-// in turn.  The layers of a portfolio are launches of their own, the portfolio
+// Lean pass of one layer with its event table, or its filter, in LDS: one block of 16
+// wavefronts per CU holds it, and each wavefront takes a trial at a time in turn.  The layers of a portfolio are launches of their own, the portfolio
 // sum accumulated in their order, so one layer's records at a time (2 MB of 16
 // ELTs x 20,000 rows) have the L2s.  A trial that a layer abandons is flagged and
 // the full pass runs all its layers again.
@@ -67,22 +68,28 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_full(SuArgs A, Ph
 // and the vector units are the bound, busy 82 % of the time with four wavefronts
 // per SIMD: the table leaves no LDS for more, so the draws are pipelined
 // (su_layer_tab).  1M trials x 16 ELTs 9.83 -> 8.50 ms; 4 portfolios of 5 layers x
-// 25,000 trials 6.87 -> 3.87 ms.
-template <int MODE, bool F64OUT, bool OCC>
+// 25,000 trials 6.87 -> 3.87 ms.  With the filter, events without rows gather
+// nothing: 100,000 trials x 1,000 over 250,007 events of 0.6 rows 693 -> 496 us, over 1M
+// events of 0.3 rows, whose pairs are twice an L2, 1150 -> 481 us.
+template <int MODE, bool F64OUT, bool OCC, typename TAB>
 __global__ __launch_bounds__(64 * kTabWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ara_su_tab(
     SuArgs A, PhiloxKeys keys, LayerDev L, int32_t l, const uint32_t *__restrict__ tab,
-    int32_t groups) {
+    int32_t words, int32_t shape) {
     __shared__ __align__(16) uint32_t T[3 * kTabGroups];
     __shared__ __align__(16) float LP[kTabWaves][kLp + kLpPad];
     __shared__ uint16_t ST[kTabWaves][kSeg + 8];
     __shared__ EltDev El[kEltLds];
-    for (int i = threadIdx.x; i < 3 * groups; i += blockDim.x) T[i] = tab[i];
+    for (int i = threadIdx.x; i < words; i += blockDim.x) T[i] = tab[i];
     if (L.n_elts <= kEltLds && (int)threadIdx.x < L.n_elts)
         El[threadIdx.x] = A.elts[L.elt_begin + threadIdx.x];
     __syncthreads();
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const LeanLds S = {LP[w], ST[w], El};
-    const EvTab E = {reinterpret_cast<const uint2 *>(T), T + 2 * groups};
+    TAB E;
+    if constexpr (std::is_same_v<TAB, EvTab>)
+        E = {reinterpret_cast<const uint2 *>(T), T + 2 * shape};
+    else
+        E = {T, reinterpret_cast<const uint2 *>(A.evoff + L.live_base), shape};
     // the next trial's offsets and first ids are on the way while one runs
     const int64_t step = (int64_t)gridDim.x * kTabWaves;
     const int64_t *off = A.off + A.trial_begin;
@@ -95,7 +102,7 @@ __global__ __launch_bounds__(64 * kTabWaves) __attribute__((amdgpu_waves_per_eu(
         const int64_t tn = t + step < A.trial_count ? t + step : t;
         const int64_t p0 = off[tn], p1 = off[tn + 1];
         double Y;
-        const bool gone = su_layer_tab<MODE, F64OUT, OCC>(A, keys, L, l, t, o0, o1 - o0, I,
+        const bool gone = su_layer_tab<MODE, F64OUT, OCC, TAB>(A, keys, L, l, t, o0, o1 - o0, I,
                                                           A.ev + p0, p1 - p0, S, E, &Y);
         // an abandoned trial, or one of no occurrences, has loaded no ids
         if (gone || o1 == o0) load_ids(I, A.ev + p0, 0, p1 - p0, L.chunk);
@@ -153,19 +160,22 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
     }
     if (p.evtab && !diag) {
         A.redo_mode = REDO_FLAGS;
-        const int32_t groups = (p.n_cat + kTabGroup - 1) / kTabGroup;
+        const bool filter = ev_filter(p.n_cat);
+        const int32_t words = (int32_t)evtab_words(p.n_cat);
+        const int32_t shape = filter ? filter_shift(p.n_cat) : words / 3;
         const int64_t blocks = (p.trial_count + kTabWaves - 1) / kTabWaves;
         const dim3 gt((unsigned)(blocks < p.n_cu ? blocks : p.n_cu)), bt(64 * kTabWaves);
         const unsigned gc = (unsigned)((p.trial_count + 255) / 256 < 1024 ? (p.trial_count + 255) / 256 : 1024);
         hipLaunchKernelGGL(k_clear_i32, dim3(gc), dim3(256), 0, s, p.redo, p.trial_count);
+        auto tab_pass = [&](auto kernel, int32_t l) {
+            hipLaunchKernelGGL(kernel, gt, bt, 0, s, A, keys, p.h_layers[l], l,
+                               p.evtab + (size_t)l * words, words, shape);
+        };
         for (int32_t l = 0; l < p.n_layers; ++l) {
-            const uint32_t *tab = p.evtab + (size_t)l * 3 * groups;
-            if (occ)
-                hipLaunchKernelGGL((k_ara_su_tab<MODE, F64OUT, true>), gt, bt, 0, s, A, keys,
-                                   p.h_layers[l], l, tab, groups);
-            else
-                hipLaunchKernelGGL((k_ara_su_tab<MODE, F64OUT, false>), gt, bt, 0, s, A, keys,
-                                   p.h_layers[l], l, tab, groups);
+            if (filter && occ) tab_pass(k_ara_su_tab<MODE, F64OUT, true, EvFilter>, l);
+            else if (filter) tab_pass(k_ara_su_tab<MODE, F64OUT, false, EvFilter>, l);
+            else if (occ) tab_pass(k_ara_su_tab<MODE, F64OUT, true, EvTab>, l);
+            else tab_pass(k_ara_su_tab<MODE, F64OUT, false, EvTab>, l);
         }
         full(gr);
         return hipGetLastError();

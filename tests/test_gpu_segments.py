@@ -174,3 +174,37 @@ def test_table_form_equals_slices(ara, n_cat, n_elts, rows, layers, keying, band
         assert all(torch.equal(q["ylt"], r["ylt"]) and torch.equal(q["ylt_pf"], r["ylt_pf"]) for q in o)
     ara.free_portfolio(p)
     ara.free_yet(y)
+
+
+# The same at sizes that the rule gives to the table form: the last catalogue of the
+# table and the first of the filter, the last with a bit per event, the first with a
+# bit for two, one with a bit for four, several layers, many rows an event.
+@pytest.mark.parametrize("n_cat,n_elts,rows,layers,keying,band", [
+    (128_512, 3, 30_000, 1, 0, 0.0), (128_513, 3, 30_000, 1, 0, 0.0), (771_072, 2, 30_000, 1, 0, 0.0),
+    (771_073, 2, 30_000, 1, 0, 0.0), (2_000_003, 4, 30_000, 1, 1, 0.0), (250_007, 3, 20_000, 2, 0, 1e-5),
+    (4_096, 15, 3_900, 2, 1, 0.0), (9_999, 6, 1_500, 1, 0, 1e-5)])
+def test_large_runs_equal_slices(ara, n_cat, n_elts, rows, layers, keying, band):
+    n = 16_384
+    yet, pf = table_case(n_cat, n_elts, rows, n, 800, layers, keying=keying)
+    for layer in pf.layers:                    # rows at both ends of the catalogue
+        layer.elts[0].event_ids[0], layer.elts[0].event_ids[-1] = 0, n_cat - 1
+    yet.event_ids[:4] = [0, n_cat - 1, n_cat - 1, 0]
+    yet.event_ids[-2:] = [n_cat - 1, 0]
+    print("large runs", n_cat, n_elts, rows, layers, flush=True)
+    y = ara.load_yet(yet)
+    p = ara.load_portfolio(pf, n_cat)
+    r = ara.run(y, p, tail_band=band)
+    assert float(r["ylt"].max()) > 0
+    for a, b in ((0, 4000), (7000, 11_000), (n - 4000, n)):
+        s = ara.run(y, p, trial_begin=a, trial_count=b - a, tail_band=band)
+        assert torch.equal(r["ylt"][:, a:b], s["ylt"])
+        assert torch.equal(r["ylt_pf"][a:b], s["ylt_pf"])
+    v = ara.run(y, p, occ_view=True, tail_band=band)
+    assert torch.equal(v["ylt"], r["ylt"])
+    s = ara.run(y, p, trial_count=4000, occ_view=True, tail_band=band)
+    assert torch.equal(v["occ_view"][:, :s["occ_view"].shape[1]], s["occ_view"])
+    if band == 0.0:
+        o = ara.run_batch(y, [p, p])
+        assert all(torch.equal(q["ylt"], r["ylt"]) and torch.equal(q["ylt_pf"], r["ylt_pf"]) for q in o)
+    ara.free_portfolio(p)
+    ara.free_yet(y)
