@@ -32,6 +32,12 @@ inline PhiloxKeys philox_keys(uint64_t seed) {
     return k;
 }
 
+// a ^ b ^ c in one instruction; the compiler makes two of it, 20 more for a draw (1M trials
+// x 16 ELTs, the lean pass: 8.49 -> 8.28 ms).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // The key is wave-uniform, so its schedule runs on the scalar unit.
 __device__ __forceinline__ uint4 philox10(uint4 c, const PhiloxKeys &k) {
     uint32_t k0 = k.k0, k1 = k.k1;
@@ -40,9 +46,9 @@ __device__ __forceinline__ uint4 philox10(uint4 c, const PhiloxKeys &k) {
         uint64_t p0 = (uint64_t)kPhiloxM0 * (uint64_t)c.x;
         uint64_t p1 = (uint64_t)kPhiloxM1 * (uint64_t)c.z;
         uint4 n;
-        n.x = (uint32_t)(p1 >> 32) ^ c.y ^ k0;
+        n.x = xor3((uint32_t)(p1 >> 32), c.y, k0);
         n.y = (uint32_t)p1;
-        n.z = (uint32_t)(p0 >> 32) ^ c.w ^ k1;
+        n.z = xor3((uint32_t)(p0 >> 32), c.w, k1);
         n.w = (uint32_t)p0;
         c = n;
         k0 += kPhiloxW0;
@@ -59,15 +65,15 @@ __device__ __forceinline__ uint32_t philox10_x0(uint4 c, const PhiloxKeys &k) {
         uint64_t p0 = (uint64_t)kPhiloxM0 * (uint64_t)c.x;
         uint64_t p1 = (uint64_t)kPhiloxM1 * (uint64_t)c.z;
         uint4 n;
-        n.x = (uint32_t)(p1 >> 32) ^ c.y ^ k0;
+        n.x = xor3((uint32_t)(p1 >> 32), c.y, k0);
         n.y = (uint32_t)p1;
-        n.z = (uint32_t)(p0 >> 32) ^ c.w ^ k1;
+        n.z = xor3((uint32_t)(p0 >> 32), c.w, k1);
         n.w = (uint32_t)p0;
         c = n;
         k0 += kPhiloxW0;
         k1 += kPhiloxW1;
     }
-    return __umulhi(kPhiloxM1, c.z) ^ c.y ^ k0;
+    return xor3(__umulhi(kPhiloxM1, c.z), c.y, k0);
 }
 
 // Odd multiple of 2^-24: u = ((w >> 8) | 1) * 2^-24, so 1 - u is exact too.
