@@ -212,8 +212,8 @@ ara_status ara_run(ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf
                    const ara_run_opts *opts, void *d_ylt_layers, void *d_ylt_portfolio,
                    void *stream);
 
-/* Device scratch an ara_run over trial_count trials needs (the list of
- * trials handed from the FP32 pass to the FP64-capable pass). */
+/* Device scratch an ara_run over trial_count trials needs (a word for each:
+ * which of them the lean pass hands to the full pass). */
 ara_status ara_run_scratch_size(int64_t trial_count, size_t *bytes);
 
 /* ara_run for callers that cannot allocate device memory at all (code under
@@ -224,8 +224,7 @@ ara_status ara_run_scratch_size(int64_t trial_count, size_t *bytes);
  * opts->d_scratch is ignored and the call allocates nothing; the caller still
  * passes the inputs and outputs.  A run of more than ARA_STATIC_MAX_TRIALS
  * trials fails with ARA_E_WORKSPACE_TOO_SMALL.  Every call on one GPU
- * shares that array (the counter is cleared by a kernel at the start of each
- * call): calls that overlap in time on one GPU -- on two streams, or from two
+ * shares that array (each call writes every trial's word): calls that overlap in time on one GPU -- on two streams, or from two
  * contexts of the same device -- race and must be serialised by the caller.
  * Asynchronous, as ara_run. */
 #define ARA_STATIC_MAX_TRIALS (1 << 22)

@@ -21,8 +21,8 @@
 
 using namespace ara;
 
-// Scratch of ara_run_static: the hand-over from the FP32 pass to the
-// FP64-capable pass (a counter, then one trial index per trial) for up to
+// Scratch of ara_run_static: the hand-over from the lean pass to the full
+// pass (a word per trial) for up to
 // ARA_STATIC_MAX_TRIALS trials, in a device array each GPU holds for the life
 // of the process.  Host code reaches it only through the address
 // hipGetSymbolAddress gives for the current device (static_scratch_address).
@@ -86,11 +86,9 @@ float band_deviate(float band) {
 }
 
 // The lean pass hands the trials it cannot finish to the full pass through
-// scratch: a counter at the start, the trial list 256 bytes in.  That pass
-// takes up to as many wavefronts as it keeps resident (4 per SIMD), each
-// looping over the list; surplus ones find it empty.
+// scratch: a flag per trial, 256 bytes in.  That pass takes up to as many
+// wavefronts as it keeps resident (4 per SIMD), each looping over flags.
 void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_opts &o) {
-    p->redo_count = (uint32_t *)scr;
     p->redo = (int32_t *)(scr + 256);
     const int64_t resident = (int64_t)ctx->n_cu * 4 * 4;
     p->redo_grid = (int)(o.trial_count < resident ? (o.trial_count > 0 ? o.trial_count : 1)
@@ -127,7 +125,8 @@ void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_op
 //  * 100 occurrences a trial: up to 2 times slower.
 bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
                    int64_t trials) {
-    if (!pf->d_evtab || (pf->all_flags & (LAYER_DENSE | LAYER_SLOW | ROW_CORR))) return false;
+    if (!pf->d_evtab || pf->n_layers == 0) return false;
+    if (pf->all_flags & (LAYER_DENSE | LAYER_SLOW | ROW_CORR)) return false;
     if (trials < (int64_t)ctx->n_cu * kTabWaves) return false;
     const int64_t mean_len = yet->n_occ / (yet->n_trials > 0 ? yet->n_trials : 1);
     const double occ = (double)trials * (double)mean_len, mb = 1024.0 * 1024.0;

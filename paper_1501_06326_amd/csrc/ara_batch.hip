@@ -41,8 +41,7 @@ __device__ __forceinline__ void batch_view(const BatchArgs &B, int p, SuArgs &A,
     A.hit_chk = nullptr;
     A.status = B.status;
     A.redo = nullptr;
-    A.redo_count = nullptr;
-    A.redo_mode = REDO_ALL;
+    A.redo_step = 0;
     A.f64_iters = kF64QuantileIters;
     A.shape_tab = P.shape_tab;
     A.row_shape = nullptr;

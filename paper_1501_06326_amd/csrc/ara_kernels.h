@@ -72,8 +72,7 @@ struct SuLaunch {
     int64_t *hits;
     uint64_t *hit_chk;
     Status *status;
-    int32_t *redo;            // [trial_count] scratch: trials handed to the FP64-capable pass
-    uint32_t *redo_count;     // scratch counter
+    int32_t *redo;            // [trial_count] scratch: flags of trials handed to the full pass
     int redo_grid;            // blocks of the second pass
     int full;                 // rows the lean pass cannot take: the full pass over every trial
     const LayerDev *h_layers; // host copies of the layers (the table form)

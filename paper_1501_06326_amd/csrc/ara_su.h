@@ -30,8 +30,6 @@ constexpr int kQMask = kQCap - 1;
 constexpr int kHCap = 128;
 constexpr int kHMask = kHCap - 1;
 
-enum { REDO_ALL = 0, REDO_LIST = 1, REDO_FLAGS = 2 };
-
 struct SuArgs {
     const int64_t *off;
     const int32_t *ev;
@@ -53,10 +51,9 @@ struct SuArgs {
     int64_t *hits;
     uint64_t *hit_chk;
     Status *status;
-    int32_t *redo;            // trials (relative index) handed to the full pass, or a
-                              // flag for each trial of the run
-    uint32_t *redo_count;
-    int32_t redo_mode;        // REDO_*: what the full pass runs
+    int32_t *redo;            // a flag for each trial of the run: handed to the full pass
+    uint32_t redo_step;       // flags a block of the full pass reads at a time (at most a
+                              // lane each); 0: it runs every trial
     int32_t f64_iters;        // step limit of the FP64 quantile
     const float *shape_tab;   // the portfolio's shape tables ([layer][kShapeSlots][kShapeStride],
                               // then the normal segments)

@@ -20,39 +20,27 @@ __global__ __launch_bounds__(64) ARA_SU_OCCUPANCY void k_ara_su(SuArgs A, Philox
     const SuLds S = {X, Q, El, nullptr, nullptr};
     const int64_t t = blockIdx.x;
     if (t >= A.trial_count) return;
-    if (su_trial<MODE, F64OUT, DIAG, false, OCC>(A, keys, t, S) && threadIdx.x == 0)
-        A.redo[atomicAdd(A.redo_count, 1u)] = (int32_t)t;
+    const bool gone = su_trial<MODE, F64OUT, DIAG, false, OCC>(A, keys, t, S);
+    if (threadIdx.x == 0) A.redo[t] = gone;
 }
 
 // Full pass, either over every trial (one block each, for portfolios with rows
-// that the lean pass cannot take) or over the trials the lean pass handed over,
-// as a list whose count is read on the device or as flags, so no host round
-// trip is needed between the passes.
+// that the lean pass cannot take) or over the trials the lean pass flagged, so no
+// host round trip is needed between the passes.  (Every trial writes its flag: a list
+// with a counter needs a launch that clears it, 2 us of a small run's 19.)
 template <int MODE, bool F64OUT, bool DIAG, bool OCC>
 __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_full(SuArgs A, PhiloxKeys keys) {
     __shared__ float X[kSeg], XH[kSeg];
     __shared__ uint2 Q[kQCap], QH[kHCap];
     __shared__ EltDev El[kEltLds];
     const SuLds S = {X, Q, El, XH, QH};
-    // the list holds at most one entry per trial of the run; an entry outside
-    // the run (scratch shared by runs that overlapped, against the contract)
-    // is reported instead of followed
-    uint32_t n = (uint32_t)A.trial_count;
-    if (A.redo_mode == REDO_LIST) n = min(n, *A.redo_count);
-    const uint32_t step = A.redo_mode == REDO_FLAGS ? (uint32_t)kWave : 1u;
+    const uint32_t n = (uint32_t)A.trial_count, step = A.redo_step ? A.redo_step : 1u;
     for (uint32_t r0 = blockIdx.x * step; r0 < n; r0 += gridDim.x * step) {
         uint64_t m = 1;
-        if (A.redo_mode == REDO_FLAGS)
-            m = __ballot(r0 + threadIdx.x < n && A.redo[r0 + threadIdx.x] != 0);
-        for (; m; m &= m - 1) {
-            const uint32_t r = r0 + (uint32_t)__builtin_ctzll(m);
-            const int32_t t = A.redo_mode == REDO_LIST ? A.redo[r] : (int32_t)r;
-            if (t < 0 || (int64_t)t >= A.trial_count) {
-                if (threadIdx.x == 0) report(A.status, ARA_E_INVALID_ARG, r, t, A.trial_count);
-                continue;
-            }
-            su_trial<MODE, F64OUT, DIAG, true, OCC>(A, keys, (int64_t)t, S);
-        }
+        if (A.redo_step)
+            m = __ballot(threadIdx.x < step && r0 + threadIdx.x < n && A.redo[r0 + threadIdx.x] != 0);
+        for (; m; m &= m - 1)
+            su_trial<MODE, F64OUT, DIAG, true, OCC>(A, keys, (int64_t)(r0 + (uint32_t)__builtin_ctzll(m)), S);
     }
 }
 
@@ -107,10 +95,9 @@ __global__ __launch_bounds__(64 * kTabWaves) __attribute__((amdgpu_waves_per_eu(
         // an abandoned trial, or one of no occurrences, has loaded no ids
         if (gone || o1 == o0) load_ids(I, A.ev + p0, 0, p1 - p0, L.chunk);
         o0 = p0, o1 = p1;
-        if (gone) {
-            if (lane == 0) A.redo[t] = 1;
-            continue;
-        }
+        // the first layer's launch clears the flags of the trials that it finishes
+        if (lane == 0 && (gone || l == 0)) A.redo[t] = gone;
+        if (gone) continue;
         if (lane == 0 && A.ylt_pf) {
             if (F64OUT) {
                 double *p = (double *)A.ylt_pf + t;
@@ -123,14 +110,6 @@ __global__ __launch_bounds__(64 * kTabWaves) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-__global__ void k_reset_u32(uint32_t *p) { *p = 0u; }
-
-__global__ void k_clear_i32(int32_t *p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
-
 template <int MODE, bool F64OUT>
 static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
     SuArgs A;
@@ -141,7 +120,7 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
     A.row_lnb = p.row_lnb;
     A.tail_band = p.tail_band; A.dev_band = p.dev_band; A.ylt_layers = p.ylt_layers; A.ylt_pf = p.ylt_pf;
     A.hits = p.hits; A.hit_chk = p.hit_chk; A.status = p.status;
-    A.redo = p.redo; A.redo_count = p.redo_count; A.f64_iters = p.f64_iters;
+    A.redo = p.redo; A.f64_iters = p.f64_iters;
     A.shape_tab = p.shape_tab; A.row_shape = p.row_shape;
     A.occ_view = p.occ_view; A.occ_stride = p.occ_stride;
     const PhiloxKeys keys = philox_keys(p.seed);
@@ -153,20 +132,19 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
         else if (occ) hipLaunchKernelGGL((k_ara_full<MODE, F64OUT, false, true>), grid, dim3(64), 0, s, A, keys);
         else hipLaunchKernelGGL((k_ara_full<MODE, F64OUT, false, false>), grid, dim3(64), 0, s, A, keys);
     };
+    A.redo_step = (uint32_t)((p.trial_count + p.redo_grid - 1) / p.redo_grid);
+    if (A.redo_step > (uint32_t)kWave) A.redo_step = (uint32_t)kWave;
     if (p.full) {
-        A.redo_mode = REDO_ALL;
+        A.redo_step = 0;
         full(g);
         return hipGetLastError();
     }
     if (p.evtab && !diag) {
-        A.redo_mode = REDO_FLAGS;
         const bool filter = ev_filter(p.n_cat);
         const int32_t words = (int32_t)evtab_words(p.n_cat);
         const int32_t shape = filter ? filter_shift(p.n_cat) : words / 3;
         const int64_t blocks = (p.trial_count + kTabWaves - 1) / kTabWaves;
         const dim3 gt((unsigned)(blocks < p.n_cu ? blocks : p.n_cu)), bt(64 * kTabWaves);
-        const unsigned gc = (unsigned)((p.trial_count + 255) / 256 < 1024 ? (p.trial_count + 255) / 256 : 1024);
-        hipLaunchKernelGGL(k_clear_i32, dim3(gc), dim3(256), 0, s, p.redo, p.trial_count);
         auto tab_pass = [&](auto kernel, int32_t l) {
             hipLaunchKernelGGL(kernel, gt, bt, 0, s, A, keys, p.h_layers[l], l,
                                p.evtab + (size_t)l * words, words, shape);
@@ -180,9 +158,6 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
         full(gr);
         return hipGetLastError();
     }
-    A.redo_mode = REDO_LIST;
-    // a kernel, not hipMemsetAsync, so the sequence can be captured in a graph
-    hipLaunchKernelGGL(k_reset_u32, dim3(1), dim3(1), 0, s, p.redo_count);
     if (diag) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, true>), g, dim3(64), 0, s, A, keys);
     else if (occ) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, true>), g, dim3(64), 0, s, A, keys);
     else hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false>), g, dim3(64), 0, s, A, keys);
