@@ -30,7 +30,7 @@ Two further modes print their own JSON line:
                   bandwidth, and the per-draw arithmetic alone (Philox and the
                   FP32 Beta quantile at the full-shape row shape).
   --mode variants the full-shape YET with the secondary-uncertainty laws that
-                  use the FP64-capable second pass: sigma_I = sigma_C = mean/4
+                  have more to a draw: sigma_I = sigma_C = mean/4
                   (section 3.2's two-normal mix), rows of varied Beta shapes
                   (sigma_I / mean 0.15-0.9, max / mean 1.5-10) and 30 % of rows
                   above the sigma cap (section 3.3); time per run and evaluations/s
@@ -76,9 +76,9 @@ PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 #    WRITE 1.0).
 PROFILED = {
     "sources_sha256": "5b33c6d22be38d8a2aa2655bdb6200c3fe8cce3fdbcded3ac6b52e3e3ef18298",
-    "draw_arith_ops": 207.0,        # profiles/ara_su_full_counters.md (k_probe_draws)
-    "su_main_bytes": 4.4169e9 + 1.2172e8,    # k_ara_su: fetch + write, 1M trials
-    "pu_bytes": 4.0934e9 + 9.714e6,          # k_ara_pu: fetch + write, 1M trials
+    "draw_arith_ops": 33.0,         # profiles/ara_probes_valu_stream_draws.md (k_probe_draws)
+    "su_main_bytes": 4.1681e9 + 5.922e8,     # k_ara_su_tab: fetch + write, 1M trials
+    "pu_bytes": 4.0935e9 + 9.685e6,          # k_ara_pu: fetch + write, 1M trials
 }
 
 
@@ -287,7 +287,7 @@ def main():
     arith = profiled("draw_arith_ops")
     ops = arith * draws if arith else None
     result["roofline"] = {
-        "kernel": "k_ara_su (+ k_ara_su_redo), ara_run",
+        "kernel": "k_ara_su_tab (+ k_ara_full), ara_run",
         "bound": "alu",
         "achieved": (ops / (run_ms / 1e3) / 1e12) if ops else None,
         "peak": PEAK_VALU_TOPS,
@@ -451,7 +451,7 @@ def bench_probes(args):
 
 
 def bench_variants(args):
-    """Full-shape runs under the laws that use the FP64-capable second pass."""
+    """Full-shape runs under the laws that have more to a draw (two normals, the FP64 quantile)."""
     import copy
     import torch
     from paper_1501_06326_amd import Ara, evaluations
@@ -498,7 +498,7 @@ def bench_variants(args):
         del p
         torch.cuda.empty_cache()
     print(json.dumps({"metric": "trial*event*ELT evaluations/s per secondary-uncertainty law",
-                      "n_gpus": 1, "steps": args.steps, "dtype": "f32 (FP64 second pass)",
+                      "n_gpus": 1, "steps": args.steps, "dtype": "f32 (FP64 quantile of shapes outside the FP32 domain)",
                       "data": "synthetic (seeded numpy generator; lognormal ELT means)",
                       "config": {"workload": w.name, "trials": n, "occurrences": yet.n_occ,
                                  "elts": 16, "sum_mode": "kahan32"}, **res}), flush=True)

@@ -137,7 +137,7 @@ typedef struct {
     uint64_t *d_hit_chk;        /* optional [n_layers][trial_count]: sum over hits of
                                    (k+1)*2654435761 + elt_id, modulo 2^64 */
     void *d_scratch;            /* ara_run_scratch_size(trial_count) bytes of device scratch
-                                   (the trials handed from the FP32 pass to the FP64-capable
+                                   (the trials handed from the lean pass to the full
                                    pass); required for portfolios with secondary
                                    uncertainty, unused without.  Runs that overlap in time
                                    need scratch of their own. */
@@ -239,22 +239,22 @@ ara_status ara_sync_status(ara_context *ctx, void *stream);
 
 /* ---- batched portfolios --------------------------------------------------
  * Several portfolios (Algorithm 1's outer portfolio / program loops) over one
- * YET in one persistent launch.  Work items are (tile of trial_tile trials,
- * portfolio), handed out from an atomic counter in one of two orders:
+ * YET.  Work items are (tile of trial_tile trials, portfolio), handed out from an atomic counter in one of two orders:
  * portfolio-major (each portfolio's tiles in turn: its ELT tables stay in the
  * caches, the better order when the draws dominate) or trial-major (the
  * portfolios of one tile together: the tile's event ids are read once for all
  * of them, the better order for primary-uncertainty batches, which are bound
  * by memory traffic).  Results are bit-identical to running each portfolio
- * alone with ara_run: the secondary-uncertainty portfolios share the one
- * launch, and each primary-uncertainty portfolio runs ara_run's per-event
- * table pass after it on the same stream (captured with it by
- * ara_batch_graph_create).  d_ylt_layers /
+ * alone with ara_run, all on one stream (and captured together by
+ * ara_batch_graph_create): the secondary-uncertainty portfolios that the lean
+ * pass can take share one launch and those with rows for the full pass
+ * another; those large enough for ara_run's event-table form, and the
+ * primary-uncertainty ones, run ara_run's passes after them.  d_ylt_layers /
  * d_ylt_portfolio are host arrays of n_portfolios device pointers (entries
  * may be NULL), laid out as for ara_run over opts->trial_count trials.
  * opts->d_hits / d_hit_chk must be NULL; its d_scratch is not used (the batch
  * scratch is the explicit argument, ara_batch_scratch_size bytes).
- * The launch takes one of two forms: one workgroup per work item (the
+ * A shared launch takes one of two forms: one workgroup per work item (the
  * hardware dispatcher hands items out in order as wavefronts retire), or a
  * persistent grid of waves_per_cu wavefronts per CU that take items from an
  * atomic counter.  cfg = NULL: trial_tile 1, one workgroup per item,
@@ -408,7 +408,7 @@ ara_status ara_debug_beta_quantile(ara_context *ctx, int64_t n, const float *d_a
 /* ara_debug_beta_quantile_shape: the same for n draws of one shape (a, b in
  * [1, 32]) through the path of rows whose shape has a table: the table is
  * built as a portfolio load builds it (in device memory allocated for the
- * call) and the FP32 quantile starts from it.  Synchronises the stream. */
+ * call) and the FP32 quantile is read from it.  Synchronises the stream. */
 ara_status ara_debug_beta_quantile_shape(ara_context *ctx, int64_t n, float a, float b,
                                          const double *d_z, const double *d_zc, float *d_x,
                                          int32_t *d_path, void *stream);
@@ -429,13 +429,13 @@ ara_status ara_debug_beta_quantile_shape(ara_context *ctx, int64_t n, float a, f
  * ara_probe_draws: the per-draw arithmetic of secondary uncertainty alone
  *   (section 3): n draws of one ELT row of shape (a, b), Philox4x32-10 keyed
  *   (j mod 1024, j / 1024, elt_id, 0) with key = seed, the draw on the 2^-24
- *   grid and the FP32 Beta quantile (the analysis' bulk path), started from
+ *   grid and the FP32 Beta quantile (the analysis' bulk path), read from
  *   the shape's table when use_shape_table is non-zero (the path of rows
- *   whose shape has a table) or from the closed-form guess otherwise; d_x[j]
+ *   whose shape has a table) or iterated from the closed-form guess otherwise; d_x[j]
  *   receives the quantile (-1 where the FP32 iteration did not converge).
  *   a, b must lie in [1, 32].  Synchronises the stream (the quantile's
  *   continued-fraction term counts and the table are made on the device
- *   first, the table in 1.3 KB of device memory allocated for the call). */
+ *   first, the table in 3 KB of device memory allocated for the call). */
 enum {
     ARA_PROBE_FMA_F32 = 0,     /* v_fma_f32 */
     ARA_PROBE_MUL_F32 = 1,     /* v_mul_f32 */

@@ -6,7 +6,7 @@
 //    moment fit, and (without secondary uncertainty) the per-event
 //    occurrence-loss table.
 //  * The analysis (Algorithm 1 with secondary uncertainty):
-//      - k_ara_pu: primary uncertainty only.  The loss of an occurrence is
+//      - k_ara_pu (ara_pu.hip): primary uncertainty only.  The loss of an occurrence is
 //        then a function of its event id alone, so the layer's per-event
 //        occurrence losses are tabulated once (lookup, ELT terms, cross-ELT
 //        sum and occurrence terms for every catalogue event) and a trial is a
@@ -18,6 +18,8 @@
 //        drained 64 hits at a time so every lane of a batch draws, reads the
 //        quantile of its row's shape slot and applies the ELT terms on real
 //        work (the paper's "convergence switching" idea applied to SIMD lanes).
+//      - k_ara_su_tab (ara_su.hip): the same for large runs, a layer at a time,
+//        with the layer's event table or filter in LDS.
 //      - k_ara_full (ara_su.hip): portfolios with rows of shapes without a
 //        slot, or outside the FP32 domain: the same trial code with the FP32
 //        iteration in the light batches and a second queue for the FP64
@@ -26,8 +28,8 @@
 //      - k_ara_batch* (ara_batch.hip): the same trial code over (portfolio,
 //        trial tile) work items of many portfolios at once.
 //      - the occurrence view (per-occurrence increments of the aggregate
-//        terms): the OCC instantiation of k_ara_su, or k_pu_occ_view without
-//        secondary uncertainty, both through occ_chunk's wavefront scan.
+//        terms): the OCC instantiations of k_ara_su and k_ara_su_tab, or the
+//        VIEW ones of k_ara_pu, through a wavefront's FP64 scan.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
