@@ -69,13 +69,14 @@ PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 #    full-shape row shape, run alone by k_probe_draws with the shape table --
 #    counted as SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F32 + _INT32 + _INT64 per
 #    wavefront of 64 draws (moves, selects, compares and lane operations are
-#    not the method's arithmetic and are left out).
+#    not the method's arithmetic and are left out; the three-way exclusive ors
+#    of Philox, 20 a draw, are counted by no class).
 #  * su_main_bytes / pu_bytes: HBM-side traffic of one launch at 1,000,000
 #    trials, FETCH_SIZE and WRITE_SIZE each scaled by what the counter reads
 #    for an elementwise kernel that reads and writes 1 GiB (FETCH 2.0,
 #    WRITE 1.0).
 PROFILED = {
-    "sources_sha256": "5b33c6d22be38d8a2aa2655bdb6200c3fe8cce3fdbcded3ac6b52e3e3ef18298",
+    "sources_sha256": "0d59b83257712af9605722c754b0beb4df3f48910365da99b6d831071ef57007",
     "draw_arith_ops": 33.0,         # profiles/ara_probes_valu_stream_draws.md (k_probe_draws)
     "su_main_bytes": 4.1681e9 + 5.922e8,     # k_ara_su_tab: fetch + write, 1M trials
     "pu_bytes": 4.0935e9 + 9.685e6,          # k_ara_pu: fetch + write, 1M trials

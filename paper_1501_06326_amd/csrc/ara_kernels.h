@@ -26,8 +26,8 @@ constexpr int kPuLayers = 4;                  // layers a pass takes together
 constexpr size_t kPuLdsOne = 156 * 1024;      // LDS of one block per CU
 constexpr size_t kPuLdsTwo = 78 * 1024;       // of each of two
 // Occurrences from which a layer whose table leaves a CU one block (or that needs the
-// bitmap form) takes it: each block stages up to 156 KB first.  250,000 events,
-// scattered loads against LDS: 2M occurrences 14 - 19 us against 13 - 24 us (by trial
+// bitmap form) takes it: each block stages up to 156 KB first.  Catalogues of 100,000 to
+// 1M events, scattered loads against LDS: 2M occurrences 14 - 19 us against 13 - 24 us (by trial
 // length), 4M 22 - 25 us against 14 - 21 us, 64M 295 - 342 us against 86 - 262 us.
 constexpr double kPuLargeOcc = 4e6;
 enum { PU_GLOBAL = 0, PU_DENSE, PU_SPARSE, PU_BITS };

@@ -150,14 +150,15 @@ __device__ __forceinline__ void occ_quads(float4 o, bool valid, int64_t pos, con
 // blocks are 4 wavefronts.  Event ids are streamed with 16-byte loads (after a
 // scalar head that reaches 16-byte alignment), four loads in flight per lane.
 // Bound, at 1M trials x 1,000 occurrences (4 GB of ids): one table of up to 78 KB
-// by the id stream (673 us, 5.9 TB/s).  Tables beyond that by the LDS lookups and
+// by the id stream (671 us, 5.9 TB/s).  Tables beyond that by the LDS lookups and
 // the one block per CU, which is still far ahead of a scattered load of a line
-// per occurrence (250k trials x 1,000 occurrences, 250k events: 325 us against
-// 1.59 ms); four layers of 60 KB taken together read the ids once and pay for the
-// block staging once (3 layers, 500k trials x 500: 565 us, one by one 653 - 766 us,
-// by scattered loads 1.45 ms).  VIEW: the layer's occurrence view is written from
-// the same ids and lookups (NL = 1), quads of occurrences scanned at a time: 660 us
-// for 200k x 1,000 where a pass of its own over single occurrences made it 970 us.
+// per occurrence (300,007 trials x 1,000 occurrences, 1M events: 320 us against
+// 1.60 ms).  Layers taken together read the ids once and pay for the staging
+// once: 8 layers, 100,003 trials x 1,000, FP64 sums, 490 - 680 us by the draw of
+// their tables, one by one 650 - 770 us, by scattered loads where a table passed
+// 60 KB 1.07 - 2.20 ms.  VIEW: the layer's occurrence view is written from the same
+// ids and lookups (NL = 1), quads of occurrences scanned at a time: 655 us for
+// 250,000 x 1,000 where a pass of its own over single occurrences made it 970 us.
 template <int MODE, bool F64OUT, int TAB, int NL, bool VIEW>
 __device__ __forceinline__ void pu_trials(const PuArgs<NL> &P) {
     extern __shared__ uint32_t sm[];
