@@ -667,23 +667,25 @@ __device__ __forceinline__ bool su_layer_tab(const SuArgs &A, const PhiloxKeys &
                 lim = ed.limit;
                 share = ed.share;
                 uint32_t at = (uint32_t)max((int)rowf_shape(F) - 1, 0) * (uint32_t)kShapeStride;
-                bool defer = false;
+                // (a draw in the tail band abandons the trial; no draw is in the default one)
+                auto tail = [&](uint32_t j) {
+                    if (__any(grid_tail(j) < A.tail_band && on && !det)) abandon = true;
+                };
                 if (plain) {
                     const uint32_t j =
                         u24(philox10_x0(make_uint4(k, i_abs, ed.elt_id, 0u), keys));
                     at += slot_segment(j, &d);
-                    if (check_tail) defer = grid_tail(j) < A.tail_band;
+                    if (check_tail) tail(j);
                 } else {
                     const uint32_t ev = L.keying == ARA_KEYING_PAPER && on ? (uint32_t)evs[k] : 0u;
                     uint32_t jI, jC;
                     draw_j(F.meta, L.keying, k, i_abs, ed.elt_id, L.program_id, ev, keys, &jI, &jC);
-                    const uint32_t j = max(jI, jC);      // a row without a mix draws one
-                    defer = grid_tail(max(j, 1u)) < A.tail_band;
-                    at += slot_segment(max(j, 1u), &d);
+                    const uint32_t j = max(max(jI, jC), 1u);     // a row without a mix draws one
+                    at += slot_segment(j, &d);
+                    if (check_tail) tail(j);
                 }
                 lo = *reinterpret_cast<const float4 *>(slots + at);
                 hi = *reinterpret_cast<const float4 *>(slots + at + 4);
-                if (__any(defer && on && !det)) abandon = true;
             }
             // start: its record
             n_start = cnt;
@@ -743,17 +745,22 @@ __device__ __forceinline__ bool su_layer_tab(const SuArgs &A, const PhiloxKeys &
                 q[u] = LP + s0;
                 cnt[u] = s1 - s0;
                 most = max(most, cnt[u]);
-                x[u] = 0.0f;
             }
-            for (int j = 0; __any(j < most); j += 4) {
+#pragma unroll
+            for (int u = 0; u < kSumChunks; ++u) {
+                const float v0 = q[u][0], v1 = q[u][1], v2 = q[u][2], v3 = q[u][3];
+                x[u] = 0 < cnt[u] ? v0 : 0.0f;       // (a loss is never -0)
+                x[u] += 1 < cnt[u] ? v1 : 0.0f;
+                x[u] += 2 < cnt[u] ? v2 : 0.0f;
+                x[u] += 3 < cnt[u] ? v3 : 0.0f;
+            }
+            for (int j = 4; __any(j < most); j += 2) {
 #pragma unroll
                 for (int u = 0; u < kSumChunks; ++u) {
-                    const float v0 = q[u][0], v1 = q[u][1], v2 = q[u][2], v3 = q[u][3];
+                    q[u] += j < cnt[u] ? (j == 4 ? 4 : 2) : 0;
+                    const float v0 = q[u][0], v1 = q[u][1];
                     x[u] += j < cnt[u] ? v0 : 0.0f;
                     x[u] += j + 1 < cnt[u] ? v1 : 0.0f;
-                    x[u] += j + 2 < cnt[u] ? v2 : 0.0f;
-                    x[u] += j + 3 < cnt[u] ? v3 : 0.0f;
-                    q[u] += j + 4 < cnt[u] ? 4 : 0;
                 }
             }
 #pragma unroll
