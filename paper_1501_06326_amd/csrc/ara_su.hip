@@ -53,12 +53,12 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_full(SuArgs A, Ph
 // The one-wavefront form is bound by its divergent gathers: per 64 occurrences,
 // 64 lines of (first record, rows) pairs, 123 cycles of the CU's address unit,
 // which was busy 83 % of the time.  Here they are LDS reads (address unit 40 %)
-// and the vector units are the bound, busy 82 % of the time with four wavefronts
+// and the vector units are the bound, busy 80 % of the time with four wavefronts
 // per SIMD: the table leaves no LDS for more, so the draws are pipelined
-// (su_layer_tab).  1M trials x 16 ELTs 9.83 -> 8.50 ms; 4 portfolios of 5 layers x
-// 25,000 trials 6.87 -> 3.87 ms.  With the filter, events without rows gather
-// nothing: 100,000 trials x 1,000 over 250,007 events of 0.6 rows 693 -> 496 us, over 1M
-// events of 0.3 rows, whose pairs are twice an L2, 1150 -> 481 us.
+// (su_layer_tab).  1M trials x 16 ELTs 9.83 -> 7.95 ms; 4 portfolios of 5 layers x
+// 25,000 trials 6.87 -> 3.68 ms.  With the filter, events without rows gather
+// nothing: 100,000 trials x 1,000 over 250,007 events of 0.6 rows 693 -> 463 us, over 1M
+// events of 0.3 rows, whose pairs are twice an L2, 1150 -> 463 us.
 template <int MODE, bool F64OUT, bool OCC, typename TAB>
 __global__ __launch_bounds__(64 * kTabWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ara_su_tab(
     SuArgs A, PhiloxKeys keys, LayerDev L, int32_t l, const uint32_t *__restrict__ tab,
