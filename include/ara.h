@@ -405,6 +405,14 @@ ara_status ara_debug_philox(ara_context *ctx, int64_t n, const uint32_t *d_ctr, 
 ara_status ara_debug_beta_quantile(ara_context *ctx, int64_t n, const float *d_a,
                                    const float *d_b, const double *d_z, const double *d_zc,
                                    float tail_band, float *d_x, int32_t *d_path, void *stream);
+/* ara_debug_run_pass: the pass that ara_run with these options (d_hits, d_hit_chk and
+ * d_occ_view count by being set) takes over the trials of a portfolio with secondary
+ * uncertainty: the lean pass, its event-table form, or the full pass alone. */
+#define ARA_PASS_LEAN 0
+#define ARA_PASS_TABLE 1
+#define ARA_PASS_FULL 2
+ara_status ara_debug_run_pass(ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
+                              const ara_run_opts *opts, int32_t *pass);
 /* ara_debug_beta_quantile_shape: the same for n draws of one shape (a, b in
  * [1, 32]) through the path of rows whose shape has a table: the table is
  * built as a portfolio load builds it (in device memory allocated for the

@@ -45,7 +45,7 @@ EXPORTS = ["ara_create", "ara_destroy", "ara_status_string", "ara_last_error", "
            "ara_server_release", "ara_server_destroy", "ara_server_last_error",
            "ara_ep_curve_scratch_size", "ara_ep_curve", "ara_probe_stream_read",
            "ara_probe_valu_lanes", "ara_probe_valu", "ara_probe_draws",
-           "ara_debug_beta_quantile_shape", "ara_run_static"]
+           "ara_debug_beta_quantile_shape", "ara_run_static", "ara_debug_run_pass"]
 
 PROBE_KINDS = {"fma_f32": 0, "mul_f32": 1, "xad_u32": 2, "mulhi_u32": 3, "mad_u64_u32": 4,
                "exp2_f32": 5, "fma_f64": 6}
@@ -79,6 +79,7 @@ class ara_portfolio_desc(C.Structure):
 
 
 ARA_KEYING_OCCURRENCE, ARA_KEYING_PAPER = 0, 1
+ARA_PASS_LEAN, ARA_PASS_TABLE, ARA_PASS_FULL = 0, 1, 2
 
 
 ARA_BATCH_PORTFOLIO_MAJOR, ARA_BATCH_TRIAL_MAJOR = 0, 1
@@ -179,6 +180,7 @@ def lib():
         L.ara_probe_valu.argtypes = [p, i32, i32, i32, p, C.POINTER(u64), p]
         L.ara_probe_draws.argtypes = [p, i64, u64, C.c_uint32, C.c_float, C.c_float, i32, p, p]
         L.ara_debug_beta_quantile_shape.argtypes = [p, i64, C.c_float, C.c_float, p, p, p, p, p]
+        L.ara_debug_run_pass.argtypes = [p, p, p, C.POINTER(ara_run_opts), C.POINTER(i32)]
         for name in EXPORTS:
             f = getattr(L, name)
             if f.restype is C.c_int:       # default
@@ -395,6 +397,13 @@ def ara_probe_draws(ctx, n: int, seed: int, elt_id: int, a: float, b: float,
     _check(ctx, lib().ara_probe_draws(ctx, int(n), int(seed) & 0xFFFFFFFFFFFFFFFF, int(elt_id),
                                       float(a), float(b), 1 if use_shape_table else 0, d_x,
                                       stream), "ara_probe_draws")
+
+
+def ara_debug_run_pass(ctx, yet, pf, opts: ara_run_opts) -> int:
+    n = C.c_int32()
+    _check(ctx, lib().ara_debug_run_pass(ctx, yet, pf, C.byref(opts), C.byref(n)),
+           "ara_debug_run_pass")
+    return n.value
 
 
 def ara_debug_beta_quantile_shape(ctx, n: int, a: float, b: float, d_z: int, d_zc: int, d_x: int,
@@ -780,6 +789,15 @@ class Ara:
         ara_debug_beta_quantile(self.ctx, A.numel(), _ptr(A), _ptr(B), _ptr(Z), _ptr(ZC),
                                 tail_band, _ptr(x), _ptr(path), _stream_handle(stream))
         return x.cpu().numpy(), path.cpu().numpy()
+
+    def debug_run_pass(self, y, p, trial_begin: int = 0, trial_count: Optional[int] = None,
+                       diagnostics: bool = False, occ_view: bool = False) -> int:
+        """The pass (ARA_PASS_*) that ``run`` with these arguments takes."""
+        one = C.addressof(C.c_int32())               # only whether it is set counts
+        o = ara_run_opts(trial_begin=trial_begin,
+                         trial_count=-1 if trial_count is None else trial_count,
+                         d_hits=one if diagnostics else None, d_occ_view=one if occ_view else None)
+        return ara_debug_run_pass(self.ctx, y.handle, p.handle, o)
 
     def debug_beta_quantile_shape(self, a: float, b: float, z, zc, stream=None):
         """The FP32 quantile of one shape through its shape table."""

@@ -138,6 +138,16 @@ bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfol
            (pf->n_layers > 1 || pf->n_rows <= pf->n_catalogue);
 }
 
+// The pass of a run of so many trials.  A layer of an event with more than kLp / 64 rows
+// has its segments end between multiples of 64 occurrences; the view's running sums,
+// which are scanned 64 at a time, then would not round as those of the other passes.
+SuForm su_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf, int64_t trials,
+               bool diag, bool view) {
+    if (pf->all_flags & LAYER_SLOW) return SU_FULL;
+    if (diag || (view && pf->chunk < kWave)) return SU_LEAN;
+    return su_table_form(ctx, yet, pf, trials) ? SU_TABLE : SU_LEAN;
+}
+
 // The launch of one secondary-uncertainty portfolio over o's trials, without its
 // outputs and hand-over scratch.
 SuLaunch su_launch(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
@@ -163,9 +173,9 @@ SuLaunch su_launch(const ara_context *ctx, const ara_yet *yet, const ara_portfol
     p.seed = pf->seed;
     p.tail_band = o.tail_band;
     p.status = status;
-    p.full = (pf->all_flags & LAYER_SLOW) != 0;
+    p.form = su_form(ctx, yet, pf, o.trial_count, o.d_hits || o.d_hit_chk, o.d_occ_view);
     p.h_layers = pf->h_layers;
-    p.evtab = su_table_form(ctx, yet, pf, o.trial_count) ? pf->d_evtab : nullptr;
+    p.evtab = pf->d_evtab;
     p.n_cat = pf->n_catalogue;
     p.n_cu = ctx->n_cu;
     return p;
@@ -802,7 +812,11 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
     }
 #undef ARA_HIP_P
     p->all_flags = 0;
-    for (int l = 0; l < nl; ++l) p->all_flags |= p->h_layers[l].flags;
+    p->chunk = kWave;
+    for (int l = 0; l < nl; ++l) {
+        p->all_flags |= p->h_layers[l].flags;
+        p->chunk = std::min(p->chunk, p->h_layers[l].chunk);
+    }
     ctx->pfs.insert(p);
     *out = p;
     return ARA_OK;
@@ -1083,12 +1097,13 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
             continue;
         }
         total += tc;
-        if (tc > 0 && su_table_form(ctx, yet, p, tc)) {
+        const SuForm form = su_form(ctx, yet, p, tc, false, false);
+        if (tc > 0 && form == SU_TABLE) {
             plan->tab.push_back({p, tb, tc, ylt_l ? ylt_l[i] : nullptr, ylt_p ? ylt_p[i] : nullptr,
                                  nullptr});
             continue;
         }
-        const int full = (p->all_flags & LAYER_SLOW) != 0;
+        const int full = form == SU_FULL;
         hs[full].emplace_back();
         BatchPf &b = hs[full].back();
         b.layers = p->d_layers;
@@ -1347,6 +1362,17 @@ ara_status ara_debug_philox(ara_context *ctx, int64_t n, const uint32_t *d_ctr, 
         return fail(ctx, ARA_E_INVALID_ARG, "ara_debug_philox: bad arguments");
     ARA_HIP(ctx, hipSetDevice(ctx->device));
     ARA_HIP(ctx, launch_debug_philox(n, d_ctr, key, d_out, (hipStream_t)stream));
+    return ARA_OK;
+}
+
+ara_status ara_debug_run_pass(ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
+                              const ara_run_opts *opts, int32_t *pass) {
+    if (!ctx) return ARA_E_INVALID_ARG;
+    if (!yet || !pf || !opts || !pass || !ctx->yets.count(const_cast<ara_yet *>(yet)) ||
+        !ctx->pfs.count(const_cast<ara_portfolio *>(pf)) || !pf->su_enabled)
+        return fail(ctx, ARA_E_INVALID_ARG, "ara_debug_run_pass: bad arguments");
+    const int64_t n = opts->trial_count < 0 ? yet->n_trials - opts->trial_begin : opts->trial_count;
+    *pass = su_form(ctx, yet, pf, n, opts->d_hits || opts->d_hit_chk, opts->d_occ_view);
     return ARA_OK;
 }
 

@@ -195,6 +195,7 @@ struct ara_portfolio {
     int32_t su_enabled;
     int32_t max_layer_elts;
     uint32_t all_flags;
+    int32_t chunk;             // the smallest of its layers' (see LayerDev)
     ara::LayerDev *d_layers;
     ara::EltDev *d_elts;
     uint32_t *d_evoff;

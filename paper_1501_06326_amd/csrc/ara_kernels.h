@@ -50,6 +50,9 @@ struct PuLaunch {
     Status *status;
 };
 
+// The passes of a run with secondary uncertainty (ARA_PASS_*).
+enum SuForm { SU_LEAN = ARA_PASS_LEAN, SU_TABLE = ARA_PASS_TABLE, SU_FULL = ARA_PASS_FULL };
+
 struct SuLaunch {
     const int64_t *off;
     const int32_t *ev;
@@ -74,9 +77,9 @@ struct SuLaunch {
     Status *status;
     int32_t *redo;            // [trial_count] scratch: flags of trials handed to the full pass
     int redo_grid;            // blocks of the second pass
-    int full;                 // rows the lean pass cannot take: the full pass over every trial
+    SuForm form;
     const LayerDev *h_layers; // host copies of the layers (the table form)
-    const uint32_t *evtab;    // the layers' event tables; null: the one-wavefront form
+    const uint32_t *evtab;    // the layers' event tables (the table form)
     int32_t n_cat;
     int n_cu;
     int32_t f64_iters;        // step limit of the FP64 quantile

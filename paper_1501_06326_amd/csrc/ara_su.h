@@ -578,8 +578,9 @@ __device__ __forceinline__ void load_ids(SegIds &I, const int32_t *evs, int64_t 
 //    a lane finds its occurrence as the last mark up to its position, the highest
 //    bit of a ballot up to its own, and loads its record; draw; finish), and
 //    each hit's loss net of the ELT terms is left at its position.
-//  * Each lane adds up its occurrences' hits in order, the order in which
-//    su_layer adds them.
+//  * Each lane adds up the hits of its occurrences in order, and the trial's sum takes
+//    them in the order in which su_layer does: occurrence k is lane k mod 64's, also
+//    where a segment begins at another multiple of L.chunk.
 // I holds the ids of the trial's first segment; the next segment's, and at the
 // end those of the next trial (evs_next, n_next), are loaded before the sums,
 // which wait for nothing but LDS.  Ids loaded a chunk ahead inside the turns
@@ -755,16 +756,19 @@ __device__ __forceinline__ bool su_layer_tab(const SuArgs &A, const PhiloxKeys &
         if (seg + taken < n) load_ids(I, evs, seg + taken, n, cw);
         else load_ids(I, evs_next, 0, n_next, cw);
         const int64_t pos0 = OCC ? o0 - A.off[A.trial_begin] + seg : 0;
+        // the lane of the segment's first occurrence (the view has segments of whole chunks of 64)
+        const int lane0 = OCC ? 0 : (int)(seg & 63);
         // kSumChunks occurrences a lane at a time, four hits of each in flight
         // (an occurrence's hits are added in order whatever the grouping)
-        for (int c = 0; c < taken; c += kSumChunks * kWave) {
+        for (int c = -lane0; c < taken; c += kSumChunks * kWave) {
             float x[kSumChunks];
             const float *q[kSumChunks];
             int cnt[kSumChunks], most = 0;
 #pragma unroll
             for (int u = 0; u < kSumChunks; ++u) {
-                const int i = min(c + u * kWave + lane, taken);
-                const int s0 = S.ST[i], s1 = S.ST[min(i + 1, taken)];
+                // (before the first occurrence, as past the last: no hits)
+                const uint32_t i = (uint32_t)(c + u * kWave + lane), end = (uint32_t)taken;
+                const int s0 = S.ST[min(i, end)], s1 = S.ST[min(i + 1u, end)];
                 q[u] = LP + s0;
                 cnt[u] = s1 - s0;
                 most = max(most, cnt[u]);
@@ -789,7 +793,7 @@ __device__ __forceinline__ bool su_layer_tab(const SuArgs &A, const PhiloxKeys &
 #pragma unroll
             for (int u = 0; u < kSumChunks; ++u) {
                 const int i = c + u * kWave + lane;
-                const bool valid = i < taken;
+                const bool valid = (uint32_t)i < (uint32_t)taken;
                 const float o = clampf_terms(x[u], L.occ_r, L.occ_l);
                 if (valid) acc.add(o);
                 if (OCC && A.occ_view && c + u * kWave < taken)

@@ -134,12 +134,12 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
     };
     A.redo_step = (uint32_t)((p.trial_count + p.redo_grid - 1) / p.redo_grid);
     if (A.redo_step > (uint32_t)kWave) A.redo_step = (uint32_t)kWave;
-    if (p.full) {
+    if (p.form == SU_FULL) {
         A.redo_step = 0;
         full(g);
         return hipGetLastError();
     }
-    if (p.evtab && !diag) {
+    if (p.form == SU_TABLE) {
         const bool filter = ev_filter(p.n_cat);
         const int32_t words = (int32_t)evtab_words(p.n_cat);
         const int32_t shape = filter ? filter_shift(p.n_cat) : words / 3;
