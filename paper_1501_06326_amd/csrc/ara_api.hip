@@ -379,7 +379,8 @@ hipError_t open_stage(Stage &S) {
 // written into pinned buffers by a thread each and copied as they are ready.  elt_row
 // holds the first row of each ELT and the number of rows.  768,000 rows (15 MB): 0.5 ms;
 // by one thread over two buffers 0.76 ms; as one array, filled and then copied through the
-// runtime's own staging, 1.3 ms.
+// runtime's own staging, 1.3 ms.  hipStreamPerThread names another stream in each thread,
+// so on it the caller's thread makes all the copies, from the buffers in turn.
 hipError_t upload_rows(ara_context *ctx, const ara_portfolio_desc *desc, const int64_t *elt_row,
                        int32_t n_elts, RawRow *d_raw, hipStream_t s) {
     const int64_t n_rows = elt_row[n_elts];
@@ -391,12 +392,12 @@ hipError_t upload_rows(ara_context *ctx, const ara_portfolio_desc *desc, const i
         for (int j = 0; j < desc->layers[l].n_elts; ++j) elts.push_back(&desc->layers[l].elts[j]);
     constexpr int64_t kRows = (int64_t)(kStageBytes / sizeof(RawRow));
     const int64_t chunks = (n_rows + kRows - 1) / kRows;
-    const int workers = (int)std::min<int64_t>(chunks, kStages);
+    const int workers = s == hipStreamPerThread ? 1 : (int)std::min<int64_t>(chunks, kStages);
     hipError_t errs[kStages] = {};
     auto work = [&](int t) {
         hipError_t e = hipSetDevice(ctx->device);
         for (int64_t c = t; c < chunks && e == hipSuccess; c += workers) {
-            Stage &S = ctx->stage[t];
+            Stage &S = ctx->stage[workers == 1 ? c % kStages : t];
             if ((e = open_stage(S)) != hipSuccess) break;
             RawRow *to = (RawRow *)S.data;
             const int64_t r0 = c * kRows, r1 = std::min(n_rows, r0 + kRows);
