@@ -540,8 +540,13 @@ __device__ inline double slot_point(double a, double b, double lnb, int seg, int
     return beta_quantile64(a, b, lnb, 0, 0, z, zc, kF64QuantileIters, &ok);
 }
 
-// Coefficients in powers of the local coordinate of the polynomial through the
-// values y at the points of a segment (divided differences, then expanded).
+// Coefficients in powers of the local coordinate d of the polynomial through the
+// values y at the points of a segment (divided differences, then expanded).  Half of
+// all draws fall in two segments, so what rounding c0 to FP32 shifts them by would stay
+// in the mean over any number of trials: the quadratic coefficient takes it up (the
+// mean of d^2 over the segment is 1/12).  The mean quantile of shapes across [1, 32]^2
+// is off by 1.6e-10 of it (root mean square; 9.8e-9 with each coefficient rounded by
+// itself), the largest error of a draw stays what the interpolation makes it (2.1e-7).
 __device__ inline void seg_fit(double *y, float *out) {
     for (int k = 1; k < kSegCoefs; ++k)
         for (int q = kSegCoefs - 1; q >= k; --q)
@@ -549,6 +554,7 @@ __device__ inline void seg_fit(double *y, float *out) {
     for (int k = kSegCoefs - 2; k >= 0; --k)
         for (int q = k; q < kSegCoefs - 1; ++q) y[q] -= seg_node(k) * y[q + 1];
     for (int q = 0; q < kSegCoefs; ++q) out[q] = (float)y[q];
+    out[2] = (float)(y[2] - 12.0 * ((double)out[0] - y[0]));
 }
 
 }  // namespace ara
