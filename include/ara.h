@@ -407,10 +407,12 @@ ara_status ara_debug_beta_quantile(ara_context *ctx, int64_t n, const float *d_a
                                    float tail_band, float *d_x, int32_t *d_path, void *stream);
 /* ara_debug_run_pass: the pass that ara_run with these options (d_hits, d_hit_chk and
  * d_occ_view count by being set) takes over the trials of a portfolio with secondary
- * uncertainty: the lean pass, its event-table form, or the full pass alone. */
+ * uncertainty: the lean pass, its event-table form, the full pass alone, or the lean
+ * pass with the FP32 iteration for shapes without a table. */
 #define ARA_PASS_LEAN 0
 #define ARA_PASS_TABLE 1
 #define ARA_PASS_FULL 2
+#define ARA_PASS_ITERATE 3
 ara_status ara_debug_run_pass(ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
                               const ara_run_opts *opts, int32_t *pass);
 /* ara_debug_beta_quantile_shape: the same for n draws of one shape (a, b in

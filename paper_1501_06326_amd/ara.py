@@ -79,7 +79,7 @@ class ara_portfolio_desc(C.Structure):
 
 
 ARA_KEYING_OCCURRENCE, ARA_KEYING_PAPER = 0, 1
-ARA_PASS_LEAN, ARA_PASS_TABLE, ARA_PASS_FULL = 0, 1, 2
+ARA_PASS_LEAN, ARA_PASS_TABLE, ARA_PASS_FULL, ARA_PASS_ITERATE = 0, 1, 2, 3
 
 
 ARA_BATCH_PORTFOLIO_MAJOR, ARA_BATCH_TRIAL_MAJOR = 0, 1

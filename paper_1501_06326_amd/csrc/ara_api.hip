@@ -66,6 +66,8 @@ constexpr int kMaxRp = 256;
 // 2^-24); the FP64 path serves shapes outside the FP32 domain, sigma-capped
 // rows and FP32 non-convergence.
 constexpr float kDefaultTailBand = 5.9604644775390625e-08f;
+constexpr int64_t kFullWaves = 16;           // of the full pass, resident on a CU
+constexpr int64_t kRedoBlocks = 65536;
 
 size_t run_scratch_need(int64_t trial_count) {
     return 256 + ((size_t)(trial_count > 0 ? trial_count : 1) * sizeof(int32_t) + 255) / 256 * 256;
@@ -87,12 +89,14 @@ float band_deviate(float band) {
 
 // The lean pass hands the trials it cannot finish to the full pass through
 // scratch: a flag per trial, 256 bytes in.  That pass takes up to as many
-// wavefronts as it keeps resident (4 per SIMD), each looping over flags.
-void su_scratch(const ara_context *ctx, SuLaunch *p, char *scr, const ara_run_opts &o) {
+// wavefronts as it keeps resident, each looping over flags; where trials are sure to be
+// handed over, up to kRedoBlocks that the dispatcher hands out as others end (65,536
+// trials, a tenth of them 0.89 against 1.07 ms; 10 us more where none is).
+void su_scratch(const ara_context *ctx, const ara_portfolio *pf, SuLaunch *p, char *scr,
+                const ara_run_opts &o) {
     p->redo = (int32_t *)(scr + 256);
-    const int64_t resident = (int64_t)ctx->n_cu * 4 * 4;
-    p->redo_grid = (int)(o.trial_count < resident ? (o.trial_count > 0 ? o.trial_count : 1)
-                                                  : resident);
+    const int64_t most = pf->n_f64 > 0 ? kRedoBlocks : (int64_t)ctx->n_cu * kFullWaves;
+    p->redo_grid = (int)std::max<int64_t>(1, std::min<int64_t>(o.trial_count, most));
     if (o.debug_flags & ARA_DEBUG_QUANTILE_ONE_STEP) {
         p->tail_band = 2.0f;       // every draw takes the FP64 quantile ...
         p->f64_iters = 1;          // ... which may take one step
@@ -141,9 +145,28 @@ bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfol
 // The pass of a run of so many trials.  A layer of an event with more than kLp / 64 rows
 // has its segments end between multiples of 64 occurrences; the view's running sums,
 // which are scanned 64 at a time, then would not round as those of the other passes.
+//
+// Rows without a slot: those of the FP32 quantile's domain are iterated in the lean pass
+// (SU_ITER), trials with a hit of the others are handed over, and where more than half of
+// the trials have one, or the full pass has every trial resident at once, so that the
+// two passes' latencies would add up, the full pass runs alone.  The share of trials is
+// that of a uniform catalogue.  65,536 trials x 1,000 occurrences of 16 x 20,000 rows, full
+// pass alone / this: 17 shapes 2.43 / 1.38 ms, every row its own 2.35 / 1.50, odd FP32
+// shapes among one in 0.01 % of the rows 1.67 / 0.61 and in 10 % 2.29 / 1.21; FP64 rows among
+// one shape, a share of the trials of 0.12 1.68 / 0.89, of 0.7 1.75 / 1.68, of 1 1.89 /
+// 1.98.  20,000 x 300: 0.09 138 / 81 us, 0.6 154 / 157; 10,000 x 100: 0.05 46 / 36, 0.4 53 / 52,
+// 1 69 / 81.  12,000 x 1,000, 0.1: 295 / 202 us, 6,000 180 / 142, 4,096 (all resident) 114 / 121,
+// 500 56 / 86.
 SuForm su_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf, int64_t trials,
                bool diag, bool view) {
-    if (pf->all_flags & LAYER_SLOW) return SU_FULL;
+    if (pf->all_flags & LAYER_SLOW) {
+        const double mean_len = (double)yet->n_occ / (double)std::max<int64_t>(yet->n_trials, 1);
+        const double hits = mean_len * (double)pf->n_f64 / (double)pf->n_catalogue;
+        const double share = 1.0 - std::exp(-hits);
+        const bool resident = trials <= (int64_t)ctx->n_cu * kFullWaves;
+        if (share > 0.5 || (resident && share * (double)trials > 1.0)) return SU_FULL;
+        return pf->all_flags & LAYER_ITER ? SU_ITER : SU_LEAN;
+    }
     if (diag || (view && pf->chunk < kWave)) return SU_LEAN;
     return su_table_form(ctx, yet, pf, trials) ? SU_TABLE : SU_LEAN;
 }
@@ -814,8 +837,10 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
 #undef ARA_HIP_P
     p->all_flags = 0;
     p->chunk = kWave;
+    p->n_f64 = 0;
     for (int l = 0; l < nl; ++l) {
         p->all_flags |= p->h_layers[l].flags;
+        p->n_f64 += p->h_layers[l].n_f64;
         p->chunk = std::min(p->chunk, p->h_layers[l].chunk);
     }
     ctx->pfs.insert(p);
@@ -900,7 +925,7 @@ ara_status run_impl(ara_context *ctx, const ara_yet *yet, const ara_portfolio *p
                     "ara_run: secondary uncertainty needs %zu bytes of scratch (opts->d_scratch)",
                     need);
     }
-    su_scratch(ctx, &p, scr, o);
+    su_scratch(ctx, pf, &p, scr, o);
     ARA_HIP(ctx, launch_su(p, o.sum_mode, f64out, s));
     return ARA_OK;
 }
@@ -1025,9 +1050,7 @@ struct PuItem {
     void *ylt_layers, *ylt_pf;
 };
 
-// The secondary-uncertainty portfolios of a batch run in up to two launches:
-// those that the lean pass can take (B), then those with rows for the full
-// pass (F), whose register budget would slow the others down.
+// A portfolio of a batch that takes the event-table form: launches of its own.
 struct TabItem {
     const ara_portfolio *pf;
     int64_t begin, count;
@@ -1035,8 +1058,12 @@ struct TabItem {
     int32_t *flags;
 };
 
+// The other secondary-uncertainty portfolios of a batch run in up to three launches,
+// one for each of these passes, whose register budgets would slow the others down.
+constexpr SuForm kBatchForms[3] = {SU_LEAN, SU_ITER, SU_FULL};
+
 struct BatchPlan {
-    BatchArgs B, F;
+    BatchArgs B[3];
     float tail_band;
     std::vector<TabItem> tab;      // launches of their own: the event-table form
     int grid, redo_grid, mode;
@@ -1078,8 +1105,8 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: bad batch configuration");
     if (ranges && c.order == ARA_BATCH_TRIAL_MAJOR)
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: trial-major order needs one trial range");
-    int64_t total = 0, listed = 0, items[2] = {0, 0};
-    std::vector<BatchPf> hs[2];    // lean, full
+    int64_t total = 0, listed = 0, items[3] = {0, 0, 0};
+    std::vector<BatchPf> hs[3];    // see kBatchForms
     plan->pu.clear();
     plan->tab.clear();
     for (int32_t i = 0; i < n; ++i) {
@@ -1104,9 +1131,9 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
                                  nullptr});
             continue;
         }
-        const int full = form == SU_FULL;
-        hs[full].emplace_back();
-        BatchPf &b = hs[full].back();
+        const int k = form == SU_LEAN ? 0 : form == SU_ITER ? 1 : 2;
+        hs[k].emplace_back();
+        BatchPf &b = hs[k].back();
         b.layers = p->d_layers;
         b.elts = p->d_elts;
         b.evoff = p->d_evoff;
@@ -1125,8 +1152,8 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         b.pad = 0;
         b.trial_begin = tb;
         b.trial_count = tc;
-        b.tile_base = items[full];
-        items[full] += (tc + c.trial_tile - 1) / c.trial_tile;
+        b.tile_base = items[k];
+        items[k] += (tc + c.trial_tile - 1) / c.trial_tile;
         listed += tc;
     }
     const size_t need = batch_need(n, total);
@@ -1134,28 +1161,30 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         return fail(ctx, ARA_E_WORKSPACE_TOO_SMALL, "ara_run_batch: need %zu scratch bytes", need);
     char *sc = (char *)scratch;
     std::vector<BatchPf> h(hs[0]);
-    h.insert(h.end(), hs[1].begin(), hs[1].end());
+    for (int k = 1; k < 3; ++k) h.insert(h.end(), hs[k].begin(), hs[k].end());
     if (!h.empty())
         ARA_HIP(ctx, hipMemcpyAsync(sc + batch_pf_off(), h.data(), sizeof(BatchPf) * h.size(),
                                     hipMemcpyHostToDevice, s));
     const bool trial_major = c.order == ARA_BATCH_TRIAL_MAJOR;
-    for (int full = 0; full < 2; ++full) {
-        BatchArgs &B = full ? plan->F : plan->B;
-        const int32_t n_su = (int32_t)hs[full].size();
+    size_t first = 0;
+    for (int k = 0; k < 3; ++k) {
+        BatchArgs &B = plan->B[k];
+        const int32_t n_su = (int32_t)hs[k].size();
         B.off = yet->d_off;
         B.ev = yet->d_ev;
         B.trial_begin = trial_major ? o.trial_begin : 0;
         B.trial_count = trial_major ? o.trial_count : 0;
-        B.pfs = (const BatchPf *)(sc + batch_pf_off()) + (full ? hs[0].size() : 0);
+        B.pfs = (const BatchPf *)(sc + batch_pf_off()) + first;
+        first += hs[k].size();
         B.n_pf = n_su;
         B.tile = c.trial_tile;
         B.tail_band = o.tail_band;
         B.dev_band = band_deviate(o.tail_band);
         B.trial_major = trial_major ? 1 : 0;
         B.n_items = trial_major ? ((o.trial_count + c.trial_tile - 1) / c.trial_tile) * (int64_t)n_su
-                                : items[full];
-        B.counter = (unsigned long long *)(sc + 32 * full);
-        B.redo_count = (uint32_t *)(sc + 32 * full + 8);
+                                : items[k];
+        B.counter = (unsigned long long *)(sc + 32 * k);
+        B.redo_count = (uint32_t *)(sc + 32 * k + 8);
         B.redo = (unsigned long long *)(sc + batch_redo_off(n));
         B.status = status ? status : ctx->d_status;
         if (c.waves_per_cu == 0 && B.n_items > 0x7fffffffll)
@@ -1170,7 +1199,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
     }
     plan->tail_band = o.tail_band;
     plan->grid = ctx->n_cu * c.waves_per_cu;           // 0: one workgroup per item
-    plan->redo_grid = ctx->n_cu * 4 * 4;
+    plan->redo_grid = (int)(ctx->n_cu * kFullWaves);
     plan->mode = o.sum_mode;
     plan->f64out = o.ylt_dtype == ARA_F64;
     return ARA_OK;
@@ -1181,9 +1210,9 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
 // primary-uncertainty one, all on stream s.
 hipError_t launch_plan(const ara_context *ctx, const ara_yet *yet, const BatchPlan &plan,
                        hipStream_t s) {
-    hipError_t e = launch_batch(plan.B, plan.mode, plan.f64out, plan.grid, plan.redo_grid, false, s);
-    if (e == hipSuccess)
-        e = launch_batch(plan.F, plan.mode, plan.f64out, plan.grid, plan.redo_grid, true, s);
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 3 && e == hipSuccess; ++k)
+        e = launch_batch(plan.B[k], plan.mode, plan.f64out, plan.grid, plan.redo_grid, kBatchForms[k], s);
     for (size_t k = 0; k < plan.tab.size() && e == hipSuccess; ++k) {
         const TabItem &t = plan.tab[k];
         ara_run_opts o;
@@ -1191,7 +1220,7 @@ hipError_t launch_plan(const ara_context *ctx, const ara_yet *yet, const BatchPl
         o.trial_begin = t.begin;
         o.trial_count = t.count;
         o.tail_band = plan.tail_band;
-        SuLaunch p = su_launch(ctx, yet, t.pf, o, plan.B.status);
+        SuLaunch p = su_launch(ctx, yet, t.pf, o, plan.B[0].status);
         p.ylt_layers = t.ylt_layers;
         p.ylt_pf = t.ylt_pf;
         p.redo = t.flags;
@@ -1204,7 +1233,7 @@ hipError_t launch_plan(const ara_context *ctx, const ara_yet *yet, const BatchPl
         const PuItem &u = plan.pu[k];
         if (u.count > 0)
             e = enqueue_pu(ctx, yet, u.pf, u.begin, u.count, plan.mode, plan.f64out, u.ylt_layers,
-                           u.ylt_pf, nullptr, 0, plan.B.status, s);
+                           u.ylt_pf, nullptr, 0, plan.B[0].status, s);
     }
     return e;
 }

@@ -55,7 +55,7 @@ __device__ __forceinline__ void batch_view(const BatchArgs &B, int p, SuArgs &A,
 // item index is wave-uniform; the portfolio and tile are derived from it
 // (trial-major: tile-then-portfolio; portfolio-major: each portfolio's block
 // of items in turn).
-template <int MODE, bool F64OUT, bool FULL>
+template <int MODE, bool F64OUT, int ROWS>
 __device__ __forceinline__ void batch_item(const BatchArgs &B, unsigned long long item,
                                            const SuLds &S) {
     int64_t tile;
@@ -84,13 +84,13 @@ __device__ __forceinline__ void batch_item(const BatchArgs &B, unsigned long lon
     const int64_t t0 = tile * B.tile;
     const int64_t t1 = (t0 + B.tile) < A.trial_count ? (t0 + B.tile) : A.trial_count;
     for (int64_t t = t0; t < t1; ++t)
-        if (su_trial<MODE, F64OUT, false, FULL>(A, keys, t, S) && threadIdx.x == 0)
+        if (su_trial<MODE, F64OUT, false, ROWS>(A, keys, t, S) && threadIdx.x == 0)
             B.redo[atomicAdd(B.redo_count, 1u)] = ((unsigned long long)p << 32) | (uint64_t)t;
 }
 
 // Persistent form: grid-wide loop over work items taken from an atomic
 // counter (waves_per_cu wavefronts per CU stay resident).
-template <int MODE, bool F64OUT, bool FULL>
+template <int MODE, bool F64OUT, int ROWS>
 __device__ __forceinline__ void batch_loop(const BatchArgs &B, const SuLds &S) {
     const unsigned long long n_items = (unsigned long long)B.n_items;
     while (true) {
@@ -100,29 +100,29 @@ __device__ __forceinline__ void batch_loop(const BatchArgs &B, const SuLds &S) {
         const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(item >> 32));
         item = ((unsigned long long)hi << 32) | lo;
         if (item >= n_items) break;
-        batch_item<MODE, F64OUT, FULL>(B, item, S);
+        batch_item<MODE, F64OUT, ROWS>(B, item, S);
     }
 }
 
-template <int MODE, bool F64OUT>
+template <int MODE, bool F64OUT, int ROWS>
 __global__ __launch_bounds__(64) void k_ara_batch(BatchArgs B) {
     __shared__ float X[kSeg];
     __shared__ uint2 Q[kQCap];
     __shared__ EltDev El[kEltLds];
-    batch_loop<MODE, F64OUT, false>(B, {X, Q, El, nullptr, nullptr});
+    batch_loop<MODE, F64OUT, ROWS>(B, {X, Q, El, nullptr, nullptr});
 }
 
 // One workgroup per work item: the dispatcher hands the items out in index
 // order as wavefronts retire, and a wavefront keeps no state across items,
 // so the kernel runs at the single-portfolio kernel's occupancy.
-template <int MODE, bool F64OUT>
-__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY void k_ara_batch_items(BatchArgs B) {
+template <int MODE, bool F64OUT, int ROWS>
+__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY(ROWS == SU_ITER) void k_ara_batch_items(BatchArgs B) {
     __shared__ float X[kSeg];
     __shared__ uint2 Q[kQCap];
     __shared__ EltDev El[kEltLds];
     const unsigned long long item = blockIdx.x;
     if (item >= (unsigned long long)B.n_items) return;
-    batch_item<MODE, F64OUT, false>(B, item, {X, Q, El, nullptr, nullptr});
+    batch_item<MODE, F64OUT, ROWS>(B, item, {X, Q, El, nullptr, nullptr});
 }
 
 // The full pass: the work items of portfolios with rows that the lean pass
@@ -138,9 +138,9 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_batch_full(BatchA
     const SuLds S = {X, Q, El, XH, QH};
     if (FORM == FULL_ITEMS) {
         if ((int64_t)blockIdx.x < B.n_items)
-            batch_item<MODE, F64OUT, true>(B, (unsigned long long)blockIdx.x, S);
+            batch_item<MODE, F64OUT, SU_FULL>(B, (unsigned long long)blockIdx.x, S);
     } else if (FORM == FULL_LOOP) {
-        batch_loop<MODE, F64OUT, true>(B, S);
+        batch_loop<MODE, F64OUT, SU_FULL>(B, S);
     } else {
         const uint32_t n = *B.redo_count;
         for (uint32_t r = blockIdx.x; r < n; r += gridDim.x) {
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_batch_full(BatchA
             SuArgs A;
             PhiloxKeys keys;
             batch_view(B, p, A, keys);
-            su_trial<MODE, F64OUT, false, true>(A, keys, t, S);
+            su_trial<MODE, F64OUT, false, SU_FULL>(A, keys, t, S);
         }
     }
 }
@@ -162,31 +162,36 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_batch_full(BatchA
 // grid <= 0: one workgroup per work item; otherwise the persistent form with
 // that many workgroups.
 template <int MODE, bool F64OUT>
-static void batch_dispatch(const BatchArgs &B, int grid, int redo_grid, bool full, hipStream_t s) {
+static void batch_dispatch(const BatchArgs &B, int grid, int redo_grid, SuForm form, hipStream_t s) {
     const dim3 items((unsigned)B.n_items), loop((unsigned)(grid > 0 ? grid : 1)), b(64);
     hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(1), 0, s, B.counter, B.redo_count);
-    if (full) {
+    if (form == SU_FULL) {
         if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_full<MODE, F64OUT, FULL_ITEMS>), items, b, 0, s, B);
         else hipLaunchKernelGGL((k_ara_batch_full<MODE, F64OUT, FULL_LOOP>), loop, b, 0, s, B);
         return;
     }
-    if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT>), items, b, 0, s, B);
-    else hipLaunchKernelGGL((k_ara_batch<MODE, F64OUT>), loop, b, 0, s, B);
+    if (form == SU_ITER) {
+        if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT, SU_ITER>), items, b, 0, s, B);
+        else hipLaunchKernelGGL((k_ara_batch<MODE, F64OUT, SU_ITER>), loop, b, 0, s, B);
+    } else {
+        if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT, SU_LEAN>), items, b, 0, s, B);
+        else hipLaunchKernelGGL((k_ara_batch<MODE, F64OUT, SU_LEAN>), loop, b, 0, s, B);
+    }
     hipLaunchKernelGGL((k_ara_batch_full<MODE, F64OUT, FULL_REDO>), dim3(redo_grid), b, 0, s, B);
 }
 
 hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
-                        bool full, hipStream_t s) {
+                        SuForm form, hipStream_t s) {
     if (B.n_items <= 0 || B.n_pf <= 0) return hipSuccess;
     if (mode == ARA_SUM_NAIVE32) {
-        if (f64out) batch_dispatch<ARA_SUM_NAIVE32, true>(B, grid, redo_grid, full, s);
-        else batch_dispatch<ARA_SUM_NAIVE32, false>(B, grid, redo_grid, full, s);
+        if (f64out) batch_dispatch<ARA_SUM_NAIVE32, true>(B, grid, redo_grid, form, s);
+        else batch_dispatch<ARA_SUM_NAIVE32, false>(B, grid, redo_grid, form, s);
     } else if (mode == ARA_SUM_KAHAN32) {
-        if (f64out) batch_dispatch<ARA_SUM_KAHAN32, true>(B, grid, redo_grid, full, s);
-        else batch_dispatch<ARA_SUM_KAHAN32, false>(B, grid, redo_grid, full, s);
+        if (f64out) batch_dispatch<ARA_SUM_KAHAN32, true>(B, grid, redo_grid, form, s);
+        else batch_dispatch<ARA_SUM_KAHAN32, false>(B, grid, redo_grid, form, s);
     } else {
-        if (f64out) batch_dispatch<ARA_SUM_F64, true>(B, grid, redo_grid, full, s);
-        else batch_dispatch<ARA_SUM_F64, false>(B, grid, redo_grid, full, s);
+        if (f64out) batch_dispatch<ARA_SUM_F64, true>(B, grid, redo_grid, form, s);
+        else batch_dispatch<ARA_SUM_F64, false>(B, grid, redo_grid, form, s);
     }
     return hipGetLastError();
 }

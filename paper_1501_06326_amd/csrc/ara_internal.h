@@ -19,8 +19,10 @@ enum : uint32_t {
     ROW_CORR = 1u << 18,   // sigma_I > 0 and sigma_C > 0: mix two normals (section 3.2)
     ROW_CONLY = 1u << 19,  // sigma_I = 0, sigma_C > 0: z = u_C
     ROW_FLAGS = 0xFu << 16,
-    // layer flag: a row that can pay draws and has no shape slot (the full pass)
+    // layer flags: a row that can pay draws and has no shape slot; such a row of the
+    // FP32 quantile's domain, without a mix
     LAYER_SLOW = 1u << 31,
+    LAYER_ITER = 1u << 29,
     // layer flag: no event table (an event with more paying rows than a nibble holds,
     // or more rows than a mark indexes)
     LAYER_DENSE = 1u << 30,
@@ -43,6 +45,8 @@ struct LayerDev {
     int32_t keying;                      // ARA_KEYING_* of the portfolio
     int32_t chunk;                       // occurrences a chunk of the table form takes: 64,
                                          // or fewer so that their hits fit one segment
+    int32_t n_f64;                       // paying rows without a slot, for the FP64 quantile
+    int32_t pad;
     int64_t live_base;                   // even index of the layer's (ev_off[E], rows of E
                                          // that can pay) pairs in the ev_off array
 };
@@ -196,6 +200,7 @@ struct ara_portfolio {
     int32_t max_layer_elts;
     uint32_t all_flags;
     int32_t chunk;             // the smallest of its layers' (see LayerDev)
+    int64_t n_f64;             // of its layers together (see LayerDev)
     ara::LayerDev *d_layers;
     ara::EltDev *d_elts;
     uint32_t *d_evoff;

@@ -51,7 +51,12 @@ struct PuLaunch {
 };
 
 // The passes of a run with secondary uncertainty (ARA_PASS_*).
-enum SuForm { SU_LEAN = ARA_PASS_LEAN, SU_TABLE = ARA_PASS_TABLE, SU_FULL = ARA_PASS_FULL };
+enum SuForm {
+    SU_LEAN = ARA_PASS_LEAN,
+    SU_TABLE = ARA_PASS_TABLE,
+    SU_FULL = ARA_PASS_FULL,
+    SU_ITER = ARA_PASS_ITERATE
+};
 
 struct SuLaunch {
     const int64_t *off;
@@ -150,9 +155,9 @@ hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s);
 hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits, uint32_t *rank,
                                float *vals, LayerDev *d_layer, hipStream_t s);
 hipError_t launch_su(const SuLaunch &p, int mode, bool f64out, hipStream_t s);
-// full: the batch's portfolios take the full pass (see SuLaunch)
+// form: the pass of the batch's portfolios (not SU_TABLE)
 hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
-                        bool full, hipStream_t s);
+                        SuForm form, hipStream_t s);
 // exclusive prefix sum of p[0, n) in place (one block; also used by the
 // exceedance-curve sort for its digit counts)
 hipError_t launch_debug_philox(int64_t n, const uint32_t *ctr, uint64_t key, uint32_t *out,

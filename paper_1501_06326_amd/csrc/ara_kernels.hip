@@ -18,13 +18,14 @@
 //        drained 64 hits at a time so every lane of a batch draws, reads the
 //        quantile of its row's shape slot and applies the ELT terms on real
 //        work (the paper's "convergence switching" idea applied to SIMD lanes).
-//      - k_ara_su_tab (ara_su.hip): the same for large runs, a layer at a time,
-//        with the layer's event table or filter in LDS.
-//      - k_ara_full (ara_su.hip): portfolios with rows of shapes without a
-//        slot, or outside the FP32 domain: the same trial code with the FP32
-//        iteration in the light batches and a second queue for the FP64
-//        quantile; it also takes the trials that the lean pass hands over (a
-//        draw in the caller's tail band).
+//        With rows of shapes without a slot, an instantiation iterates those in
+//        the FP32 domain.
+//      - k_ara_su_tab (ara_su.hip): the same for large runs of slotted rows, a
+//        layer at a time, with the layer's event table or filter in LDS.
+//      - k_ara_full (ara_su.hip): the same trial code with a second queue for
+//        the FP64 quantile; it takes the trials that the lean pass hands over
+//        (a hit outside the FP32 domain, a draw in the caller's tail band), or
+//        every trial where most have such a hit.
 //      - k_ara_batch* (ara_batch.hip): the same trial code over (portfolio,
 //        trial tile) work items of many portfolios at once.
 //      - the occurrence view (per-occurrence increments of the aggregate
@@ -704,7 +705,8 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
     if (threadIdx.x < kShapeSlots) slot[threadIdx.x] = keys[threadIdx.x];
     __syncthreads();
     const uint32_t n = liveoff[n_cat];
-    bool slow = false;         // a row that needs the full pass
+    bool slow = false, iter = false;       // rows without a slot; for the FP32 iteration
+    int32_t n_f64 = 0;                     // for the FP64 quantile
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         RowF &F = rowf[row_base + i];
         uint32_t sh = 0;
@@ -718,9 +720,17 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
         }
         F.rs = (F.rs & ~31u) | sh;
         row_shape[row_base + rowf_row(F)] = sh;
-        slow = slow || (sh == 0u && !(F.meta & ROW_DET));
+        if (sh == 0u && !(F.meta & ROW_DET)) {
+            slow = true;
+            if (F.meta & (ROW_F64 | ROW_CORR)) ++n_f64;
+            else iter = true;
+        }
     }
-    if (__any(slow) && (threadIdx.x & 63) == 0) atomicOr(&layer->flags, LAYER_SLOW);
+    const uint32_t fl = (__any(slow) ? LAYER_SLOW : 0u) | (__any(iter) ? LAYER_ITER : 0u);
+    n_f64 = wave_sum(n_f64);
+    if ((threadIdx.x & 63) != 0) return;
+    if (fl) atomicOr(&layer->flags, fl);
+    if (n_f64) atomicAdd(&layer->n_f64, n_f64);
 }
 
 // The segments of the used slots, and after them the normal segments: one

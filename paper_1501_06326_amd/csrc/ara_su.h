@@ -16,9 +16,11 @@ namespace ara {
 // ---------------------------------------------------------------------------
 // LDS per wavefront: X[kSeg] floats + Q[kQCap] pairs + El[kEltLds] records =
 // 5 KB, so LDS allows the 32 waves per CU that the lean pass's registers do
-// (1M trials, 16 ELTs: 9.92 ms at 8 per SIMD, 10.04 ms at 7)
+// (1M trials, 16 ELTs: 9.92 ms at 8 per SIMD, 10.04 ms at 7).  With the FP32 iteration
+// 6: at 7 it spills 8 registers (65,536 trials x 1,000 occurrences, one row in 10,000
+// iterated: 0.61 against 0.67 ms; all: 1.50 and 1.51).
 constexpr int kQCap = 256;        // hit queue (power of two)
-#define ARA_SU_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
+#define ARA_SU_OCCUPANCY(ITER) __attribute__((amdgpu_waves_per_eu(ITER ? 6 : 8, ITER ? 6 : 8)))
 #define ARA_FULL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 4)))
 // A layer's ELT records are staged in LDS when it has at most this many ELTs
 // (1 KB per wavefront, within the occupancy above); the draw then
@@ -212,12 +214,12 @@ struct SuLds {
 
 // One trial of one layer (Algorithm 1 inside the layer loop).
 //
-// FULL = false is the lean pass: rows without a draw and rows whose shape has
-// a slot.  A draw outside the slot's range (the caller's tail band) abandons
-// the trial, which is then queued for the full pass.  Returns true when
-// abandoned.
+// ROWS = SU_LEAN is the lean pass: rows without a draw and rows whose shape has
+// a slot; SU_ITER also iterates the FP32 quantile of shapes without one.  Any other
+// hit, and a draw in the caller's tail band, abandons the trial, which is then handed
+// to the full pass.  Returns true when abandoned.
 //
-// FULL = true takes every row.  What a light batch cannot finish in FP32
+// ROWS = SU_FULL takes every row.  What a light batch cannot finish in FP32
 // (shapes outside the FP32 domain, the tail band, the mix of shapes without a
 // slot, FP32 non-convergence) goes to a second queue and is drained 64 at a
 // time by the FP64 quantile, so that neither kind of hit waits with idle lanes
@@ -231,10 +233,11 @@ struct SuLds {
 // converged), with 30 % capped rows 0.77 ms (36.6 ms).  Four wavefronts per SIMD
 // (128 VGPRs): the FP64 quantile is a call of its own, since inlined its
 // hoisted constants spill 450 registers; as a call 42.
-template <int MODE, bool F64OUT, bool DIAG, bool FULL, bool OCC>
+template <int MODE, bool F64OUT, bool DIAG, int ROWS, bool OCC>
 __device__ __forceinline__ bool su_layer(const SuArgs &A, const PhiloxKeys &keys, const LayerDev &L,
                                          int l, int64_t t, int64_t o0, int64_t n, const SuLds &S,
                                          double *Y_out) {
+    constexpr bool FULL = ROWS == SU_FULL;
     float *X = S.X;
     uint2 *Q = S.Q;
     EltDev *El = S.El;
@@ -402,7 +405,7 @@ __device__ __forceinline__ bool su_layer(const SuArgs &A, const PhiloxKeys &keys
                         x = slot_quantile(tab, j);
                     }
                     loss = mul_rn(scale, x);
-                } else if (!FULL || (meta & (ROW_F64 | ROW_CORR))) {
+                } else if (ROWS == SU_LEAN || (meta & (ROW_F64 | ROW_CORR))) {
                     defer = true;
                 } else {
                     uint32_t jI, jC;
@@ -817,7 +820,7 @@ __device__ __forceinline__ bool su_layer_tab(const SuArgs &A, const PhiloxKeys &
 }
 
 // All layers of one trial, one wavefront.
-template <int MODE, bool F64OUT, bool DIAG, bool FULL, bool OCC = false>
+template <int MODE, bool F64OUT, bool DIAG, int ROWS, bool OCC = false>
 __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys, int64_t t,
                                          const SuLds &S) {
     const int64_t o0 = A.off[A.trial_begin + t];
@@ -826,7 +829,7 @@ __device__ __forceinline__ bool su_trial(const SuArgs &A, const PhiloxKeys &keys
     for (int l = 0; l < A.n_layers; ++l) {
         const LayerDev L = A.layers[l];
         double Y;
-        if (su_layer<MODE, F64OUT, DIAG, FULL, OCC>(A, keys, L, l, t, o0, n, S, &Y))
+        if (su_layer<MODE, F64OUT, DIAG, ROWS, OCC>(A, keys, L, l, t, o0, n, S, &Y))
             return true;
         if (F64OUT) pf_sum += Y;
         else pf_sum = (double)((float)pf_sum + (float)Y);

@@ -8,19 +8,20 @@
 
 namespace ara {
 
-// Lean pass: one wavefront (block) per trial.  DIAG: every row visited, hit
+// Lean pass: one wavefront (block) per trial.  ITER: with the FP32 quantile of shapes
+// without a slot.  DIAG: every row visited, hit
 // counts and checksums (and the occurrence view when asked for); OCC: the
 // lean pass that also writes the occurrence view (its per-occurrence sums
 // are those of the DIAG pass: the rows it skips add +0).
-template <int MODE, bool F64OUT, bool DIAG, bool OCC = false>
-__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY void k_ara_su(SuArgs A, PhiloxKeys keys) {
+template <int MODE, bool F64OUT, bool DIAG, bool OCC, bool ITER>
+__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY(ITER) void k_ara_su(SuArgs A, PhiloxKeys keys) {
     __shared__ float X[kSeg];
     __shared__ uint2 Q[kQCap];
     __shared__ EltDev El[kEltLds];
     const SuLds S = {X, Q, El, nullptr, nullptr};
     const int64_t t = blockIdx.x;
     if (t >= A.trial_count) return;
-    const bool gone = su_trial<MODE, F64OUT, DIAG, false, OCC>(A, keys, t, S);
+    const bool gone = su_trial<MODE, F64OUT, DIAG, ITER ? SU_ITER : SU_LEAN, OCC>(A, keys, t, S);
     if (threadIdx.x == 0) A.redo[t] = gone;
 }
 
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_full(SuArgs A, Ph
         if (A.redo_step)
             m = __ballot(threadIdx.x < step && r0 + threadIdx.x < n && A.redo[r0 + threadIdx.x] != 0);
         for (; m; m &= m - 1)
-            su_trial<MODE, F64OUT, DIAG, true, OCC>(A, keys, (int64_t)(r0 + (uint32_t)__builtin_ctzll(m)), S);
+            su_trial<MODE, F64OUT, DIAG, SU_FULL, OCC>(A, keys, (int64_t)(r0 + (uint32_t)__builtin_ctzll(m)), S);
     }
 }
 
@@ -158,9 +159,14 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
         full(gr);
         return hipGetLastError();
     }
-    if (diag) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, true>), g, dim3(64), 0, s, A, keys);
-    else if (occ) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, true>), g, dim3(64), 0, s, A, keys);
-    else hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false>), g, dim3(64), 0, s, A, keys);
+    auto lean = [&](auto iter) {
+        constexpr bool I = decltype(iter)::value;
+        if (diag) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, true, false, I>), g, dim3(64), 0, s, A, keys);
+        else if (occ) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, true, I>), g, dim3(64), 0, s, A, keys);
+        else hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, false, I>), g, dim3(64), 0, s, A, keys);
+    };
+    if (p.form == SU_ITER) lean(std::true_type());
+    else lean(std::false_type());
     full(gr);
     return hipGetLastError();
 }
