@@ -363,6 +363,8 @@ hipError_t enqueue_pu(const ara_context *ctx, const ara_yet *yet, const ara_port
             p.form = PU_GLOBAL;
             p.lds = 0;
         }
+        p.short_trials = p.form != PU_BITS &&
+                         occ < (double)count * (p.form == PU_GLOBAL ? kPuViewGlobal : kPuViewLds);
         for (int u = 0; u < p.n_layers; ++u, ++l) {
             PuTable &T = p.tab[u];
             T.otab = pf->d_otab + (int64_t)l * pf->n_catalogue;

@@ -30,6 +30,14 @@ constexpr size_t kPuLdsTwo = 78 * 1024;       // of each of two
 // 1M events, scattered loads against LDS: 2M occurrences 14 - 19 us against 13 - 24 us (by trial
 // length), 4M 22 - 25 us against 14 - 21 us, 64M 295 - 342 us against 86 - 262 us.
 constexpr double kPuLargeOcc = 4e6;
+// Occurrences a trial (the mean) below which the view is made from single occurrences a
+// lane: quads are scanned in three pieces (head, quads, tail), single ones in pieces of
+// 64.  Tables in LDS (sparse; dense alike), quads / singles: 1M trials x 8 594 / 379 us, x 60
+// 768 / 524, 600,000 x 100 497 / 395, 400,000 x 150 360 / 336, 300,000 x 200 291 / 297,
+// 100,000 x 600 172 / 226.  In global memory, where singles are read once more: 1M x 8
+// 704 / 572, x 20 794 / 651, x 40 883 / 863, x 60 995 / 1365.  The bitmap form: 1M x 8 650 /
+// 638, x 20 725 / 768, x 60 806 / 1031, quads always.
+constexpr double kPuViewLds = 160.0, kPuViewGlobal = 32.0;
 enum { PU_GLOBAL = 0, PU_DENSE, PU_SPARSE, PU_BITS };
 
 struct PuLaunch {
@@ -45,6 +53,7 @@ struct PuLaunch {
     void *ylt_layers;
     void *ylt_pf;
     int32_t accumulate_pf;      // 0: ylt_pf = Y, 1: ylt_pf += Y
+    bool short_trials;          // a view by single occurrences
     void *occ_view;             // optional occurrence view (see ara_run_opts)
     int64_t occ_stride;
     Status *status;

@@ -15,6 +15,10 @@ namespace ara {
 //  * the dense table in global memory.
 enum { TAB_GLOBAL = 0, TAB_LDS_DENSE = 1, TAB_LDS_SPARSE = 2, TAB_LDS_BITS = 3 };
 
+// How the occurrence view is made: not, by quads of occurrences a lane from the lookups of
+// the sums, or of short trials by single ones, looked up once more.
+enum { VIEW_NONE = 0, VIEW_QUADS, VIEW_SINGLES };
+
 template <int NL>
 struct PuArgs {
     const int64_t *off;
@@ -55,7 +59,8 @@ template <int TAB>
 __device__ __forceinline__ float pu_look(int32_t n_cat, const PuTable &T, const uint32_t *sm,
                                          int32_t E) {
     if (TAB == TAB_LDS_DENSE) return ((const float *)sm)[E];
-    if (TAB != TAB_LDS_SPARSE) return T.otab[E];
+    if (TAB == TAB_LDS_BITS) return (sm[E >> 5] >> (E & 31)) & 1u ? T.otab[E] : 0.0f;
+    if (TAB == TAB_GLOBAL) return T.otab[E];
     const int32_t nw = (n_cat + 31) >> 5;
     const uint32_t w = sm[E >> 5];
     const uint32_t m = 1u << (E & 31);
@@ -158,9 +163,12 @@ __device__ __forceinline__ void occ_quads(float4 o, bool valid, int64_t pos, con
 // their tables, one by one 650 - 770 us, by scattered loads where a table passed
 // 60 KB 1.07 - 2.20 ms.  VIEW: the layer's occurrence view is written from the same
 // ids and lookups (NL = 1), quads of occurrences scanned at a time: 655 us for
-// 250,000 x 1,000 where a pass of its own over single occurrences made it 970 us.
-template <int MODE, bool F64OUT, int TAB, int NL, bool VIEW>
+// 250,000 x 1,000 where a pass of its own over single occurrences made it 970 us; of
+// short trials from single occurrences (kPuViewLds), 1M x 60 0.52 ms where quads took 0.81
+// and that pass 0.60.
+template <int MODE, bool F64OUT, int TAB, int NL, int VIEWS>
 __device__ __forceinline__ void pu_trials(const PuArgs<NL> &P) {
+    constexpr bool VIEW = VIEWS == VIEW_QUADS;
     extern __shared__ uint32_t sm[];
     pu_stage<TAB, NL>(P, sm);
     const uint32_t *tabs[NL];
@@ -169,9 +177,11 @@ __device__ __forceinline__ void pu_trials(const PuArgs<NL> &P) {
     for (int u = 1; u < NL; ++u)
         tabs[u] = tabs[u - 1] + 2 * ((P.n_cat + 31) >> 5) + 1 + P.tab[u - 1].nnz;
     const int lane = threadIdx.x & 63;
-    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+    // (with a view the trial and what follows from it are kept in scalar registers)
+    const uint32_t w = VIEWS ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / 64) + w;
     const int64_t nwv = (int64_t)gridDim.x * (blockDim.x / 64);
-    const int64_t base = VIEW ? P.off[P.trial_begin] : 0;
+    const int64_t base = VIEWS ? P.off[P.trial_begin] : 0;
     for (int64_t t = wid; t < P.trial_count; t += nwv) {
         const int64_t a = P.off[P.trial_begin + t], b = P.off[P.trial_begin + t + 1];
         const int64_t n = b - a;
@@ -259,6 +269,15 @@ __device__ __forceinline__ void pu_trials(const PuArgs<NL> &P) {
         }
         const int64_t done = head + 4 * n4;
         if (VIEW ? done < n : lane < n - done) add1(done, (int)(n - done));
+        if constexpr (VIEWS == VIEW_SINGLES) {
+            for (int64_t k = lane; k - lane < n; k += 64) {
+                const bool on = k < n;
+                const float o = on ? pu_look<TAB>(P.n_cat, P.tab[0], tabs[0], P.ev[a + k]) : 0.0f;
+                occ_chunk<F64OUT>((double)o, on, a - base + k, P.tab[0].layer, P.occ_view, P.occ_stride,
+                                  P.tab[0].agg_r, P.tab[0].agg_l, &cs, &ca, P.status,
+                                  P.trial_begin + t);
+            }
+        }
         double sum64 = 0.0;               // the portfolio's sum, in layer order
         float sum32 = 0.0f;
 #pragma unroll
@@ -292,17 +311,17 @@ __device__ __forceinline__ void pu_trials(const PuArgs<NL> &P) {
 }
 
 // Tables in LDS: 16 wavefronts per block.
-template <int MODE, bool F64OUT, int TAB, int NL, bool VIEW>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(VIEW || NL > 1 ? 4 : 8, 8))) void k_ara_pu(
+template <int MODE, bool F64OUT, int TAB, int NL, int VIEWS>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(VIEWS == VIEW_QUADS || NL > 1 ? 4 : 8, 8))) void k_ara_pu(
     PuArgs<NL> P) {
-    pu_trials<MODE, F64OUT, TAB, NL, VIEW>(P);
+    pu_trials<MODE, F64OUT, TAB, NL, VIEWS>(P);
 }
 
 // Table in global memory: 4 wavefronts per block.
-template <int MODE, bool F64OUT, bool VIEW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(VIEW ? 4 : 7, 7))) void k_ara_pu_global(
+template <int MODE, bool F64OUT, int VIEWS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(VIEWS == VIEW_QUADS ? 4 : 7, 7))) void k_ara_pu_global(
     PuArgs<1> P) {
-    pu_trials<MODE, F64OUT, TAB_GLOBAL, 1, VIEW>(P);
+    pu_trials<MODE, F64OUT, TAB_GLOBAL, 1, VIEWS>(P);
 }
 
 template <int NL>
@@ -316,9 +335,9 @@ static PuArgs<NL> pu_args(const PuLaunch &p) {
     return A;
 }
 
-template <int MODE, bool F64OUT, int TAB, int NL, bool VIEW>
+template <int MODE, bool F64OUT, int TAB, int NL, int VIEWS>
 static hipError_t pu_lds(const PuLaunch &p, hipStream_t s) {
-    const auto kernel = k_ara_pu<MODE, F64OUT, TAB, NL, VIEW>;
+    const auto kernel = k_ara_pu<MODE, F64OUT, TAB, NL, VIEWS>;
     const int64_t blocks = (p.trial_count + 15) / 16;
     const int64_t cap = (int64_t)p.n_cu * (p.lds <= kPuLdsTwo ? 2 : 1);
     if (p.lds > 64 * 1024) {
@@ -332,27 +351,29 @@ static hipError_t pu_lds(const PuLaunch &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int MODE, bool F64OUT, bool VIEW>
+template <int MODE, bool F64OUT, int VIEWS>
 static hipError_t pu_dispatch(const PuLaunch &p, hipStream_t s) {
-    if (p.form == PU_DENSE) return pu_lds<MODE, F64OUT, TAB_LDS_DENSE, 1, VIEW>(p, s);
-    if (p.form == PU_BITS) return pu_lds<MODE, F64OUT, TAB_LDS_BITS, 1, VIEW>(p, s);
+    if (p.form == PU_DENSE) return pu_lds<MODE, F64OUT, TAB_LDS_DENSE, 1, VIEWS>(p, s);
+    if (p.form == PU_BITS) return pu_lds<MODE, F64OUT, TAB_LDS_BITS, 1, VIEWS ? VIEW_QUADS : VIEW_NONE>(p, s);
     if (p.form == PU_SPARSE) {
-        if constexpr (!VIEW) {
-            if (p.n_layers == 2) return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 2, false>(p, s);
-            if (p.n_layers == 3) return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 3, false>(p, s);
-            if (p.n_layers == 4) return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 4, false>(p, s);
+        if constexpr (VIEWS == VIEW_NONE) {
+            if (p.n_layers == 2) return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 2, VIEW_NONE>(p, s);
+            if (p.n_layers == 3) return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 3, VIEW_NONE>(p, s);
+            if (p.n_layers == 4) return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 4, VIEW_NONE>(p, s);
         }
-        return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 1, VIEW>(p, s);
+        return pu_lds<MODE, F64OUT, TAB_LDS_SPARSE, 1, VIEWS>(p, s);
     }
     const int64_t blocks = (p.trial_count + 3) / 4, cap = (int64_t)p.n_cu * 16;
-    hipLaunchKernelGGL((k_ara_pu_global<MODE, F64OUT, VIEW>),
+    hipLaunchKernelGGL((k_ara_pu_global<MODE, F64OUT, VIEWS>),
                        dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(256), 0, s, pu_args<1>(p));
     return hipGetLastError();
 }
 
 template <int MODE, bool F64OUT>
 static hipError_t pu_view(const PuLaunch &p, hipStream_t s) {
-    return p.occ_view ? pu_dispatch<MODE, F64OUT, true>(p, s) : pu_dispatch<MODE, F64OUT, false>(p, s);
+    if (!p.occ_view) return pu_dispatch<MODE, F64OUT, VIEW_NONE>(p, s);
+    return p.short_trials ? pu_dispatch<MODE, F64OUT, VIEW_SINGLES>(p, s)
+                          : pu_dispatch<MODE, F64OUT, VIEW_QUADS>(p, s);
 }
 
 hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s) {
