@@ -56,3 +56,43 @@ def test_per_thread_stream(ara):
         ara.free_portfolio(q)
     ara.free_portfolio(p)
     ara.free_yet(y)
+
+
+@pytest.mark.parametrize("rows", [1, 32_767, 32_768, 32_769, 52_428, 52_429, 120_000])
+def test_rows_by_size(ara, rows):
+    """Rows copied from the caller's array (up to 32,768), from one buffer and from
+    several: split over two ELTs of one layer, every row arrives (the diagnostic pass
+    counts a hit for each, once per event of a YET that visits every event)."""
+    import numpy as np
+    from workloads import ELT, YET
+    n_cat = 70_000
+    elts, left = [], rows
+    for e in range(2):
+        n = (rows + 1) // 2 if e == 0 else left
+        left -= n
+        ev = np.arange(n, dtype=np.int32)
+        m = np.full(n, 1e5, np.float32) + np.arange(n, dtype=np.float32)
+        zero = np.zeros(n, np.float32)
+        elts.append(ELT(elt_id=e, event_ids=ev, mean=m, sigma_i=zero, sigma_c=zero, max_loss=2 * m,
+                        retention=0.0, limit=1e12, share=1.0))
+    inf = float("inf")
+    pf = Portfolio(layers=[Layer(elts=elts, occ_retention=0.0, occ_limit=inf, agg_retention=0.0,
+                                 agg_limit=inf)], seed=1)
+    off = np.arange(0, n_cat + 1, 70, dtype=np.int64)
+    yet = YET(offsets=off, event_ids=np.arange(n_cat, dtype=np.int32), times=None, n_catalogue=n_cat)
+    print("rows by size", rows, flush=True)
+    y = ara.load_yet(yet)
+    for _ in range(2):
+        p = ara.load_portfolio(pf, n_cat)
+        d = ara.run(y, p, diagnostics=True, sum_mode="f64", ylt_dtype="f64")
+        per_event = np.zeros(n_cat)
+        hits = np.zeros(n_cat, np.int64)
+        for e in elts:
+            np.add.at(per_event, e.event_ids, e.mean.astype(np.float64))
+            np.add.at(hits, e.event_ids, 1)
+        assert np.array_equal(d["hits"][0].cpu().numpy(), hits.reshape(-1, 70).sum(axis=1))
+        # two FP32 losses an event are added in FP32
+        want = per_event.reshape(-1, 70).sum(axis=1)
+        assert np.all(np.abs(d["ylt"][0].cpu().numpy() - want) <= 2.0 ** -24 * want)
+        ara.free_portfolio(p)
+    ara.free_yet(y)
