@@ -147,26 +147,29 @@ bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfol
 // which are scanned 64 at a time, then would not round as those of the other passes.
 //
 // Rows without a slot: those of the FP32 quantile's domain are iterated in the lean pass
-// (SU_ITER), trials with a hit of the others are handed over, and where more than half of
-// the trials have one, or the full pass has every trial resident at once, so that the
-// two passes' latencies would add up, the full pass runs alone.  The share of trials is
-// that of a uniform catalogue.  65,536 trials x 1,000 occurrences of 16 x 20,000 rows, full
+// (SU_ITER), trials with a hit of the others, or a mixed draw beyond the deviate segments'
+// 2^-24, are handed over, and where more than half of the trials are, or the full pass
+// has every trial resident at once, so that the two passes' latencies would add up, and
+// one of them is to be expected, the full pass runs alone.  The share of trials is that of a uniform
+// catalogue.  65,536 trials x 1,000 occurrences of 16 x 20,000 rows, full
 // pass alone / this: 17 shapes 2.43 / 1.38 ms, every row its own 2.35 / 1.50, odd FP32
 // shapes among one in 0.01 % of the rows 1.67 / 0.61 and in 10 % 2.29 / 1.21; FP64 rows among
 // one shape, a share of the trials of 0.12 1.68 / 0.89, of 0.7 1.75 / 1.68, of 1 1.89 /
 // 1.98.  20,000 x 300: 0.09 138 / 81 us, 0.6 154 / 157; 10,000 x 100: 0.05 46 / 36, 0.4 53 / 52,
 // 1 69 / 81.  12,000 x 1,000, 0.1: 295 / 202 us, 6,000 180 / 142, 4,096 (all resident) 114 / 121,
-// 500 56 / 86.
+// 500 56 / 86.  1,000 x 1,000 of 2 x 24 x 30,000 mixed rows, 1.5 trials expected: 0.55 / 0.90 ms
+// (0.47 where none was; 100 x 1,000: 0.47 / 0.38).
 SuForm su_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf, int64_t trials,
                bool diag, bool view) {
-    if (pf->all_flags & LAYER_SLOW) {
+    if (pf->n_f64 > 0 || pf->n_mix > 0) {
         const double mean_len = (double)yet->n_occ / (double)std::max<int64_t>(yet->n_trials, 1);
-        const double hits = mean_len * (double)pf->n_f64 / (double)pf->n_catalogue;
-        const double share = 1.0 - std::exp(-hits);
+        // a mixed draw lies beyond 2^-24 on either side once in 2^23
+        const double rows = (double)pf->n_f64 + (double)pf->n_mix / 8388608.0;
+        const double share = 1.0 - std::exp(-mean_len * rows / (double)pf->n_catalogue);
         const bool resident = trials <= (int64_t)ctx->n_cu * kFullWaves;
         if (share > 0.5 || (resident && share * (double)trials > 1.0)) return SU_FULL;
-        return pf->all_flags & LAYER_ITER ? SU_ITER : SU_LEAN;
     }
+    if (pf->all_flags & LAYER_SLOW) return pf->all_flags & LAYER_ITER ? SU_ITER : SU_LEAN;
     if (diag || (view && pf->chunk < kWave)) return SU_LEAN;
     return su_table_form(ctx, yet, pf, trials) ? SU_TABLE : SU_LEAN;
 }
@@ -852,10 +855,11 @@ ara_status ara_load_portfolio(ara_context *ctx, const ara_portfolio_desc *desc,
 #undef ARA_HIP_P
     p->all_flags = 0;
     p->chunk = kWave;
-    p->n_f64 = 0;
+    p->n_f64 = p->n_mix = 0;
     for (int l = 0; l < nl; ++l) {
         p->all_flags |= p->h_layers[l].flags;
         p->n_f64 += p->h_layers[l].n_f64;
+        p->n_mix += p->h_layers[l].n_mix;
         p->chunk = std::min(p->chunk, p->h_layers[l].chunk);
     }
     ctx->pfs.insert(p);

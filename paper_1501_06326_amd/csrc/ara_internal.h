@@ -46,7 +46,7 @@ struct LayerDev {
     int32_t chunk;                       // occurrences a chunk of the table form takes: 64,
                                          // or fewer so that their hits fit one segment
     int32_t n_f64;                       // paying rows without a slot, for the FP64 quantile
-    int32_t pad;
+    int32_t n_mix;                       // paying rows of the two-normal mix with a slot
     int64_t live_base;                   // even index of the layer's (ev_off[E], rows of E
                                          // that can pay) pairs in the ev_off array
 };
@@ -200,7 +200,7 @@ struct ara_portfolio {
     int32_t max_layer_elts;
     uint32_t all_flags;
     int32_t chunk;             // the smallest of its layers' (see LayerDev)
-    int64_t n_f64;             // of its layers together (see LayerDev)
+    int64_t n_f64, n_mix;      // of its layers together (see LayerDev)
     ara::LayerDev *d_layers;
     ara::EltDev *d_elts;
     uint32_t *d_evoff;

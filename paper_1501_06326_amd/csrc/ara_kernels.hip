@@ -706,7 +706,7 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
     __syncthreads();
     const uint32_t n = liveoff[n_cat];
     bool slow = false, iter = false;       // rows without a slot; for the FP32 iteration
-    int32_t n_f64 = 0;                     // for the FP64 quantile
+    int32_t n_f64 = 0, n_mix = 0;          // for the FP64 quantile; mixed, with a slot
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         RowF &F = rowf[row_base + i];
         uint32_t sh = 0;
@@ -725,12 +725,15 @@ __global__ __launch_bounds__(256) void k_shape_assign(RowF *__restrict__ rowf,
             if (F.meta & (ROW_F64 | ROW_CORR)) ++n_f64;
             else iter = true;
         }
+        if (sh != 0u && (F.meta & ROW_CORR)) ++n_mix;
     }
     const uint32_t fl = (__any(slow) ? LAYER_SLOW : 0u) | (__any(iter) ? LAYER_ITER : 0u);
     n_f64 = wave_sum(n_f64);
+    n_mix = wave_sum(n_mix);
     if ((threadIdx.x & 63) != 0) return;
     if (fl) atomicOr(&layer->flags, fl);
     if (n_f64) atomicAdd(&layer->n_f64, n_f64);
+    if (n_mix) atomicAdd(&layer->n_mix, n_mix);
 }
 
 // The segments of the used slots, and after them the normal segments: one

@@ -134,3 +134,29 @@ def test_odd_rows(ara, n_iter, n_f64, n_mix, keying, layers, want):
     for h in (p, p2):
         ara.free_portfolio(h)
     ara.free_yet(y)
+
+
+def test_mixed_rows_all_resident(ara):
+    """10.8 million mixed draws in 4,000 resident trials: more than one is expected beyond
+    2^-24, so the full pass runs alone; slices, where none is, take the lean pass and give
+    the same bits."""
+    from paper_1501_06326_amd.ara import ARA_PASS_FULL, ARA_PASS_LEAN
+    rng = np.random.default_rng(2)
+    n_cat, n = 500, 4000
+    off = np.arange(n + 1, dtype=np.int64) * 600
+    yet = YET(offsets=off, event_ids=rng.integers(0, n_cat, off[-1]).astype(np.int32), times=None,
+              n_catalogue=n_cat)
+    pf = Portfolio(layers=[Layer(elts=[make_elt(e, 450, n_cat, e, corr=True, retention=1e3, limit=5e7)
+                                       for e in range(5)], occ_retention=1e4, occ_limit=2e8,
+                                 agg_retention=1e5, agg_limit=1e12)], seed=3)
+    print("mixed rows, all resident", flush=True)
+    y = ara.load_yet(yet)
+    p = ara.load_portfolio(pf, n_cat)
+    assert ara.debug_run_pass(y, p) == ARA_PASS_FULL
+    r = ara.run(y, p)
+    for a in range(0, n, 1000):
+        assert ara.debug_run_pass(y, p, trial_begin=a, trial_count=1000) == ARA_PASS_LEAN
+        s = ara.run(y, p, trial_begin=a, trial_count=1000)
+        assert torch.equal(s["ylt"], r["ylt"][:, a:a + 1000])
+    ara.free_portfolio(p)
+    ara.free_yet(y)
