@@ -95,7 +95,8 @@ float band_deviate(float band) {
 void su_scratch(const ara_context *ctx, const ara_portfolio *pf, SuLaunch *p, char *scr,
                 const ara_run_opts &o) {
     p->redo = (int32_t *)(scr + 256);
-    const int64_t most = pf->n_f64 > 0 ? kRedoBlocks : (int64_t)ctx->n_cu * kFullWaves;
+    const bool many = pf->n_f64 > 0 || o.tail_band > kDefaultTailBand;
+    const int64_t most = many ? kRedoBlocks : (int64_t)ctx->n_cu * kFullWaves;
     p->redo_grid = (int)std::max<int64_t>(1, std::min<int64_t>(o.trial_count, most));
     if (o.debug_flags & ARA_DEBUG_QUANTILE_ONE_STEP) {
         p->tail_band = 2.0f;       // every draw takes the FP64 quantile ...
