@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64) void k_ara_batch(BatchArgs B) {
 // order as wavefronts retire, and a wavefront keeps no state across items,
 // so the kernel runs at the single-portfolio kernel's occupancy.
 template <int MODE, bool F64OUT, int ROWS>
-__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY(ROWS == SU_ITER) void k_ara_batch_items(BatchArgs B) {
+__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY(ROWS == SU_ITER ? 6 : 8) void k_ara_batch_items(BatchArgs B) {
     __shared__ float X[kSeg];
     __shared__ uint2 Q[kQCap];
     __shared__ EltDev El[kEltLds];

@@ -18,9 +18,10 @@ namespace ara {
 // 5 KB, so LDS allows the 32 waves per CU that the lean pass's registers do
 // (1M trials, 16 ELTs: 9.92 ms at 8 per SIMD, 10.04 ms at 7).  With the FP32 iteration
 // 6: at 7 it spills 8 registers (65,536 trials x 1,000 occurrences, one row in 10,000
-// iterated: 0.61 against 0.67 ms; all: 1.50 and 1.51).
+// iterated: 0.61 against 0.67 ms; all: 1.50 and 1.51), with a view or diagnostics 7 (at 8 up
+// to 14: 20,000 x 200 over 2 layers of 250,000 events 104 against 128 us with a view).
 constexpr int kQCap = 256;        // hit queue (power of two)
-#define ARA_SU_OCCUPANCY(ITER) __attribute__((amdgpu_waves_per_eu(ITER ? 6 : 8, ITER ? 6 : 8)))
+#define ARA_SU_OCCUPANCY(N) __attribute__((amdgpu_waves_per_eu(N, N)))
 #define ARA_FULL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 4)))
 // A layer's ELT records are staged in LDS when it has at most this many ELTs
 // (1 KB per wavefront, within the occupancy above); the draw then

@@ -14,7 +14,7 @@ namespace ara {
 // lean pass that also writes the occurrence view (its per-occurrence sums
 // are those of the DIAG pass: the rows it skips add +0).
 template <int MODE, bool F64OUT, bool DIAG, bool OCC, bool ITER>
-__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY(ITER) void k_ara_su(SuArgs A, PhiloxKeys keys) {
+__global__ __launch_bounds__(64) ARA_SU_OCCUPANCY(ITER ? 6 : DIAG || OCC ? 7 : 8) void k_ara_su(SuArgs A, PhiloxKeys keys) {
     __shared__ float X[kSeg];
     __shared__ uint2 Q[kQCap];
     __shared__ EltDev El[kEltLds];
