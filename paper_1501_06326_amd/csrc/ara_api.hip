@@ -107,6 +107,15 @@ void su_scratch(const ara_context *ctx, const ara_portfolio *pf, SuLaunch *p, ch
     p->dev_band = band_deviate(p->tail_band);
 }
 
+constexpr double kL2 = 4.0 * 1024.0 * 1024.0;     // of an XCD
+
+int64_t su_mean_len(const ara_yet *yet) { return yet->n_occ / (yet->n_trials > 0 ? yet->n_trials : 1); }
+// What the lean pass gathers from: the layers' pairs and an eighth of their records, which
+// are read by hits alone.
+double su_bytes(const ara_portfolio *pf) {
+    return 8.0 * pf->n_layers * (double)pf->n_catalogue + 2.0 * (double)pf->n_rows;
+}
+
 // Whether a run of so many trials takes the lean pass in its event-table form (with the
 // table of small catalogues in LDS, or the filter of larger ones), for portfolios that it
 // can hold: no rows for the full pass, no mixed rows, whose extra lookups its four
@@ -115,8 +124,8 @@ void su_scratch(const ara_context *ctx, const ara_portfolio *pf, SuLaunch *p, ch
 // it saves the scattered pair lookups, which cost the more the more of them miss the 4 MB
 // L2 of an XCD.  Measured, one-wavefront form / this one (lam: occurrences a trial; hits:
 // rows per event):
-//  * the layers' pairs and an eighth of their records, which are read by hits alone, beyond
-//    the L2: 1 layer of 1M events, 0.3 hits: lam 300 x 4,096 trials 25 / 22 us, 1000 x 65,536
+//  * su_bytes beyond the L2 (the one-wavefront form as it was at eight wavefronts per SIMD,
+//    see su_lds): 1 layer of 1M events, 0.3 hits: lam 300 x 4,096 trials 25 / 22 us, 1000 x 65,536
 //    763 / 326; 4 layers of 250,000 events: 300 x 16,384 153 / 163 (0.07 hits) and 407 / 288
 //    (2.9), 1000 x 4,096 103 / 113 and 241 / 234, 1000 x 16,384 516 / 316 and 1339 / 740; 3 of
 //    100,000 events, 3.2 hits: 300 x 32,768 377 / 378, 1000 x 16,384 559 / 500.  The line is
@@ -133,11 +142,11 @@ bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfol
     if (!pf->d_evtab || pf->n_layers == 0) return false;
     if (pf->all_flags & (LAYER_DENSE | LAYER_SLOW | ROW_CORR)) return false;
     if (trials < (int64_t)ctx->n_cu * kTabWaves) return false;
-    const int64_t mean_len = yet->n_occ / (yet->n_trials > 0 ? yet->n_trials : 1);
-    const double occ = (double)trials * (double)mean_len, mb = 1024.0 * 1024.0;
-    const double bytes = 8.0 * pf->n_layers * (double)pf->n_catalogue + 2.0 * (double)pf->n_rows;
-    if (bytes > 4.0 * mb) return mean_len >= kSeg / 2 && occ * bytes >= 16e6 * mb * pf->n_layers;
-    if (4.0 * occ > 256.0 * mb)
+    const int64_t mean_len = su_mean_len(yet);
+    const double occ = (double)trials * (double)mean_len;
+    if (su_bytes(pf) > kL2)
+        return mean_len >= kSeg / 2 && occ * su_bytes(pf) >= 4e6 * kL2 * pf->n_layers;
+    if (4.0 * occ > 64.0 * kL2)
         return mean_len >= (ev_filter(pf->n_catalogue) ? kSeg : kSeg * 5 / 4);
     return mean_len >= kSeg * 3 / 2 && trials >= 16384 &&
            (pf->n_layers > 1 || pf->n_rows <= pf->n_catalogue);
@@ -175,6 +184,23 @@ SuForm su_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *
     return su_table_form(ctx, yet, pf, trials) ? SU_TABLE : SU_LEAN;
 }
 
+// Dynamic LDS of the lean pass' one-wavefront form, which it doesn't use: with it a CU
+// holds 21 wavefronts, not 32.  Each wavefront is in a layer of its own, and where what
+// they gather from together (bytes, of several layers) exceeds the 4 MB L2 of an XCD well,
+// more wavefronts miss it more; not where all trials are resident at once.  Eight / six /
+// five per SIMD: 4 layers of 250,000 events (8 MB), 300 x 16,384 152 / 125 / 134 us, 1000 x
+// 16,384 514 / 405 / 371; 8 of 100,000 (6.5 MB), 300 x 40,000 717 / 565 / 537, batches of 4 such, 300 x
+// 8,000 699 / 594 / 512; 2 of 250,000 (4.4 MB) 300 x 12,288 67 / - / 70, 4 of 100,000 (3.2
+// MB) 300 x 16,384 111 / 109 / 115; one layer of 250,000 1000 x 8,192 56 / 57 / 58; short
+// trials, 4 of 250,000, 100 x 16,384 66 / 70 / 79.  The diagnostic pass gathers more: 2 of
+// 250,000, 600 x 16,384 409 / 387 / 357.
+size_t su_lds(const ara_context *ctx, const ara_yet *yet, double bytes, bool several, int64_t trials,
+              bool diag) {
+    const bool misses = several && bytes > (diag ? 1.0 : 1.25) * kL2 &&
+                        su_mean_len(yet) >= kSeg / 2 && trials > (int64_t)ctx->n_cu * 32;
+    return misses ? 2560 : 0;
+}
+
 // The launch of one secondary-uncertainty portfolio over o's trials, without its
 // outputs and hand-over scratch.
 SuLaunch su_launch(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *pf,
@@ -205,6 +231,8 @@ SuLaunch su_launch(const ara_context *ctx, const ara_yet *yet, const ara_portfol
     p.evtab = pf->d_evtab;
     p.n_cat = pf->n_catalogue;
     p.n_cu = ctx->n_cu;
+    p.lds = su_lds(ctx, yet, su_bytes(pf), pf->n_layers > 1, o.trial_count,
+                   o.d_hits || o.d_hit_chk);
     return p;
 }
 
@@ -1086,6 +1114,7 @@ struct BatchPlan {
     BatchArgs B[3];
     float tail_band;
     std::vector<TabItem> tab;      // launches of their own: the event-table form
+    size_t lds[3];                 // of the shared launches of the lean pass (see su_lds)
     int grid, redo_grid, mode;
     bool f64out;
     std::vector<PuItem> pu;
@@ -1126,6 +1155,9 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
     if (ranges && c.order == ARA_BATCH_TRIAL_MAJOR)
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: trial-major order needs one trial range");
     int64_t total = 0, listed = 0, items[3] = {0, 0, 0};
+    double gathered[3] = {0.0, 0.0, 0.0};
+    bool several[3] = {false, false, false};
+    int64_t trials[3] = {0, 0, 0};
     std::vector<BatchPf> hs[3];    // see kBatchForms
     plan->pu.clear();
     plan->tab.clear();
@@ -1152,6 +1184,11 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
             continue;
         }
         const int k = form == SU_LEAN ? 0 : form == SU_ITER ? 1 : 2;
+        // what wavefronts gather from at a time: a portfolio's, or in trial-major order all
+        const double more = su_bytes(p);
+        several[k] = several[k] || p->n_layers > 1 || (c.order == ARA_BATCH_TRIAL_MAJOR && !hs[k].empty());
+        trials[k] += tc;
+        gathered[k] = c.order == ARA_BATCH_TRIAL_MAJOR ? gathered[k] + more : std::max(gathered[k], more);
         hs[k].emplace_back();
         BatchPf &b = hs[k].back();
         b.layers = p->d_layers;
@@ -1190,6 +1227,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
     for (int k = 0; k < 3; ++k) {
         BatchArgs &B = plan->B[k];
         const int32_t n_su = (int32_t)hs[k].size();
+        plan->lds[k] = su_lds(ctx, yet, gathered[k], several[k], trials[k], false);
         B.off = yet->d_off;
         B.ev = yet->d_ev;
         B.trial_begin = trial_major ? o.trial_begin : 0;
@@ -1232,7 +1270,8 @@ hipError_t launch_plan(const ara_context *ctx, const ara_yet *yet, const BatchPl
                        hipStream_t s) {
     hipError_t e = hipSuccess;
     for (int k = 0; k < 3 && e == hipSuccess; ++k)
-        e = launch_batch(plan.B[k], plan.mode, plan.f64out, plan.grid, plan.redo_grid, kBatchForms[k], s);
+        e = launch_batch(plan.B[k], plan.mode, plan.f64out, plan.grid, plan.redo_grid, kBatchForms[k],
+                         plan.lds[k], s);
     for (size_t k = 0; k < plan.tab.size() && e == hipSuccess; ++k) {
         const TabItem &t = plan.tab[k];
         ara_run_opts o;

@@ -159,10 +159,10 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_batch_full(BatchA
     }
 }
 
-// grid <= 0: one workgroup per work item; otherwise the persistent form with
-// that many workgroups.
+// grid <= 0: one workgroup per work item (of the lean pass with so much dynamic LDS);
+// otherwise the persistent form with that many workgroups.
 template <int MODE, bool F64OUT>
-static void batch_dispatch(const BatchArgs &B, int grid, int redo_grid, SuForm form, hipStream_t s) {
+static void batch_dispatch(const BatchArgs &B, int grid, int redo_grid, SuForm form, size_t lds, hipStream_t s) {
     const dim3 items((unsigned)B.n_items), loop((unsigned)(grid > 0 ? grid : 1)), b(64);
     hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(1), 0, s, B.counter, B.redo_count);
     if (form == SU_FULL) {
@@ -171,27 +171,27 @@ static void batch_dispatch(const BatchArgs &B, int grid, int redo_grid, SuForm f
         return;
     }
     if (form == SU_ITER) {
-        if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT, SU_ITER>), items, b, 0, s, B);
+        if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT, SU_ITER>), items, b, lds, s, B);
         else hipLaunchKernelGGL((k_ara_batch<MODE, F64OUT, SU_ITER>), loop, b, 0, s, B);
     } else {
-        if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT, SU_LEAN>), items, b, 0, s, B);
+        if (grid <= 0) hipLaunchKernelGGL((k_ara_batch_items<MODE, F64OUT, SU_LEAN>), items, b, lds, s, B);
         else hipLaunchKernelGGL((k_ara_batch<MODE, F64OUT, SU_LEAN>), loop, b, 0, s, B);
     }
     hipLaunchKernelGGL((k_ara_batch_full<MODE, F64OUT, FULL_REDO>), dim3(redo_grid), b, 0, s, B);
 }
 
 hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
-                        SuForm form, hipStream_t s) {
+                        SuForm form, size_t lds, hipStream_t s) {
     if (B.n_items <= 0 || B.n_pf <= 0) return hipSuccess;
     if (mode == ARA_SUM_NAIVE32) {
-        if (f64out) batch_dispatch<ARA_SUM_NAIVE32, true>(B, grid, redo_grid, form, s);
-        else batch_dispatch<ARA_SUM_NAIVE32, false>(B, grid, redo_grid, form, s);
+        if (f64out) batch_dispatch<ARA_SUM_NAIVE32, true>(B, grid, redo_grid, form, lds, s);
+        else batch_dispatch<ARA_SUM_NAIVE32, false>(B, grid, redo_grid, form, lds, s);
     } else if (mode == ARA_SUM_KAHAN32) {
-        if (f64out) batch_dispatch<ARA_SUM_KAHAN32, true>(B, grid, redo_grid, form, s);
-        else batch_dispatch<ARA_SUM_KAHAN32, false>(B, grid, redo_grid, form, s);
+        if (f64out) batch_dispatch<ARA_SUM_KAHAN32, true>(B, grid, redo_grid, form, lds, s);
+        else batch_dispatch<ARA_SUM_KAHAN32, false>(B, grid, redo_grid, form, lds, s);
     } else {
-        if (f64out) batch_dispatch<ARA_SUM_F64, true>(B, grid, redo_grid, form, s);
-        else batch_dispatch<ARA_SUM_F64, false>(B, grid, redo_grid, form, s);
+        if (f64out) batch_dispatch<ARA_SUM_F64, true>(B, grid, redo_grid, form, lds, s);
+        else batch_dispatch<ARA_SUM_F64, false>(B, grid, redo_grid, form, lds, s);
     }
     return hipGetLastError();
 }

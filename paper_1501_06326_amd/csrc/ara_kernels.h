@@ -92,6 +92,7 @@ struct SuLaunch {
     int32_t *redo;            // [trial_count] scratch: flags of trials handed to the full pass
     int redo_grid;            // blocks of the second pass
     SuForm form;
+    size_t lds;               // dynamic LDS of the lean pass (see su_lds)
     const LayerDev *h_layers; // host copies of the layers (the table form)
     const uint32_t *evtab;    // the layers' event tables (the table form)
     int32_t n_cat;
@@ -164,9 +165,9 @@ hipError_t launch_pu(const PuLaunch &p, int mode, bool f64out, hipStream_t s);
 hipError_t launch_build_sparse(const float *otab, int32_t n_cat, uint32_t *bits, uint32_t *rank,
                                float *vals, LayerDev *d_layer, hipStream_t s);
 hipError_t launch_su(const SuLaunch &p, int mode, bool f64out, hipStream_t s);
-// form: the pass of the batch's portfolios (not SU_TABLE)
+// form: the pass of the batch's portfolios (not SU_TABLE); lds: see su_lds
 hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
-                        SuForm form, hipStream_t s);
+                        SuForm form, size_t lds, hipStream_t s);
 // exclusive prefix sum of p[0, n) in place (one block; also used by the
 // exceedance-curve sort for its digit counts)
 hipError_t launch_debug_philox(int64_t n, const uint32_t *ctr, uint64_t key, uint32_t *out,

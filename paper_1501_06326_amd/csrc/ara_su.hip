@@ -161,9 +161,9 @@ static hipError_t su_dispatch2(const SuLaunch &p, hipStream_t s) {
     }
     auto lean = [&](auto iter) {
         constexpr bool I = decltype(iter)::value;
-        if (diag) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, true, false, I>), g, dim3(64), 0, s, A, keys);
-        else if (occ) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, true, I>), g, dim3(64), 0, s, A, keys);
-        else hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, false, I>), g, dim3(64), 0, s, A, keys);
+        if (diag) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, true, false, I>), g, dim3(64), p.lds, s, A, keys);
+        else if (occ) hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, true, I>), g, dim3(64), p.lds, s, A, keys);
+        else hipLaunchKernelGGL((k_ara_su<MODE, F64OUT, false, false, I>), g, dim3(64), p.lds, s, A, keys);
     };
     if (p.form == SU_ITER) lean(std::true_type());
     else lean(std::false_type());
