@@ -23,7 +23,8 @@
  *  - The library allocates no large device memory: the YET is borrowed from
  *    the caller, portfolio tables live in a caller-provided workspace, outputs
  *    and scratch are caller buffers.  A context keeps a few hundred bytes of
- *    device status words.
+ *    device status words and, from its first load of more than 32,768 rows to
+ *    ara_destroy, up to 4 MB of pinned host memory that rows are staged in.
  *
  * Readings of points the paper leaves open (used identically by the tests'
  * FP64 reference):
@@ -239,17 +240,18 @@ ara_status ara_sync_status(ara_context *ctx, void *stream);
 
 /* ---- batched portfolios --------------------------------------------------
  * Several portfolios (Algorithm 1's outer portfolio / program loops) over one
- * YET.  Work items are (tile of trial_tile trials, portfolio), handed out from an atomic counter in one of two orders:
- * portfolio-major (each portfolio's tiles in turn: its ELT tables stay in the
+ * YET.  Work items are (tile of trial_tile trials, portfolio), handed out in one
+ * of two orders: portfolio-major (each portfolio's tiles in turn: its ELT tables stay in the
  * caches, the better order when the draws dominate) or trial-major (the
  * portfolios of one tile together: the tile's event ids are read once for all
  * of them, the better order for primary-uncertainty batches, which are bound
  * by memory traffic).  Results are bit-identical to running each portfolio
  * alone with ara_run, all on one stream (and captured together by
- * ara_batch_graph_create): the secondary-uncertainty portfolios that the lean
- * pass can take share one launch and those with rows for the full pass
- * another; those large enough for ara_run's event-table form, and the
- * primary-uncertainty ones, run ara_run's passes after them.  d_ylt_layers /
+ * ara_batch_graph_create): the secondary-uncertainty portfolios share up to
+ * three launches, one for each pass that their rows ask for (ARA_PASS_LEAN,
+ * ARA_PASS_ITERATE, ARA_PASS_FULL); those large enough for ara_run's event-table
+ * form, and the primary-uncertainty ones, run ara_run's passes after them, to
+ * which trial_tile, waves_per_cu and order do not apply.  d_ylt_layers /
  * d_ylt_portfolio are host arrays of n_portfolios device pointers (entries
  * may be NULL), laid out as for ara_run over opts->trial_count trials.
  * opts->d_hits / d_hit_chk must be NULL; its d_scratch is not used (the batch

@@ -147,7 +147,8 @@ __global__ __launch_bounds__(64) ARA_FULL_OCCUPANCY void k_ara_batch_full(BatchA
             const unsigned long long e = B.redo[r];
             const int p = (int)(e >> 32);
             const int64_t t = (int64_t)(e & 0xffffffffull);
-            if (p >= B.n_pf || t >= B.pfs[p].trial_count) {     // see k_ara_full
+            // (an entry that no lean pass of this batch wrote: scratch shared with another)
+            if (p >= B.n_pf || t >= B.pfs[p].trial_count) {
                 if (threadIdx.x == 0) report(B.status, ARA_E_INVALID_ARG, r, p, t);
                 continue;
             }

@@ -69,10 +69,8 @@ struct RowQ {
 // the index of the same row in the layer's per-row arrays (bits 5-31, so a
 // layer holds fewer than kRowFMaxRows rows) and 1 + the slot of the row's
 // Beta shape among the layer's shape tables, or 0 when it has none (bits
-// 0-4); cfrac is the two-normal mix weight.  A row with a slot takes its
-// Beta parameters (alpha, beta, log2 B(alpha, beta)) from the slot, which
-// holds exactly the values of its rows (they are functions of the shape
-// alone); a row without one reads them from the per-row arrays.
+// 0-4); cfrac is the two-normal mix weight.  A row without a slot reads its
+// Beta parameters from the per-row arrays.
 struct __attribute__((aligned(16))) RowF {
     float scale;
     uint32_t meta;
@@ -130,8 +128,9 @@ constexpr int kF64QuantileIters = 400;
 //    form z): segments of width 1/2 around i / 2, |i| <= kDevHalf, with the
 //    local coordinate d = 2 v - i.
 // Over FP32-evaluated draws of shapes across [1, 32]^2 the error is at most
-// 2.4e-7 (by draw) and 3.1e-7 (by deviate) of max(root, mean); a host
-// emulation of the iteration it replaced peaked at 1.6e-6 there.  Octaves and
+// 2.4e-7 (by draw) and 3.1e-7 (by deviate) of max(root, mean), its mean below
+// 5e-10 of the mean in the emulation (seg_fit); the iteration it replaced
+// peaked at 1.9e-6 and 6e-8 to 1.7e-7 in the mean of (1.5, 6) and (1, 32).  Octaves and
 // half-unit steps are the widest segments that degree 7 holds to that; most
 // draws fall in a few of them, so the 64 lanes of a batch touch a handful of
 // cache lines (a one-segment-per-lane gather over a larger table was slower
@@ -142,10 +141,8 @@ constexpr int kOctaves = 23;                 // p = 1 .. 2^23 - 1
 constexpr int kDevHalf = 11;
 constexpr int kDevSegs = 2 * kDevHalf + 1;
 constexpr float kDevMax = 5.7f;              // |v| the deviate segments serve
-// floats per slot: (alpha, beta, log2 B(alpha, beta), 0) in the first segment's
-// space, the octaves of the lower then the upper half, the deviate segments
-constexpr int kSlotOct = kSegCoefs;
-constexpr int kSlotDev = kSlotOct + 2 * kOctaves * kSegCoefs;
+// floats per slot: the octaves of the lower then the upper half, the deviate segments
+constexpr int kSlotDev = 2 * kOctaves * kSegCoefs;
 constexpr int kShapeStride = kSlotDev + kDevSegs * kSegCoefs;
 // after a portfolio's slots: Phi^-1(p 2^-24) by octave of p, the same segments
 constexpr int kNormFloats = kOctaves * kSegCoefs;

@@ -90,7 +90,7 @@ struct SuLaunch {
     uint64_t *hit_chk;
     Status *status;
     int32_t *redo;            // [trial_count] scratch: flags of trials handed to the full pass
-    int redo_grid;            // blocks of the second pass
+    int redo_grid;            // blocks of the full pass over the flags
     SuForm form;
     size_t lds;               // dynamic LDS of the lean pass (see su_lds)
     const LayerDev *h_layers; // host copies of the layers (the table form)
@@ -168,8 +168,6 @@ hipError_t launch_su(const SuLaunch &p, int mode, bool f64out, hipStream_t s);
 // form: the pass of the batch's portfolios (not SU_TABLE); lds: see su_lds
 hipError_t launch_batch(const BatchArgs &B, int mode, bool f64out, int grid, int redo_grid,
                         SuForm form, size_t lds, hipStream_t s);
-// exclusive prefix sum of p[0, n) in place (one block; also used by the
-// exceedance-curve sort for its digit counts)
 hipError_t launch_debug_philox(int64_t n, const uint32_t *ctr, uint64_t key, uint32_t *out,
                                hipStream_t s);
 hipError_t launch_debug_quantile(int64_t n, const float *a, const float *b, const double *z,

@@ -762,11 +762,7 @@ __global__ __launch_bounds__(kSlotSegs *kSegCoefs) void k_shape_tables(
     y[threadIdx.x] = slot_point(a, b, lnb, seg, q);
     __syncthreads();
     if ((int)threadIdx.x < kSlotSegs)
-        seg_fit(y + threadIdx.x * kSegCoefs, slot + kSlotOct + threadIdx.x * kSegCoefs);
-    // the Beta parameters of the slot's rows, as the row fit computes them
-    if (threadIdx.x == 0)
-        *reinterpret_cast<float4 *>(slot) =
-            make_float4((float)a, (float)b, (float)(lnb * 1.4426950408889634), 0.0f);
+        seg_fit(y + threadIdx.x * kSegCoefs, slot + threadIdx.x * kSegCoefs);
 }
 
 hipError_t launch_shape_collect(RowF *rowf, const RowQ *rowq, int64_t row_base, int64_t n_rows,

@@ -388,7 +388,7 @@ __device__ __forceinline__ bool su_layer(const SuArgs &A, const PhiloxKeys &keys
                     // continued fraction took 120: 12.75 -> 10.98 ms for
                     // 1.24e9 draws (1M trials, 16 ELTs), which the walk over
                     // the occurrences now sets; mixed rows, once redone
-                    // whole in the second pass, 3.93 -> 0.62 ms for 40,003
+                    // whole in a pass of their own, 3.93 -> 0.62 ms for 40,003
                     // trials.
                     const float *tab =
                         A.shape_tab + ((size_t)l * kShapeSlots + (shape - 1u)) * kShapeStride;

@@ -160,3 +160,30 @@ def test_mixed_rows_all_resident(ara):
         assert torch.equal(s["ylt"], r["ylt"][:, a:a + 1000])
     ara.free_portfolio(p)
     ara.free_yet(y)
+
+
+@pytest.mark.parametrize("n_elts,rows,layers,n,lam,want", [
+    (6, 3000, 4, 9000, 280, 0), (12, 12_000, 2, 5000, 1500, 0), (12, 12_000, 2, 8192, 1500, 1)])
+def test_layers_beyond_the_cache(ara, n_elts, rows, layers, n, lam, want):
+    """Runs whose layers' tables exceed a cache: with fewer wavefronts a CU, and at the
+    line of the event-table form (5,000 trials fill its second round to a fifth), the bits
+    of a slice, of the diagnostic pass and of a batch in both orders."""
+    n_cat = 250_007
+    yet, pf = table_case(n_cat, n_elts, rows, n, lam, layers)
+    print("layers beyond the cache", layers, n, flush=True)
+    y = ara.load_yet(yet)
+    p = ara.load_portfolio(pf, n_cat)
+    assert ara.debug_run_pass(y, p) == want
+    r = ara.run(y, p)
+    assert float(r["ylt"].max()) > 0
+    s = ara.run(y, p, trial_begin=n - 2000, trial_count=2000)
+    assert torch.equal(s["ylt"], r["ylt"][:, n - 2000:])
+    d = ara.run(y, p, diagnostics=True)
+    assert torch.equal(d["ylt"], r["ylt"]) and torch.equal(d["ylt_pf"], r["ylt_pf"])
+    v = ara.run(y, p, occ_view=True)
+    assert torch.equal(v["ylt"], r["ylt"])
+    for cfg in (None, (1, 0, 1)):
+        o = ara.run_batch(y, [p, p], cfg=cfg)
+        assert all(torch.equal(q["ylt"], r["ylt"]) for q in o)
+    ara.free_portfolio(p)
+    ara.free_yet(y)
