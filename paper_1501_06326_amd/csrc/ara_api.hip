@@ -193,7 +193,9 @@ SuForm su_form(const ara_context *ctx, const ara_yet *yet, const ara_portfolio *
 // Dynamic LDS of the lean pass' one-wavefront form, which it doesn't use: with it a CU
 // holds 21 wavefronts, not 32.  Each wavefront is in a layer of its own, and where what
 // they gather from together (bytes, of several layers) exceeds the 4 MB L2 of an XCD well,
-// more wavefronts miss it more; not where all trials are resident at once.  Eight / six /
+// more wavefronts miss it more; not where all trials are resident at once, nor with mixed
+// rows, whose dependent loads want the wavefronts (a batch of 4 of 2 layers, 300 x 25,000,
+// trial-major 500 us at eight, 548 at five).  Eight / six /
 // five per SIMD: 4 layers of 250,000 events (8 MB), 300 x 16,384 152 / 125 / 134 us, 1000 x
 // 16,384 514 / 405 / 371; 8 of 100,000 (6.5 MB), 300 x 40,000 717 / 565 / 537, batches of 4 such, 300 x
 // 8,000 699 / 594 / 512; 2 of 250,000 (4.4 MB) 300 x 12,288 67 / - / 70, 4 of 100,000 (3.2
@@ -237,7 +239,7 @@ SuLaunch su_launch(const ara_context *ctx, const ara_yet *yet, const ara_portfol
     p.evtab = pf->d_evtab;
     p.n_cat = pf->n_catalogue;
     p.n_cu = ctx->n_cu;
-    p.lds = su_lds(ctx, yet, su_bytes(pf), pf->n_layers > 1, o.trial_count,
+    p.lds = su_lds(ctx, yet, su_bytes(pf), pf->n_layers > 1 && !(pf->all_flags & ROW_CORR), o.trial_count,
                    o.d_hits || o.d_hit_chk);
     return p;
 }
@@ -1162,7 +1164,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         return fail(ctx, ARA_E_INVALID_ARG, "ara_run_batch: trial-major order needs one trial range");
     int64_t total = 0, listed = 0, items[3] = {0, 0, 0};
     double gathered[3] = {0.0, 0.0, 0.0};
-    bool several[3] = {false, false, false};
+    bool several[3] = {false, false, false}, mixed[3] = {false, false, false};
     int64_t trials[3] = {0, 0, 0};
     std::vector<BatchPf> hs[3];    // see kBatchForms
     plan->pu.clear();
@@ -1193,6 +1195,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
         // what wavefronts gather from at a time: a portfolio's, or in trial-major order all
         const double more = su_bytes(p);
         several[k] = several[k] || p->n_layers > 1 || (c.order == ARA_BATCH_TRIAL_MAJOR && !hs[k].empty());
+        mixed[k] = mixed[k] || (p->all_flags & ROW_CORR);
         trials[k] += tc;
         gathered[k] = c.order == ARA_BATCH_TRIAL_MAJOR ? gathered[k] + more : std::max(gathered[k], more);
         hs[k].emplace_back();
@@ -1233,7 +1236,7 @@ ara_status prep_batch_ranges(ara_context *ctx, const ara_yet *yet, int32_t n,
     for (int k = 0; k < 3; ++k) {
         BatchArgs &B = plan->B[k];
         const int32_t n_su = (int32_t)hs[k].size();
-        plan->lds[k] = su_lds(ctx, yet, gathered[k], several[k], trials[k], false);
+        plan->lds[k] = su_lds(ctx, yet, gathered[k], several[k] && !mixed[k], trials[k], false);
         B.off = yet->d_off;
         B.ev = yet->d_ev;
         B.trial_begin = trial_major ? o.trial_begin : 0;
