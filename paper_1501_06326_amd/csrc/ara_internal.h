@@ -141,9 +141,10 @@ constexpr int kOctaves = 23;                 // p = 1 .. 2^23 - 1
 constexpr int kDevHalf = 11;
 constexpr int kDevSegs = 2 * kDevHalf + 1;
 constexpr float kDevMax = 5.7f;              // |v| the deviate segments serve
-// floats per slot: the octaves of the lower then the upper half, the deviate segments
-constexpr int kSlotDev = 2 * kOctaves * kSegCoefs;
-constexpr int kShapeStride = kSlotDev + kDevSegs * kSegCoefs;
+// A slot's segments: the octaves of the lower half, of the upper half, the deviates, each
+// from a 128-byte line on, so that the octaves of seven draws in eight share a line a half.
+constexpr int kSegUpper = 24, kSegDev = 48;
+constexpr int kShapeStride = 72 * kSegCoefs;     // floats
 // after a portfolio's slots: Phi^-1(p 2^-24) by octave of p, the same segments
 constexpr int kNormFloats = kOctaves * kSegCoefs;
 

@@ -761,8 +761,12 @@ __global__ __launch_bounds__(kSlotSegs *kSegCoefs) void k_shape_tables(
     const double lnb = lgamma(a) + lgamma(b) - lgamma(a + b);
     y[threadIdx.x] = slot_point(a, b, lnb, seg, q);
     __syncthreads();
-    if ((int)threadIdx.x < kSlotSegs)
-        seg_fit(y + threadIdx.x * kSegCoefs, slot + threadIdx.x * kSegCoefs);
+    const int s = threadIdx.x;
+    if (s < kSlotSegs) {
+        const int at = s < kOctaves ? s : s < 2 * kOctaves ? kSegUpper + s - kOctaves
+                                                           : kSegDev + s - 2 * kOctaves;
+        seg_fit(y + s * kSegCoefs, slot + at * kSegCoefs);
+    }
 }
 
 hipError_t launch_shape_collect(RowF *rowf, const RowQ *rowq, int64_t row_base, int64_t n_rows,

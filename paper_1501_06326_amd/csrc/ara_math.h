@@ -195,14 +195,14 @@ __device__ __forceinline__ float grid_tail(uint32_t j) {
 __device__ __forceinline__ uint32_t slot_segment(uint32_t j, float *d) {
     bool upper;
     const int e = grid_octave(j, &upper, d);
-    return (uint32_t)(kSegCoefs * (e + (upper ? kOctaves : 0)));
+    return (uint32_t)(kSegCoefs * (e + (upper ? kSegUpper : 0)));
 }
 
 // The same of a normal deviate v, |v| <= kDevMax.
 __device__ __forceinline__ uint32_t dev_segment(float v, float *d) {
     const float i = rintf(2.0f * v);
     *d = fmaf(2.0f, v, -i);
-    return (uint32_t)(kSlotDev + kSegCoefs * min(max((int)i + kDevHalf, 0), kDevSegs - 1));
+    return (uint32_t)(kSegCoefs * (kSegDev + min(max((int)i + kDevHalf, 0), kDevSegs - 1)));
 }
 
 // The quantile of a slot's shape at the draw z = j 2^-24.
