@@ -76,10 +76,10 @@ PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 #    for an elementwise kernel that reads and writes 1 GiB (FETCH 2.0,
 #    WRITE 1.0).
 PROFILED = {
-    "sources_sha256": "2560ea3cab51c6132108b853f4f610dddc59247bef8a4625797daa0897a96425",
-    "draw_arith_ops": 33.0,         # profiles/ara_probes_valu_stream_draws.md (k_probe_draws)
-    "su_main_bytes": 4.1504e9 + 8.139e7,     # k_ara_su_tab: fetch + write, 1M trials
-    "pu_bytes": 4.0935e9 + 9.702e6,          # k_ara_pu: fetch + write, 1M trials
+    "sources_sha256": "d84fe2a474cd47068f1aa3066a4af0b2fc07156166afc7a2ba40e1df922f8685",
+    "draw_arith_ops": 32.0,         # profiles/ara_probes_valu_stream_draws.md (k_probe_draws)
+    "su_main_bytes": 4.1507e9 + 8.156e7,     # k_ara_su_tab: fetch + write, 1M trials
+    "pu_bytes": 4.0937e9 + 9.707e6,          # k_ara_pu: fetch + write, 1M trials
 }
 
 

@@ -157,7 +157,7 @@ __device__ __forceinline__ void occ_quads(float4 o, bool valid, int64_t pos, con
 // Bound, at 1M trials x 1,000 occurrences (4 GB of ids): one table of up to 78 KB
 // by the id stream (671 us, 5.9 TB/s).  Tables beyond that by the LDS lookups and
 // the one block per CU, which is still far ahead of a scattered load of a line
-// per occurrence (300,007 trials x 1,000 occurrences, 1M events: 320 us against
+// per occurrence (300,007 trials x 1,000 occurrences, 1M events: 289 us against
 // 1.60 ms).  Layers taken together read the ids once and pay for the staging
 // once: 8 layers, 100,003 trials x 1,000, FP64 sums, 490 - 680 us by the draw of
 // their tables, one by one 650 - 770 us, by scattered loads where a table passed
