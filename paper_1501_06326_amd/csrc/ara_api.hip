@@ -129,9 +129,9 @@ double su_bytes(const ara_portfolio *pf) {
 //    763 / 326; 4 layers of 250,000 events: 300 x 16,384 153 / 163 (0.07 hits) and 407 / 288
 //    (2.9), 1000 x 4,096 103 / 113 and 241 / 234, 1000 x 16,384 516 / 316 and 1339 / 740; 3 of
 //    100,000 events, 3.2 hits: 300 x 32,768 377 / 378, 1000 x 16,384 559 / 500.  The line is
-//    where bytes times occurrences pay for the layers' launches, less what the last round
-//    of trials leaves idle: 2 layers of 250,000 events, 0.6 hits, 1500 x 4,096 91 / 82, 5,000
-//    106 / 129, 8,192 174 / 135.
+//    where bytes times occurrences pay for the layers' launches, less what the last trials
+//    leave idle: 2 layers of 250,000 events, 0.6 hits, 1500 x 4,096 91 / 82, 5,000 106 /
+//    129, 8,192 174 / 135.
 //  * within it, the ids beyond the 256 MB last-level cache, so that the form's ids a segment
 //    ahead count: 1 layer of 250,000 events lam 520 x 200,000 638 / 547; of 100,000 events,
 //    3.2 hits, 640 x 262,144 1708 / 1668, 520 x 262,144 1414 / 1437, 1000 x 1M 9.8 / 8.5 ms.
@@ -147,9 +147,9 @@ bool su_table_form(const ara_context *ctx, const ara_yet *yet, const ara_portfol
     const int64_t mean_len = su_mean_len(yet);
     const double occ = (double)trials * (double)mean_len;
     if (su_bytes(pf) > kL2) {
-        // (of the last round of trials, one to each resident wavefront, only part is filled)
-        const int64_t slots = (int64_t)ctx->n_cu * kTabWaves, rounds = (trials + slots - 1) / slots;
-        const double fill = (double)trials / (double)(rounds * slots);
+        // (the wavefronts take a trial each at a time: the share of them that the last time fills)
+        const int64_t slots = (int64_t)ctx->n_cu * kTabWaves, times = (trials + slots - 1) / slots;
+        const double fill = (double)trials / (double)(times * slots);
         return mean_len >= kSeg / 2 && occ * fill * su_bytes(pf) >= 3.75e6 * kL2 * pf->n_layers;
     }
     if (4.0 * occ > 64.0 * kL2)
